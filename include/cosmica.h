@@ -333,9 +333,11 @@ void cosmica_plan_destroy(cosmica_plan* plan);
 cosmica_status cosmica_run_static(cosmica_ctx* ctx, const cosmica_job* jobs, int32_t n_jobs,
                                   cosmica_precision precision, cosmica_result* results);
 
-/* Launch shape used for (model, precision); the defaults come from the
- * autotuner cache when one was loaded, else built-in values (256 threads, full
- * residency, 32-particle chunks, order 2). */
+/* Launch shape used for (model, precision).  Until one is set here or by the
+ * tuner, the library picks it per pass: built-in values (256 threads, full
+ * residency, 32-particle chunks, order 2), or, where the expected work says that
+ * the longest path and not the throughput bounds the pass, a kernel for few
+ * waves per SIMD.  Results are the same bit for bit. */
 cosmica_status cosmica_set_launch(cosmica_ctx* ctx, cosmica_model model,
                                   cosmica_precision precision, const cosmica_launch* cfg);
 cosmica_status cosmica_get_launch(cosmica_ctx* ctx, cosmica_model model,

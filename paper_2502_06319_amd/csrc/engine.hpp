@@ -140,6 +140,8 @@ struct PropArgs {
     uint32_t shaped;              // 1: some job of the launch has a squashed boundary or a heliosheath
     uint32_t energy;              // 1: some job of the launch is in the energy form
     uint32_t key_lo, key_hi;
+    uint32_t latency;             // 1: run the kernel for few particles per SIMD
+    uint32_t lane_cap;            // lanes a wave of that kernel fills (1..64)
     const uint32_t* job_cancel;   // optional per-job cancel flags
     uint32_t* job_done;           // optional per-job count of finished particles
 };

@@ -8,6 +8,8 @@
 //   its idle lanes by ballot rank, so waves stay full until the queue drains.
 //   R = double is the plain FP64 path; R = float is the mixed path (bulk FP32
 //   with the hardware transcendentals, r / t / P accumulated in FP64).
+//   Two kernels: k_propagate at full residency for throughput, k_latency with
+//   few waves per SIMD for passes that the longest path bounds.
 //   Variants per launch: surface tests (nose-squashed heliosphere with a
 //   heliosheath, Sec. II.B) and the energy form (Eq.(1), with the loss of
 //   Eq.(4)).
@@ -477,16 +479,13 @@ __device__ __forceinline__ bool outside_turn(float x)
 }
 __device__ __forceinline__ bool outside_turn(double x) { return !(x >= 0.0 && x < kTwoPi); }
 
-// One EM step of the 3D model.  The caller tests for the exit.
-template <typename R, bool UKEY, bool SHAPED, bool ENERGY>
-__device__ __forceinline__ void step3d(const JobReg<R>& J, const JobDev<R>* __restrict__ jd,
-                                       const RegionRef<R> reg, PState<R>& s,
-                                       uint32_t pid, uint32_t bin, uint32_t k0, uint32_t k1)
+// One EM step of the 3D model with the normals z and the particle's region
+// entry g.  The caller applies the reflections and tests for the exit.
+template <typename R, bool ENERGY>
+__device__ __forceinline__ void step3d(const JobReg<R>& J, const RegionDev<R>& g, PState<R>& s,
+                                       const R* z)
 {
     using M = Mth<R>;
-    R z[3];
-    normals<R, 3>(UKEY ? k0 : J.seed_lo, UKEY ? k1 : J.seed_hi, s.n, pid, bin, J.job_tag, z);
-    const RegionDev<R> g = reg.at(region_at<R, SHAPED>(J, jd, s.r, s.th, s.ph));
     const bool efo = ENERGY && J.energy != 0;
     R Pc = (R)s.P;  // the rigidity the coefficients see
     if (efo) {
@@ -519,6 +518,33 @@ __device__ __forceinline__ void step3d(const JobReg<R>& J, const JobDev<R>* __re
         ph1 = s.ph + c.Ap * dt + (c.Bpr * z[0] + c.Bpp * z[1]) * sdt * (c.invr * c.invst);
         P1 = s.P + c.AP * dt;
     }
+    if (efo) {
+        // (1/3) div V, alpha T and the loss at the start of the step
+        const R T = (R)s.T, Mr = J.mass;
+        const R divV3 = ((R)2.0 / (R)3.0) * c.V * c.invr;
+        const R ie = M::rcp(T + Mr);
+        const R alphaT = ((T + (R)2.0 * Mr) * ie) * T;
+        const R me = Mr * ie;
+        const R L = divV3 * ((R)2.0 - me * me);  // (div V) (1 - (1 + me^2) / 3)
+        s.T = s.T + (double)(divV3 * alphaT * dt);
+        s.lam = s.lam + (double)(L * dt);
+        P1 = s.P;  // the rigidity is refreshed from T when the particle leaves
+    }
+    s.r = r1;
+    s.th = th1;
+    s.ph = ph1;
+    s.P = P1;
+    s.t = s.t + (double)dt;
+    s.n = s.n + 1u;
+}
+
+// Reflections of a step through the origin and the poles, and phi modulo 2 pi.
+template <typename R>
+__device__ __forceinline__ void reflect3d(PState<R>& s)
+{
+    using M = Mth<R>;
+    double r1 = s.r;
+    R th1 = s.th, ph1 = s.ph;
     // reflections through the origin and the poles are rare: a wave branches
     // to them only when one of its lanes needs them
     if (__builtin_amdgcn_ballot_w64(r1 < 0.0) != 0) {
@@ -547,36 +573,73 @@ __device__ __forceinline__ void step3d(const JobReg<R>& J, const JobDev<R>* __re
         ph1 = M::fmod2pi(ph1);
         if (ph1 < (R)0) ph1 = ph1 + (R)kTwoPi;
     }
-    if (efo) {
-        // (1/3) div V, alpha T and the loss at the start of the step
-        const R T = (R)s.T, Mr = J.mass;
-        const R divV3 = ((R)2.0 / (R)3.0) * c.V * c.invr;
-        const R ie = M::rcp(T + Mr);
-        const R alphaT = ((T + (R)2.0 * Mr) * ie) * T;
-        const R me = Mr * ie;
-        const R L = divV3 * ((R)2.0 - me * me);  // (div V) (1 - (1 + me^2) / 3)
-        s.T = s.T + (double)(divV3 * alphaT * dt);
-        s.lam = s.lam + (double)(L * dt);
-        P1 = s.P;  // the rigidity is refreshed from T when the particle leaves
-    }
     s.r = r1;
     s.th = th1;
     s.ph = ph1;
-    s.P = P1;
-    s.t = s.t + (double)dt;
-    s.n = s.n + 1u;
+}
+
+// phi modulo 2 pi, and all of the above, without branches: for a wave known to
+// need some of them.
+__device__ __forceinline__ float turn_select(float ph)
+{
+    float w = Mth<float>::fmod2pi(ph);
+    w = w < 0.0f ? w + (float)kTwoPi : w;
+    return outside_turn(ph) ? w : ph;
+}
+__device__ __forceinline__ double turn_select(double ph)
+{
+    if (outside_turn(ph)) {
+        ph = Mth<double>::fmod2pi(ph);
+        if (ph < 0.0) ph = ph + kTwoPi;
+    }
+    return ph;
+}
+__device__ __forceinline__ void reflect3d_select(PState<float>& s)
+{
+    using M = Mth<float>;
+    const bool back = s.r < 0.0;
+    s.r = back ? -s.r : s.r;
+    float th = back ? (float)kPi - s.th : s.th;
+    float ph = back ? s.ph + (float)kPi : s.ph;
+    const bool north = th < 0.0f;
+    th = north ? -th : th;
+    ph = north ? ph + (float)kPi : ph;
+    const float thm = M::fmod2pi(th);
+    const bool wrap = th > (float)kPi;
+    const bool south = wrap && thm > (float)kPi;
+    th = wrap ? thm : th;
+    th = south ? (float)kTwoPi - th : th;
+    ph = south ? ph + (float)kPi : ph;
+    s.th = th;
+    s.ph = turn_select(ph);
+}
+__device__ __forceinline__ void reflect3d_select(PState<double>& s) { reflect3d(s); }
+
+// r outside [0, limit) (or -0, or NaN), by the same order of the bit patterns.
+__device__ __forceinline__ bool outside_range(double r, double limit)
+{
+    return (unsigned long long)__double_as_longlong(r) >=
+           (unsigned long long)__double_as_longlong(limit);
+}
+
+// theta outside [0, pi] (or -0, or NaN): non-negative floats order like their
+// bit patterns, and every pattern with the sign bit set lies above them.
+__device__ __forceinline__ bool outside_half_turn(float x)
+{
+    return __float_as_uint(x) > __float_as_uint((float)kPi);
+}
+__device__ __forceinline__ bool outside_half_turn(double x)
+{
+    return (unsigned long long)__double_as_longlong(x) >
+           (unsigned long long)__double_as_longlong(kPi);
 }
 
 // One EM step of the radial model: dr = (2k/r - V) ds + sqrt(2k) dW.
-template <typename R, bool UKEY>
-__device__ __forceinline__ void step1d(const JobReg<R>& J, const RegionRef<R> reg,
-                                       PState<R>& s, uint32_t pid, uint32_t bin, uint32_t k0,
-                                       uint32_t k1)
+template <typename R>
+__device__ __forceinline__ void step1d(const JobReg<R>& J, const RegionDev<R>& g, PState<R>& s,
+                                       const R* z)
 {
     using M = Mth<R>;
-    R z[1];
-    normals<R, 1>(UKEY ? k0 : J.seed_lo, UKEY ? k1 : J.seed_hi, s.n, pid, bin, J.job_tag, z);
-    const RegionDev<R> g = reg.at(region_of(J, s.r));
     const R r0 = (R)s.r;
     const R r = r0 > M::kRFloor ? r0 : M::kRFloor;
     const R P = (R)s.P;
@@ -615,11 +678,38 @@ __device__ __forceinline__ uint32_t wave_uniform(uint32_t v)
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
 
-// The binary32 energy-form variants are held to 128 VGPRs (4 waves per SIMD).
-template <typename R, bool M3D, bool UKEY, bool SHAPED, bool ENERGY>
-__global__ void __launch_bounds__(256, ((std::is_same<R, float>::value && M3D) ? (ENERGY ? 4 : 1) : 1))
-k_propagate(const PropArgs<R> a)
+// The LDS operations of a wave are performed in order; this keeps the compiler
+// from moving them past each other.
+__device__ __forceinline__ void wave_lds_order()
 {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// The value that lane src holds.
+template <typename T>
+__device__ __forceinline__ void from_lane(T& v, int src)
+{
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    uint32_t w[sizeof(T) / 4];
+    __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+    for (uint32_t k = 0; k < sizeof(T) / 4; ++k) w[k] = (uint32_t)__shfl((int)w[k], src, 64);
+    __builtin_memcpy(&v, w, sizeof(T));
+}
+
+// A wave with at most this many particles and nothing to refill its idle lanes
+// with draws random numbers ahead on them: at least 4 lanes a particle.  With 2
+// lanes each (17 to 32 particles) a step took as long as without (0.61 us, 3D
+// binary32), and 16 region tables of 0.5 or 1 KB a wave fit LDS.
+constexpr uint32_t kTailLanes = 16;
+
+template <typename R, bool M3D, bool UKEY, bool SHAPED, bool ENERGY, bool TAIL>
+__device__ __forceinline__ void propagate(const PropArgs<R>& a)
+{
+    constexpr int kNormals = M3D ? 3 : 1;  // random numbers of a step
+    // per wave: random numbers drawn ahead, and region tables
+    __shared__ R tail_z[TAIL ? 4 : 1][TAIL ? 64 * kNormals : 1];
+    __shared__ RegionDev<R> tail_tab[TAIL ? 4 : 1][TAIL ? kTailLanes * kRegionStride : 1];
     const uint32_t lane = __lane_id();
     PState<R> s = {0.0, 0.0, 0.0, (R)0, (R)0, 0u, 0.0, 0.0};
     uint32_t pid = 0, bin = 0, job = 0, out = 0, seg = 0;
@@ -647,12 +737,18 @@ k_propagate(const PropArgs<R> a)
     bool queue_open = true;
     bool launch_open = true;  // false once this wave used its step budget
 
+    // Lanes this wave may still fill.
+    auto room = [&]() -> uint32_t {
+        if constexpr (TAIL) return a.lane_cap - (uint32_t)__popcll(__ballot(active));
+        return 64u;
+    };
+
     for (;;) {
         uint64_t need = __ballot(!active);
         // 1) suspended particles of earlier slices come back first
-        while (need != 0 && resume_open && launch_open) {
+        while (need != 0 && resume_open && launch_open && room() != 0) {
             uint32_t base = 0;
-            const uint32_t cnt = (uint32_t)__popcll(need);
+            const uint32_t cnt = min((uint32_t)__popcll(need), room());
             if (lane == 0) base = atomicAdd(sv->resume_head, cnt);
             base = wave_uniform(base);
             // (a count past the list's capacity only follows an overflow,
@@ -663,7 +759,7 @@ k_propagate(const PropArgs<R> a)
                 break;
             }
             const uint32_t rank = lane_rank(need);
-            if (!active && base + rank < n_resume) {
+            if (!active && rank < cnt && base + rank < n_resume) {
                 // kernels without the energy form leave T and the loss unread
                 const uint32_t i = base + rank;
                 const ParkDev& q = sv->resume;
@@ -693,7 +789,7 @@ k_propagate(const PropArgs<R> a)
             need = __ballot(!active);
         }
         // 2) new particles from the chunk queue
-        while (need != 0 && !resume_open && queue_open && launch_open) {
+        while (need != 0 && !resume_open && queue_open && launch_open && room() != 0) {
             if (c_next == c_end) {
                 // remainders the previous slice left unissued go first
                 ChunkDev ch;
@@ -725,7 +821,7 @@ k_propagate(const PropArgs<R> a)
                 c_end = c_next + wave_uniform(ch.count);
             }
             const SegmentDev sg = a.segs[c_seg];
-            const uint32_t avail = c_end - c_next;
+            const uint32_t avail = min(c_end - c_next, room());
             const uint32_t rank = lane_rank(need);
             if (!active && rank < avail) {
                 const JobDev<R>& Jd = a.jobs[sg.job];
@@ -808,10 +904,16 @@ k_propagate(const PropArgs<R> a)
             for (;;) {
                 bool leave = false;
                 if (active) {
-                    if (M3D)
-                        step3d<R, SK, SHAPED, ENERGY>(J, jd, reg, s, pid, bin, k0, k1);
-                    else
-                        step1d<R, SK>(J, reg, s, pid, bin, k0, k1);
+                    R z[kNormals];
+                    normals<R, kNormals>(SK ? k0 : J.seed_lo, SK ? k1 : J.seed_hi, s.n, pid, bin,
+                                         J.job_tag, z);
+                    const RegionDev<R> g = reg.at(region_at<R, SHAPED>(J, jd, s.r, s.th, s.ph));
+                    if constexpr (M3D) {
+                        step3d<R, ENERGY>(J, g, s, z);
+                        reflect3d<R>(s);
+                    } else {
+                        step1d<R>(J, g, s, z);
+                    }
                     leave = outside_boundary<R, SHAPED>(J, jd, s.r, s.th, s.ph) ||
                             s.n >= J.step_cap;
                 }
@@ -843,7 +945,156 @@ k_propagate(const PropArgs<R> a)
                     lockstep(std::false_type{}, sl);
             }
         };
-        if (sliced)
+        // The step loop of a launch with few waves per SIMD, where a step takes its
+        // own latency.  A wave that issues alone was measured to pay 4.2 cycles per
+        // VALU instruction (dependent or not), 8 per transcendental and 30 to 50 per
+        // compare-and-branch, so the rare events of a step (reflections, phi past a
+        // turn, the exit) share one test.  One particle, us per step, the throughput
+        // kernel's loop and this one: 3D binary32 0.603 and 0.397, binary64 2.56 and
+        // 1.56; radial 0.261 and 0.144, 0.724 and 0.315.  With 64 particles a wave:
+        // 0.609 and 0.547, 2.70 and 2.56, 0.266 and 0.228, 0.734 and 0.571.
+        // Idle lanes hold copies of the wave's particles, so every lane runs the loop
+        // and its control flow is the wave's.
+        // AHEAD: the wave has few particles and nothing to refill it with; they move
+        // to the first lanes of groups of `ahead`, whose lanes draw the random
+        // numbers of the next `ahead` steps at once.  These and the region tables
+        // stay in LDS.
+        auto tail = [&](auto ah, auto sl) {
+            constexpr bool AHEAD = decltype(ah)::value;
+            constexpr bool SL = decltype(sl)::value;
+            constexpr bool WRAP = M3D && !AHEAD && std::is_same<R, float>::value;
+            const uint64_t act = __builtin_amdgcn_ballot_w64(active);
+            const uint32_t na = (uint32_t)__popcll(act);
+            const uint32_t lgk =
+                AHEAD ? 6u - (na > 1u ? 32u - (uint32_t)__builtin_clz(na - 1u) : 0u) : 0u;
+            const uint32_t ahead = 1u << lgk;
+            const uint32_t sub = lane & (ahead - 1u);  // this lane's place in its group
+            const uint32_t of = min(lane >> lgk, na - 1u);
+            int src = active ? (int)lane : (int)__builtin_ctzll(act);
+            R* const zw = tail_z[threadIdx.x >> 6];
+            const RegionDev<R>* const tab = tail_tab[threadIdx.x >> 6] + kRegionStride * of;
+            if constexpr (AHEAD) {
+                uint32_t* const lane_of = (uint32_t*)zw;
+                if (active) lane_of[lane_rank(act)] = lane;
+                wave_lds_order();
+                src = (int)lane_of[of];
+                wave_lds_order();
+                active = sub == 0 && (lane >> lgk) < na;
+            }
+            from_lane(s, src);
+            from_lane(J, src);
+            from_lane(pid, src);
+            from_lane(bin, src);
+            from_lane(seg, src);
+            from_lane(out, src);
+            from_lane(job, src);
+            jd = a.jobs + job;
+            reg.off = job * (uint32_t)(kRegionStride * sizeof(RegionDev<R>));
+            // steps until a lane reaches its cap or the slice its budget
+            uint32_t left = J.step_cap - s.n;
+            for (int o = 32; o > 0; o >>= 1) left = min(left, (uint32_t)__shfl_xor((int)left, o, 64));
+            left = wave_uniform(left);
+            if (SL) left = min(left, a.step_budget - wave_steps);
+            if constexpr (AHEAD) {
+                // the tables, one after the other, a 64th by each lane
+                constexpr uint32_t kPart = kRegionStride * sizeof(RegionDev<R>) / 64;
+                struct alignas(8) Part { uint32_t w[kPart / 4]; };
+                Part* const dst = (Part*)tail_tab[threadIdx.x >> 6];
+                for (uint32_t j = 0; j < na; ++j) {
+                    const uint32_t off =
+                        (uint32_t)__builtin_amdgcn_readlane((int)reg.off, (int)(j << lgk));
+                    dst[64 * j + lane] = ((const Part*)((const char*)reg.base + off))[lane];
+                }
+                wave_lds_order();
+            }
+            uint32_t zn = s.n + sub;  // the step this lane draws for next
+            const R* zr = zw + (of << lgk);
+            auto region = [&](int k) -> RegionDev<R> {
+                if constexpr (AHEAD) return tab[k];
+                return reg.at(k);
+            };
+            // The region of the next step, loaded as soon as r is known (a reflection
+            // through the origin only changes its sign).
+            RegionDev<R> g = region(region_at<R, SHAPED>(J, jd, s.r, s.th, s.ph));
+            for (bool stop = false; !stop;) {
+                uint32_t m = left;
+                if constexpr (AHEAD) {
+                    R z[kNormals];
+                    normals<R, kNormals>(UKEY ? k0 : J.seed_lo, UKEY ? k1 : J.seed_hi, zn, pid, bin,
+                                         J.job_tag, z);
+                    wave_lds_order();
+                    for (int c = 0; c < kNormals; ++c) zw[64 * c + lane] = z[c];
+                    zn += ahead;
+                    wave_lds_order();
+                    m = min(m, ahead);
+                } else if (SL) {
+                    m = min(m, 16u);
+                }
+                m = wave_uniform(m);
+                uint32_t i = 0;
+                for (bool on = true; on;) {
+                    uint64_t out_of, event;
+                    bool far;
+                    __asm__ volatile("");  // keeps the two loops apart
+                    do {
+                        R z[kNormals];
+                        if constexpr (AHEAD)
+                            for (int c = 0; c < kNormals; ++c) z[c] = zr[64 * c + i];
+                        else
+                            normals<R, kNormals>(UKEY ? k0 : J.seed_lo, UKEY ? k1 : J.seed_hi, s.n,
+                                                 pid, bin, J.job_tag, z);
+                        ++i;
+                        if constexpr (M3D)
+                            step3d<R, ENERGY>(J, g, s, z);
+                        else
+                            step1d<R>(J, g, s, z);
+                        int k = region_of(J, fabs(s.r));
+                        if (SHAPED) k = s.r >= J.ts_tail ? kRegionHeliosheath : k;
+                        g = region(k);
+                        far = outside_range(s.r, J.rb);
+                        if (SHAPED) far |= s.r >= J.ts_nose && s.r < J.ts_tail;
+                        if constexpr (M3D) far |= outside_half_turn(s.th);
+                        out_of = __builtin_amdgcn_ballot_w64(far);
+                        event = out_of | (i == m ? ~0ull : 0ull);
+                        if constexpr (WRAP)
+                            s.ph = far ? s.ph : turn_select(s.ph);
+                        else if constexpr (M3D)
+                            event |= __builtin_amdgcn_ballot_w64(outside_turn(s.ph));
+                    } while (event == 0);
+                    on = i != m;
+                    // (phi modulo 2 pi is taken once a step: the result may be 2 pi)
+                    if (M3D && !WRAP && out_of == 0) s.ph = turn_select(s.ph);
+                    if (out_of != 0) {
+                        const R ph = s.ph;
+                        if constexpr (M3D) reflect3d_select(s);
+                        if (WRAP && !far) s.ph = ph;
+                        on = on && __builtin_amdgcn_ballot_w64(outside_boundary<R, SHAPED>(
+                                       J, jd, s.r, s.th, s.ph)) == 0;
+                        if (SHAPED) g = region(region_at<R, SHAPED>(J, jd, s.r, s.th, s.ph));
+                    }
+                }
+                wave_steps += i;
+                left = wave_uniform(left - i);
+                stop = left == 0 || __builtin_amdgcn_ballot_w64(outside_boundary<R, SHAPED>(
+                                        J, jd, s.r, s.th, s.ph)) != 0;
+                if constexpr (SL) {
+                    if (wave_steps >= a.step_budget || (uint64_t)wall_clock64() >= t_stop)
+                        slice_over = stop = true;
+                }
+            }
+        };
+        if constexpr (TAIL) {
+            const bool few = (!queue_open || room() == 0) &&
+                             (uint32_t)__popcll(__ballot(active)) <= kTailLanes;
+            if (few && sliced)
+                tail(std::true_type{}, std::true_type{});
+            else if (few)
+                tail(std::true_type{}, std::false_type{});
+            else if (sliced)
+                tail(std::false_type{}, std::true_type{});
+            else
+                tail(std::false_type{}, std::false_type{});
+        } else if (sliced)
             keyed(std::true_type{});
         else
             keyed(std::false_type{});
@@ -906,11 +1157,32 @@ k_propagate(const PropArgs<R> a)
     }
 }
 
+// The binary32 energy-form variants are held to 128 VGPRs (4 waves per SIMD).
+template <typename R, bool M3D, bool UKEY, bool SHAPED, bool ENERGY>
+__global__ void __launch_bounds__(256, ((std::is_same<R, float>::value && M3D) ? (ENERGY ? 4 : 1) : 1))
+k_propagate(const PropArgs<R> a)
+{
+    propagate<R, M3D, UKEY, SHAPED, ENERGY, false>(a);
+}
+
+template <typename R, bool M3D, bool UKEY, bool SHAPED, bool ENERGY>
+__global__ void __launch_bounds__(256, (std::is_same<R, float>::value ? 2 : 1))
+k_latency(const PropArgs<R> a)
+{
+    propagate<R, M3D, UKEY, SHAPED, ENERGY, true>(a);
+}
+
 template <typename R, bool M3D, bool SHAPED, bool ENERGY>
 static void launch_keyed(const PropArgs<R>& a, int grid, int block, hipStream_t s)
 {
     // one Philox key for the whole launch: the key schedule runs on the scalar unit
-    if (a.uniform_key)
+    if (a.uniform_key && a.latency)
+        hipLaunchKernelGGL((k_latency<R, M3D, true, SHAPED, ENERGY>), dim3(grid), dim3(block), 0,
+                           s, a);
+    else if (a.latency)
+        hipLaunchKernelGGL((k_latency<R, M3D, false, SHAPED, ENERGY>), dim3(grid), dim3(block), 0,
+                           s, a);
+    else if (a.uniform_key)
         hipLaunchKernelGGL((k_propagate<R, M3D, true, SHAPED, ENERGY>), dim3(grid), dim3(block),
                            0, s, a);
     else

@@ -402,6 +402,9 @@ struct cosmica_ctx {
     int wall_khz = 0;  // rate of the device's constant-rate clock [kHz]
     std::string arch;
     cosmica_launch launch[2][2];
+    // no caller and no tuner has chosen the launch shape: the library picks the
+    // kernel and the number of waves from the work of each pass
+    bool auto_launch[2][2] = {{true, true}, {true, true}};
     cosmica_timings timings{};
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     // steps of the last execution: device array and its length
@@ -517,7 +520,7 @@ struct DevSet {
 };
 
 // Expected Euler-Maruyama steps per particle of one (job, bin), used only to
-// order the work queue.  Particles whose drift runs against the Parker
+// order the work queue and to choose the launch.  Particles whose drift runs against the Parker
 // spiral's polarity (sign(Z) A < 0, Eq.(3)'s drift term) ride the wavy current
 // sheet: 10^3-10^5 steps, more the wavier the sheet, so the shells' mean tilt
 // sets their cost; the others take 300-600 steps, weakly dependent on
@@ -525,19 +528,23 @@ struct DevSet {
 // measured mean steps per bin of the batched workload (64 parameter sets x 4
 // species x 30 bins, seed 42); on an independent draw of that workload
 // (seed 43) the estimate ranks the bins with a Spearman correlation of 0.93.
+// A heliosheath takes 2.15 times the steps of the sphere.  The radial model's
+// estimate goes through its mean steps at 0.5, 3.2 and 20 GV (642, 347, 263 at
+// kappa0 = 1.5e22 cm^2/s, 400 km/s, 100 AU).
 // A wrong estimate costs time only: results do not depend on the queue order.
 double expected_steps(const cosmica_helio& h, const cosmica_species& sp, double P0)
 {
-    if (h.model != COSMICA_MODEL_3D) return 1.0;
     const double lp = std::log(P0);
+    if (h.model != COSMICA_MODEL_3D) return std::exp(6.195 - 0.355 * lp + 0.049 * lp * lp);
+    const double sheath = h.heliosheath ? 2.15 : 1.0;
     const int sq = sp.charge > 0 ? 1 : -1;
     if (h.drift == 1 && h.hcs == 1 && sq * h.polarity < 0) {
         double tilt = 0.0;
         for (int k = 0; k < h.n_regions; ++k) tilt += h.tilt_deg[k];
         tilt /= (double)h.n_regions;
-        return std::exp(3.697 + 0.0365 * lp + 0.0201 * lp * lp + 6.653 * tilt / 45.0);
+        return sheath * std::exp(3.697 + 0.0365 * lp + 0.0201 * lp * lp + 6.653 * tilt / 45.0);
     }
-    return std::exp(5.825 - 0.0657 * lp + 0.0489 * lp * lp);
+    return sheath * std::exp(5.825 - 0.0657 * lp + 0.0489 * lp * lp);
 }
 
 // Chunks of every segment of a model group, in the requested order: 0 as
@@ -595,6 +602,67 @@ bool launch_ok(const cosmica_launch& L)
            L.order >= 0 && L.order <= 2;
 }
 
+// The work of one model's particles in a pass.
+struct PassWork {
+    uint64_t particles = 0;
+    double steps = 0.0;    // expected, all particles
+    double longest = 0.0;  // largest expected steps per particle of a bin
+    void add(uint64_t count, double per_particle)
+    {
+        particles += count;
+        steps += (double)count * per_particle;
+        longest = std::max(longest, per_particle);
+    }
+};
+
+// How a pass runs: the throughput kernel in the context's launch shape, or the
+// latency kernel with few waves per SIMD.
+struct PassShape {
+    bool latency = false;
+    int blocks_per_cu = 0;    // latency kernel: workgroups per CU (waves per SIMD)
+    uint32_t lane_cap = 64;   // latency kernel: lanes a wave fills
+    int chunk = 32;
+};
+
+// A pass ends when its longest path does.  A step of that path takes the time
+// that a SIMD needs for one step of each of its waves: 1.7 us at full residency
+// (binary32, 3D) against 0.40 us for a wave alone in the latency kernel, whose
+// throughput is 10% lower.  The pass is bound by the longest path while the
+// work per lane of the full grid is below a few times the longest expected
+// path.  Measured crossings, as work per lane over the largest expected mean
+// of a bin: 3D binary32 12 (no particle on the current sheet) and 8 (the
+// batched mix), 3D binary64 12; radial binary32 7, binary64 20.  At 1e8 steps
+// (306,000 particles, 3D binary32) the throughput kernel takes 5.1 ms, the
+// latency kernel 3.1 ms; at 9e9 steps 56 and 72 ms.
+PassShape pass_shape(cosmica_ctx* ctx, int model, int prec, const PassWork& w, bool shaped,
+                     bool energy, bool ukey)
+{
+    const cosmica_launch& L = ctx->launch[model][prec];
+    PassShape s;
+    s.chunk = L.chunk;
+    if (!ctx->auto_launch[model][prec] || w.particles == 0) return s;
+    const uint64_t lanes =
+        (uint64_t)grid_for(ctx, model, prec, L, ~0ull >> 8, shaped, energy, ukey) * (uint64_t)L.block;
+    const double crossing = model == 1 ? 10.0 : (prec == COSMICA_PREC_MIXED ? 6.0 : 20.0);
+    if (w.steps >= crossing * (double)lanes * w.longest) return s;
+    s.latency = true;
+    // One wave per SIMD while every particle finds a lane (a step then costs its
+    // own latency only); else 2, for the throughput (spectrum of 100,000
+    // particles: 2.70 ms with 1, 2.62 ms with 2; a batch of 6.7e6: 770, 587 and
+    // 604 ms with 1, 2 and 3), the radial binary32 step 3 (1.07, 0.82 and
+    // 0.85 ms; 4e6 particles: 10.4, 6.1 and 5.1 ms).  The 3D binary64 variants
+    // fill the register file with 1.
+    const uint64_t simd_waves = (uint64_t)ctx->num_cus * 4;
+    s.blocks_per_cu = 1;
+    if (w.particles > simd_waves * 64 && !(model == 1 && prec == COSMICA_PREC_FP64))
+        s.blocks_per_cu = model == 0 && prec == COSMICA_PREC_MIXED ? 3 : 2;
+    const uint64_t waves = simd_waves * (uint64_t)s.blocks_per_cu;
+    // particles spread evenly over the waves: a wave with few of them steps faster
+    s.lane_cap = (uint32_t)std::min<uint64_t>(64, (w.particles + waves - 1) / waves);
+    s.chunk = (int)std::min<uint32_t>((uint32_t)L.chunk, s.lane_cap);
+    return s;
+}
+
 template <typename R>
 hipError_t launch_model(int model, const PropArgs<R>& a, int grid, int block, hipStream_t s);
 template <>
@@ -625,7 +693,8 @@ struct cosmica_plan {
     std::vector<SegmentDev> segs;
     std::vector<uint32_t> seg_first;  // first segment of each job
     uint64_t total_particles = 0;
-    uint64_t model_particles[2] = {0, 0};
+    PassWork work[2];      // of the radial and the 3D particles
+    PassShape shape[2];
     std::vector<ChunkDev> chunks_h[2];
     DevSet mem;
     void* jobs_d = nullptr;
@@ -708,7 +777,8 @@ struct PassDev {
     const SegmentDev* segs;
     const ChunkDev* chunks[2];  // the refill queues of the radial and 3D groups
     uint32_t n_chunks[2];
-    uint64_t model_particles[2];
+    PassWork work[2];
+    PassShape shape[2];
     uint32_t* counters;  // 8 words, zeroed: the queue heads of the two models (64-bit each)
     double *exP, *exT, *exL, *exR, *exTh, *exPh;
     uint32_t* exNF;
@@ -752,11 +822,21 @@ cosmica_status execute_prop(cosmica_ctx* ctx, const PassDev& d)
         a.exL = d.exL;
         a.key_lo = (uint32_t)(d.key & 0xffffffffu);
         a.key_hi = (uint32_t)(d.key >> 32);
-        const int grid =
-            grid_for(ctx, model, d.prec, L, d.model_particles[model], d.shaped, d.energy, d.uniform_key);
+        int grid = 0, block = L.block;
+        if (d.shape[model].latency && ctx->auto_launch[model][d.prec]) {
+            const PassShape& f = d.shape[model];
+            a.latency = 1u;
+            a.lane_cap = f.lane_cap;
+            const uint64_t per_block = (uint64_t)f.lane_cap * (uint64_t)block / 64;
+            grid = (int)std::min<uint64_t>((uint64_t)ctx->num_cus * (uint64_t)f.blocks_per_cu,
+                                           (d.work[model].particles + per_block - 1) / per_block);
+        } else {
+            grid = grid_for(ctx, model, d.prec, L, d.work[model].particles, d.shaped, d.energy,
+                            d.uniform_key);
+        }
         ctx->timings.grid_blocks = grid;
-        ctx->timings.block = L.block;
-        HIP_TRY(launch_model<R>(model, a, grid, L.block, ctx->stream));
+        ctx->timings.block = block;
+        HIP_TRY(launch_model<R>(model, a, grid, block, ctx->stream));
     }
     return COSMICA_OK;
 }
@@ -771,7 +851,8 @@ PassDev pass_of(const cosmica_plan* p)
     for (int m = 0; m < 2; ++m) {
         d.chunks[m] = p->chunks_d[m];
         d.n_chunks[m] = (uint32_t)p->chunks_h[m].size();
-        d.model_particles[m] = p->model_particles[m];
+        d.work[m] = p->work[m];
+        d.shape[m] = p->shape[m];
     }
     d.counters = p->counters_d;
     d.exP = p->exP;
@@ -900,20 +981,22 @@ cosmica_status cosmica_plan_create(cosmica_ctx* ctx, const cosmica_job* jobs, in
             s.out_offset = off;
             off += jc.cnt[b];
             ids[model].push_back((uint32_t)p->segs.size());
-            p->model_particles[model] += jc.cnt[b];
             p->segs.push_back(s);
             cost.push_back(expected_steps(jc.helio, jc.species, jc.rig[b]));
+            p->work[model].add(jc.cnt[b], cost.back());
         }
-    }
-    for (int m = 0; m < 2; ++m) {
-        const cosmica_launch& L = ctx->launch[m][precision];
-        make_chunks(p->segs, ids[m], L.chunk, L.order, &p->chunks_h[m], &cost);
     }
     p->key = p->jobs[0].seed;
     p->uniform_key = true;
     for (const JobCopy& jc : p->jobs) p->uniform_key &= jc.seed == p->key;
     for (const JobCopy& jc : p->jobs) p->shaped |= job_shaped(jc);
     for (const JobCopy& jc : p->jobs) p->energy |= jc.formulation == 1;
+    for (int m = 0; m < 2; ++m) {
+        p->shape[m] =
+            pass_shape(ctx, m, precision, p->work[m], p->shaped, p->energy, p->uniform_key);
+        make_chunks(p->segs, ids[m], p->shape[m].chunk, ctx->launch[m][precision].order,
+                    &p->chunks_h[m], &cost);
+    }
     cosmica_status st = precision == COSMICA_PREC_MIXED ? upload_tables<float>(p.get())
                                                          : upload_tables<double>(p.get());
     if (st != COSMICA_OK) return st;
@@ -1298,16 +1381,15 @@ cosmica_status run_static(cosmica_ctx* ctx, const cosmica_job* jobs, uint32_t n_
     StaticHost& H = *ctx->stat;
     // sizes of the work
     uint32_t n_bins = 0, n_orbit = 0;
-    uint64_t total = 0, model_particles[2] = {0, 0};
+    uint64_t total = 0;
+    PassWork work[2];
+    PassShape shape[2];
     bool energy = false, shaped = false, exits = false, ukey = true;
     for (uint32_t j = 0; j < n_jobs; ++j) {
         const cosmica_job& J = jobs[j];
         n_bins += (uint32_t)J.n_bins;
         n_orbit += J.n_orbit;
-        for (int b = 0; b < J.n_bins; ++b) {
-            total += J.particles_per_bin[b];
-            model_particles[J.helio->model] += J.particles_per_bin[b];
-        }
+        for (int b = 0; b < J.n_bins; ++b) total += J.particles_per_bin[b];
         energy |= J.formulation == 1;
         shaped |= helio_shaped(*J.helio);
         exits |= results[j].exits != nullptr;
@@ -1331,6 +1413,7 @@ cosmica_status run_static(cosmica_ctx* ctx, const cosmica_job* jobs, uint32_t n_
             g.out_offset = off;
             off += J.particles_per_bin[b];
             H.cost[ns] = expected_steps(*J.helio, *J.species, J.rigidity_gv[b]);
+            work[J.helio->model].add(g.count, H.cost[ns]);
         }
     }
     // refill chunks of each model group in the launch's queue order; the chunk
@@ -1340,8 +1423,9 @@ cosmica_status run_static(cosmica_ctx* ctx, const cosmica_job* jobs, uint32_t n_
     uint32_t nc = 0, first[2] = {0, 0}, nch[2] = {0, 0};
     for (int m = 0; m < 2; ++m) {
         const cosmica_launch& L = ctx->launch[m][prec];
-        const uint32_t c =
-            (uint32_t)std::max<uint64_t>((uint64_t)std::max(1, L.chunk), (total + room - 1) / room);
+        shape[m] = pass_shape(ctx, m, prec, work[m], shaped, energy, ukey);
+        const uint32_t c = (uint32_t)std::max<uint64_t>((uint64_t)std::max(1, shape[m].chunk),
+                                                        (total + room - 1) / room);
         uint32_t k = 0;
         for (uint32_t i = 0; i < ns; ++i)
             if (jobs[H.segs[i].job].helio->model == m) H.ids[k++] = i;
@@ -1417,7 +1501,8 @@ cosmica_status run_static(cosmica_ctx* ctx, const cosmica_job* jobs, uint32_t n_
     for (int m = 0; m < 2; ++m) {
         d.chunks[m] = (const ChunkDev*)at(Lo.chunks) + first[m];
         d.n_chunks[m] = nch[m];
-        d.model_particles[m] = model_particles[m];
+        d.work[m] = work[m];
+        d.shape[m] = shape[m];
     }
     d.counters = (uint32_t*)at(Lo.counters);
     d.exP = (double*)at(Lo.exP);
@@ -1522,6 +1607,7 @@ cosmica_status cosmica_set_launch(cosmica_ctx* ctx, cosmica_model model,
         (precision != 0 && precision != 1) || !launch_ok(*cfg))
         return COSMICA_EINVAL;
     ctx->launch[model][precision] = *cfg;
+    ctx->auto_launch[model][precision] = false;
     return COSMICA_OK;
 }
 
@@ -1793,6 +1879,7 @@ cosmica_status time_shape(cosmica_ctx* ctx, const cosmica_job* jobs, int n_jobs,
                           int precision, const cosmica_launch& c, double* rate)
 {
     ctx->launch[model][precision] = c;
+    ctx->auto_launch[model][precision] = false;
     cosmica_plan* p = nullptr;
     cosmica_status st = cosmica_plan_create(ctx, jobs, n_jobs, (cosmica_precision)precision, 0, &p);
     if (st != COSMICA_OK) return st;
@@ -1815,6 +1902,7 @@ cosmica_status sweep(cosmica_ctx* ctx, const cosmica_job* jobs, int n_jobs, int 
 {
     const std::string key = tune_key(ctx, model, precision);
     const cosmica_launch saved = ctx->launch[model][precision];
+    const bool saved_auto = ctx->auto_launch[model][precision];
     // Start from full residency, 32-particle chunks and queue order 2 (long
     // paths kept out of the tail); the other orders are tried last.  Timings
     // of one shape vary by about 1% from run to run as the device warms, so
@@ -1869,6 +1957,7 @@ cosmica_status sweep(cosmica_ctx* ctx, const cosmica_job* jobs, int n_jobs, int 
     }
     if (st != COSMICA_OK) {
         ctx->launch[model][precision] = saved;
+        ctx->auto_launch[model][precision] = saved_auto;
         return st;
     }
     ctx->launch[model][precision] = best;
@@ -1886,6 +1975,7 @@ extern "C" cosmica_status cosmica_tune(cosmica_ctx* ctx, cosmica_model model,
     cosmica_launch L;
     if (cache_lookup(cache_path, tune_key(ctx, model, precision), &L)) {
         ctx->launch[model][precision] = L;
+        ctx->auto_launch[model][precision] = false;
         return COSMICA_OK;
     }
     HIP_TRY(hipSetDevice(ctx->device));
@@ -1913,6 +2003,7 @@ extern "C" cosmica_status cosmica_tune_jobs(cosmica_ctx* ctx, const cosmica_job*
     cosmica_launch L;
     if (cache_lookup(cache_path, tune_key(ctx, model, precision), &L)) {
         ctx->launch[model][precision] = L;
+        ctx->auto_launch[model][precision] = false;
         return COSMICA_OK;
     }
     HIP_TRY(hipSetDevice(ctx->device));

@@ -1,0 +1,82 @@
+"""The latency kernel (few waves per SIMD, random numbers drawn ahead on idle
+lanes) against the throughput kernel: results and exit records equal bit for
+bit.  An explicit launch shape selects the throughput kernel, the default shape
+the latency kernel for passes of this size.  Sizes sit at the edges of its
+rules: 1,024 waves at one wave per SIMD, 16 particles per wave (random numbers
+ahead), 64 lanes, and the second wave per SIMD."""
+import numpy as np
+import pytest
+
+from paper_2502_06319_amd import cosmica as C
+from paper_2502_06319_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("hist", "flux", "flux_se", "mean_exit_time_s", "steps", "n_capped", "n_nan")
+WAVES = 1024
+
+
+def _both(jobs, precision, model=1):
+    """The same call with the latency and with the throughput kernel."""
+    with C.Engine(0) as e:
+        few = e.run(jobs, precision, exits=True)
+        shape = e.timings()
+        e.set_launch(model, precision, block=256, blocks_per_cu=0, chunk=32, order=2)
+        full = e.run(jobs, precision, exits=True)
+    for a, b in zip(few, full):
+        for k in KEYS:
+            np.testing.assert_array_equal(a[k], b[k], err_msg=k)
+        for k in C.EXIT_DTYPE.names:  # field by field: NaN equals NaN
+            np.testing.assert_array_equal(a["exits"][k], b["exits"][k], err_msg=k)
+    return few, shape
+
+
+def _job(kind, bins, per_bin, seed=42, tag=0):
+    if kind == "radial":
+        job = W.c1_job(particles_per_bin=1, seed=seed)
+        rig = W.log_bins(0.5, 20.0, bins)
+    else:
+        job = W.c2_heliosheath_job(1, seed) if kind == "heliosheath" else W.c2_job(1, seed)
+        rig = W.log_bins(0.3, 30.0, bins)
+    job.update(rigidity_gv=rig, particles_per_bin=[per_bin] * bins, job_tag=tag)
+    if kind in ("energy", "energy orbit"):
+        job["formulation"] = 1
+    if kind == "energy orbit":
+        job = W.with_orbit(job, W.ulysses_like_orbit(5))
+    return job
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("kind,n", [("radial", 1), ("radial", 65), ("radial", 17 * WAVES + 3),
+                                    ("radial", 64 * WAVES + 1), ("3d", 1), ("3d", WAVES),
+                                    ("3d", WAVES + 1), ("3d", 16 * WAVES), ("3d", 16 * WAVES + 1),
+                                    ("3d", 64 * WAVES), ("3d", 64 * WAVES + 1),
+                                    ("heliosheath", 333), ("heliosheath", 20 * WAVES + 7),
+                                    ("energy", 3 * WAVES), ("energy orbit", 33 * WAVES)])
+def test_latency_kernel_equals_throughput_kernel(kind, n, precision):
+    first = min(n, 7)
+    job = _job(kind, 3 if n > 100 else 1, first)
+    if n > 100:
+        job["particles_per_bin"] = [first, n - first - 5, 5]
+    else:
+        job["particles_per_bin"] = [n]
+    r, shape = _both(job, precision, 0 if kind == "radial" else 1)
+    assert int(r[0]["hist"].sum()) == n
+    assert shape["grid_blocks"] * shape["block"] <= 3 * 64 * WAVES
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_latency_kernel_mixed_jobs_caps_and_non_finite(precision):
+    """Jobs with their own seeds, shapes and formulations in one wave; a step
+    cap inside a batch of drawn-ahead numbers; particles that turn non-finite;
+    particles that ride the current sheet (phi past a turn, poles, reflections
+    through the origin)."""
+    sheet = W.make_job(W.c2_helio(), W.species("e-"), [0.5, 5.0], 300, seed=3, job_tag=9)
+    sheet["step_cap"] = 3001
+    jobs = [_job("3d", 4, 50, seed=5, tag=1), _job("heliosheath", 3, 61, seed=6, tag=2),
+            _job("energy", 2, 33, seed=7, tag=3), _job("energy orbit", 2, 40, seed=8, tag=4),
+            dict(_job("3d", 2, 70, seed=9, tag=5), step_cap=7), sheet,
+            dict(_job("3d", 2, 9, seed=9, tag=6), rigidity_gv=[1.0, 1e20])]
+    r, _ = _both(jobs, precision)
+    assert np.all(r[4]["n_capped"] == 70)
+    assert r[5]["n_capped"].sum() > 0
