@@ -190,7 +190,11 @@ struct ReweightArgs {
     const double* lnJ;  // n_lis * n_knots
     uint32_t n_lis, n_knots;
     double lnP0, dlnP;
-    uint32_t seg_base, out_base, total_bins, pad0;
+    uint32_t seg_base, out_base, total_bins;
+    uint32_t small_tables;  // 1: every |ln J| < 1e4
+    // a segment's exits in parts of `part`, at most `parts` of them (1: whole)
+    uint32_t part, parts;
+    double* partial;    // 4 * n_lis * total_bins * parts (null when parts is 1)
     double* flux;       // n_lis * total_bins
     double* flux_se;
 };
@@ -203,6 +207,8 @@ struct RangeArgs {
     const double* exP;
     const uint32_t* exNF;
     uint32_t n_hist, seg_base, out_base, total_bins;
+    uint32_t part, parts;  // as in ReweightArgs
+    double* part_max;      // segments of the launch * parts (null when parts is 1)
     double* p_max;   // total_bins
     uint32_t* hist;  // total_bins * n_hist
 };

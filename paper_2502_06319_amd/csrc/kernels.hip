@@ -1400,23 +1400,109 @@ hipError_t launch_reduce(const ReduceArgs& a, uint32_t n_segs, hipStream_t s)
 
 // ---------------------------------------------------------------------------
 // Re-weighting of stored exit records with tabulated spectra (Eq.(4) with
-// other J_LIS): one workgroup per (segment, group of kReweightGroup spectra).
-// ln J is linear in ln P between knots ln P = lnP0 + k dlnP, with the end
-// segments extended.  The group's tables sit in LDS; each particle's ln P and
-// its form-dependent factor are computed once for the whole group.
+// other J_LIS): one workgroup per (segment, group of kReweightGroup spectra,
+// part of the segment).  ln J is linear in ln P between knots ln P = lnP0 + k
+// dlnP, with the end segments extended.  The group's tables sit in LDS as
+// (value, difference) pairs; each particle's ln P and its form-dependent factor
+// are computed once for the whole group.
+//
+// Bound by FP64 VALU: one exponential per particle and spectrum.  One pass
+// accumulates w - s and (w - s)^2 with s the weight of the segment's first used
+// particle: |s - mean| is at most sqrt(N) standard deviations, so the variance
+// keeps all but N ulps, and N equal weights give a standard error of exactly 0.
+// Segments are split over workgroups where segments and groups alone would
+// leave CUs idle.  64 spectra x 516,000 exits of 30 bins: 521 us with two passes
+// of the library's exp in 120 workgroups, 73 us so.
 // ---------------------------------------------------------------------------
+// e^x = 2^k e^r, k = round(x / ln 2), the Taylor series of e^r to r^13 (|r| <=
+// ln(2)/2: the next term is below 2^-57).  For |x| < 2^30; ldexp saturates to 0
+// and infinity.
+__device__ __forceinline__ double exp_taylor(double x)
+{
+    const double k = __builtin_rint(x * 1.4426950408889634);
+    const double r = fma(k, -2.3190468138462996e-17, fma(k, -0.6931471805599453, x));
+    double p = 1.0 / 6227020800.0;
+    p = fma(p, r, 1.0 / 479001600.0);
+    p = fma(p, r, 1.0 / 39916800.0);
+    p = fma(p, r, 1.0 / 3628800.0);
+    p = fma(p, r, 1.0 / 362880.0);
+    p = fma(p, r, 1.0 / 40320.0);
+    p = fma(p, r, 1.0 / 5040.0);
+    p = fma(p, r, 1.0 / 720.0);
+    p = fma(p, r, 1.0 / 120.0);
+    p = fma(p, r, 1.0 / 24.0);
+    p = fma(p, r, 1.0 / 6.0);
+    p = fma(p, r, 0.5);
+    p = fma(p, r, 1.0);
+    p = fma(p, r, 1.0);
+    return __builtin_amdgcn_ldexp(p, (int)k);
+}
+
+// Sums of v[0..15] over the wave in a fixed order, each level halving the lanes
+// that hold a value (H = 8, 4, 2, 1); lane l returns that of v[l / 4].
+template <int H>
+__device__ __forceinline__ double wave_sums(const double* v, uint32_t lane)
+{
+    if constexpr (H == 0) {
+        return v[0];
+    } else {
+        const bool up = (lane & (4 * H)) != 0;
+        double w[H];
+#pragma unroll
+        for (int i = 0; i < H; ++i)
+            w[i] = (up ? v[i + H] : v[i]) + __shfl_xor(up ? v[i] : v[i + H], 4 * H, 64);
+        return wave_sums<H / 2>(w, lane);
+    }
+}
+__device__ __forceinline__ double wave_sum16(const double* v, uint32_t lane)
+{
+    double t = wave_sums<8>(v, lane);
+    t += __shfl_xor(t, 2, 64);
+    return t + __shfl_xor(t, 1, 64);
+}
+
+struct LisStep {
+    double at, d;  // ln J at a knot, and the difference to the next one
+};
+
+// Mean and standard error from the sums about s of n weights.
+__device__ __forceinline__ void mean_and_se(double n, double s, double s1, double s2,
+                                            double* mean, double* se)
+{
+    *mean = n > 0.0 ? s + s1 / n : 0.0;
+    double m2 = s2 - s1 * (s1 / n);
+    m2 = m2 < 0.0 ? 0.0 : m2;
+    *se = n > 1.0 ? ::sqrt(m2 / (n - 1.0) / n) : 0.0;
+}
+
 __global__ void __launch_bounds__(kReduceBlock) k_reweight(const ReweightArgs a)
 {
-    __shared__ double tab[kReweightGroup * kMaxLisKnots];
-    __shared__ double shd[kReduceBlock / 64];
+    __shared__ LisStep tab[kReweightGroup * (kMaxLisKnots - 1)];
+    __shared__ double sums[2][kReduceBlock / 64][kReweightGroup];
+    __shared__ double about[kReweightGroup];
+    __shared__ unsigned long long shu[kReduceBlock / 64];
+    __shared__ uint32_t pilot;
     const uint32_t sidx = a.seg_base + blockIdx.x;
     const uint32_t l0 = blockIdx.y * kReweightGroup;
     const uint32_t nl = a.n_lis - l0 < (uint32_t)kReweightGroup ? a.n_lis - l0
                                                                  : (uint32_t)kReweightGroup;
-    for (uint32_t i = threadIdx.x; i < nl * a.n_knots; i += kReduceBlock)
-        tab[i] = a.lnJ[(size_t)l0 * a.n_knots + i];
-    __syncthreads();
     const SegmentDev sg = a.segs[sidx];
+    const uint32_t first = blockIdx.z * a.part;
+    if (first >= sg.count) return;
+    const uint32_t end = sg.count - first < a.part ? sg.count : first + a.part;
+    const uint32_t ns = a.n_knots - 1;
+    const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
+    for (uint32_t l = wid; l < (uint32_t)kReweightGroup; l += kReduceBlock / 64) {
+        for (uint32_t k = lane; k < ns; k += 64u) {
+            LisStep t = {0.0, 0.0};
+            if (l < nl) {
+                const double* row = a.lnJ + (size_t)(l0 + l) * a.n_knots + k;
+                t.at = row[0];
+                t.d = row[1] - row[0];
+            }
+            tab[l * ns + k] = t;
+        }
+    }
     const LisDev L = a.lis[sg.job];
     const double beta0 = L.energy ? beta_of(L, sg.P0) : 0.0;
     const double p02 = sg.P0 * sg.P0;
@@ -1434,66 +1520,119 @@ __global__ void __launch_bounds__(kReduceBlock) k_reweight(const ReweightArgs a)
         *k = kk;
         *f = x - (double)kk;
     };
-    double acc[kReweightGroup];
-    for (int l = 0; l < kReweightGroup; ++l) acc[l] = 0.0;
+    // the segment's first used particle
+    if (threadIdx.x == 0) pilot = ~0u;
+    for (uint32_t i0 = 0; i0 < sg.count; i0 += kReduceBlock) {
+        const uint32_t i = i0 + threadIdx.x;
+        __syncthreads();
+        if (i < sg.count && (a.exNF[sg.out_offset + i] >> kFlagShift) == 0u) atomicMin(&pilot, i);
+        __syncthreads();
+        if (pilot != ~0u) break;
+    }
+    if (threadIdx.x < (uint32_t)kReweightGroup) {
+        double w = 0.0;
+        if (pilot != ~0u) {
+            double fac, f;
+            int k;
+            factor_and_pos(sg.out_offset + pilot, &fac, &k, &f);
+            const LisStep t = tab[threadIdx.x * ns + (uint32_t)k];
+            w = fac * ::exp(t.at + f * t.d);
+            if (!(fabs(w) < __builtin_huge_val())) w = 0.0;
+        }
+        about[threadIdx.x] = w;
+    }
+    __syncthreads();
+    double s1[kReweightGroup], s2[kReweightGroup], about_r[kReweightGroup];
+#pragma unroll
+    for (int l = 0; l < kReweightGroup; ++l) {
+        s1[l] = s2[l] = 0.0;
+        about_r[l] = about[l];
+    }
     unsigned long long nused = 0;
-    for (uint32_t i = threadIdx.x; i < sg.count; i += kReduceBlock) {
+    for (uint32_t i = first + threadIdx.x; i < end; i += kReduceBlock) {
         const uint32_t o = sg.out_offset + i;
         if ((a.exNF[o] >> kFlagShift) != 0u) continue;  // capped or non-finite
         double fac, f;
         int k;
         factor_and_pos(o, &fac, &k, &f);
         ++nused;
-#pragma unroll
-        for (int l = 0; l < kReweightGroup; ++l) {
-            if ((uint32_t)l < nl) {
-                const double* t = tab + l * a.n_knots;
-                acc[l] += fac * ::exp(t[k] + f * (t[k + 1] - t[k]));
-            }
-        }
-    }
-    __shared__ unsigned long long shu[kReduceBlock / 64];
-    const double N = (double)block_sum<unsigned long long>(nused, shu);
-    double mean[kReweightGroup];
-    for (int l = 0; l < kReweightGroup; ++l) {
-        const double S = block_sum<double>(acc[l], shd);
-        mean[l] = N > 0.0 ? S / N : 0.0;
-        acc[l] = 0.0;
-    }
-    if (N > 1.0) {
-        for (uint32_t i = threadIdx.x; i < sg.count; i += kReduceBlock) {
-            const uint32_t o = sg.out_offset + i;
-            if ((a.exNF[o] >> kFlagShift) != 0u) continue;
-            double fac, f;
-            int k;
-            factor_and_pos(o, &fac, &k, &f);
+        const LisStep* t = tab + k;
+        // (tables and positions of any use keep the argument far inside the
+        // range of exp_taylor)
+        if (a.small_tables && fabs(f) < 1e4) {
 #pragma unroll
             for (int l = 0; l < kReweightGroup; ++l) {
-                if ((uint32_t)l < nl) {
-                    const double* t = tab + l * a.n_knots;
-                    const double d = fac * ::exp(t[k] + f * (t[k + 1] - t[k])) - mean[l];
-                    acc[l] += d * d;
-                }
+                const LisStep q = t[(uint32_t)l * ns];
+                const double d = fac * exp_taylor(fma(f, q.d, q.at)) - about_r[l];
+                s1[l] += d;
+                s2[l] += d * d;
+            }
+        } else {
+#pragma unroll
+            for (int l = 0; l < kReweightGroup; ++l) {
+                const LisStep q = t[(uint32_t)l * ns];
+                const double d = fac * ::exp(q.at + f * q.d) - about_r[l];
+                s1[l] += d;
+                s2[l] += d * d;
             }
         }
     }
-    for (int l = 0; l < kReweightGroup; ++l) {
-        const double SS = block_sum<double>(acc[l], shd);
-        if (threadIdx.x == 0 && (uint32_t)l < nl) {
-            const size_t ob = (size_t)(l0 + l) * a.total_bins + a.out_base + blockIdx.x;
-            a.flux[ob] = mean[l];
-            a.flux_se[ob] = N > 1.0 ? ::sqrt(SS / (N - 1.0) / N) : 0.0;
+    const double v1 = wave_sum16(s1, lane), v2 = wave_sum16(s2, lane);
+    if ((lane & 3u) == 0) {
+        sums[0][wid][lane >> 2] = v1;
+        sums[1][wid][lane >> 2] = v2;
+    }
+    const double n = (double)block_sum<unsigned long long>(nused, shu);
+    if (threadIdx.x < nl) {
+        const uint32_t l = threadIdx.x;
+        double t1 = 0.0, t2 = 0.0;
+        for (int w = 0; w < kReduceBlock / 64; ++w) {
+            t1 += sums[0][w][l];
+            t2 += sums[1][w][l];
+        }
+        const size_t ob = (size_t)(l0 + l) * a.total_bins + a.out_base + blockIdx.x;
+        if (a.parts == 1) {
+            mean_and_se(n, about[l], t1, t2, &a.flux[ob], &a.flux_se[ob]);
+        } else {
+            double* q = a.partial + 4 * (ob * a.parts + blockIdx.z);
+            q[0] = n;
+            q[1] = about[l];
+            q[2] = t1;
+            q[3] = t2;
         }
     }
 }
 
+// The parts of every (spectrum, segment), in order.
+__global__ void __launch_bounds__(kReduceBlock) k_reweight_sum(const ReweightArgs a, uint32_t n_segs)
+{
+    const uint32_t i = blockIdx.x * kReduceBlock + threadIdx.x;
+    if (i >= a.n_lis * n_segs) return;
+    const uint32_t l = i / n_segs, b = i - l * n_segs;
+    const size_t ob = (size_t)l * a.total_bins + a.out_base + b;
+    const uint32_t count = a.segs[a.seg_base + b].count;
+    const uint32_t np = (count + a.part - 1) / a.part;
+    double n = 0.0, s = 0.0, s1 = 0.0, s2 = 0.0;
+#pragma unroll 4
+    for (uint32_t z = 0; z < np; ++z) {
+        const double* q = a.partial + 4 * (ob * a.parts + z);
+        n += q[0];
+        s = q[1];
+        s1 += q[2];
+        s2 += q[3];
+    }
+    mean_and_se(n, s, s1, s2, &a.flux[ob], &a.flux_se[ob]);
+}
+
 // ---------------------------------------------------------------------------
 // Exit histogram over the reached range (Sec. IV.A: the largest exit energy of
-// the sample sets the histogram's binning): one workgroup per bin takes the
-// largest used exit rigidity P_max, then counts ln(P_ex / P0) in n_hist equal
-// bins over [0, ln(P_max / P0)] (index floor(n_hist x / x_max), the record at
-// P_max in the last bin) with LDS atomics.  Capped and non-finite records are
-// left out.
+// the sample sets the histogram's binning): the largest used exit rigidity
+// P_max of a bin, then the counts of ln(P_ex / P0) in n_hist equal bins over
+// [0, ln(P_max / P0)] (index floor(n_hist x / x_max), the record at P_max in
+// the last bin) with LDS atomics.  Capped and non-finite records are left out.
+// Bound by latency in one workgroup per bin: larger bins are split into parts,
+// whose maxima come from a first launch and whose counts are added up in
+// memory.  4.0e6 exits of 240 bins: 150 us unsplit, 46 us in parts of 4,096.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ double block_max(double v, double* sh)
 {
@@ -1513,27 +1652,64 @@ __device__ __forceinline__ double block_max(double v, double* sh)
     return t;
 }
 
+// The largest used exit rigidity of exits [first, end) of a segment.
+__device__ __forceinline__ double range_max(const RangeArgs& a, const SegmentDev& sg,
+                                            uint32_t first, uint32_t end, double* sh)
+{
+    double pm = 0.0;
+#pragma unroll 4
+    for (uint32_t i = first + threadIdx.x; i < end; i += kReduceBlock) {
+        const uint32_t o = sg.out_offset + i;
+        const double P = a.exP[o];  // (both words of a record at once)
+        if ((a.exNF[o] >> kFlagShift) == 0u) pm = fmax(pm, P);
+    }
+    return block_max(pm, sh);
+}
+
+// First launch of a split histogram: the maximum of each part; the counters
+// are cleared.
+__global__ void __launch_bounds__(kReduceBlock) k_range_max(const RangeArgs a)
+{
+    __shared__ double shd[kReduceBlock / 64];
+    const SegmentDev sg = a.segs[a.seg_base + blockIdx.x];
+    const uint32_t first = min(blockIdx.y * a.part, sg.count);
+    const double pm = range_max(a, sg, first, min(sg.count - first, a.part) + first, shd);
+    if (threadIdx.x == 0) a.part_max[(size_t)blockIdx.x * a.parts + blockIdx.y] = pm;
+    uint32_t* h = a.hist + ((size_t)a.out_base + blockIdx.x) * a.n_hist;
+    for (uint32_t k = blockIdx.y * kReduceBlock + threadIdx.x; k < a.n_hist;
+         k += a.parts * kReduceBlock)
+        h[k] = 0u;
+}
+
 __global__ void __launch_bounds__(kReduceBlock) k_exit_range(const RangeArgs a)
 {
     __shared__ uint32_t h[kMaxRangeBins];
     __shared__ double shd[kReduceBlock / 64];
     const SegmentDev sg = a.segs[a.seg_base + blockIdx.x];
+    const bool split = a.parts > 1;
+    const uint32_t first = blockIdx.y * a.part;
+    if (split && first >= sg.count && blockIdx.y != 0) return;
+    const uint32_t end = split ? min(sg.count - first, a.part) + first : sg.count;
     double pm = 0.0;
-    for (uint32_t i = threadIdx.x; i < sg.count; i += kReduceBlock) {
-        const uint32_t o = sg.out_offset + i;
-        if ((a.exNF[o] >> kFlagShift) == 0u) pm = fmax(pm, a.exP[o]);
+    if (split) {
+        for (uint32_t z = threadIdx.x; z < a.parts; z += kReduceBlock)
+            pm = fmax(pm, a.part_max[(size_t)blockIdx.x * a.parts + z]);
+        pm = block_max(pm, shd);
+    } else {
+        pm = range_max(a, sg, first, end, shd);
     }
-    pm = block_max(pm, shd);
     for (uint32_t k = threadIdx.x; k < a.n_hist; k += kReduceBlock) h[k] = 0u;
     __syncthreads();
     if (pm > 0.0) {
         const double xmax = ::log(pm / sg.P0);
-        for (uint32_t i = threadIdx.x; i < sg.count; i += kReduceBlock) {
+#pragma unroll 2
+        for (uint32_t i = first + threadIdx.x; i < end; i += kReduceBlock) {
             const uint32_t o = sg.out_offset + i;
+            const double P = a.exP[o];
             if ((a.exNF[o] >> kFlagShift) != 0u) continue;
             uint32_t k = 0;
             if (xmax > 0.0) {
-                const double x = ::log(a.exP[o] / sg.P0);
+                const double x = ::log(P / sg.P0);
                 const double f = ::floor((double)a.n_hist * x / xmax);
                 k = f <= 0.0 ? 0u : (f >= (double)a.n_hist ? a.n_hist - 1u : (uint32_t)f);
             }
@@ -1542,24 +1718,35 @@ __global__ void __launch_bounds__(kReduceBlock) k_exit_range(const RangeArgs a)
     }
     __syncthreads();
     const size_t ob = (size_t)a.out_base + blockIdx.x;
-    for (uint32_t k = threadIdx.x; k < a.n_hist; k += kReduceBlock)
-        a.hist[ob * a.n_hist + k] = h[k];
-    if (threadIdx.x == 0) a.p_max[ob] = pm;
+    for (uint32_t k = threadIdx.x; k < a.n_hist; k += kReduceBlock) {
+        if (!split)
+            a.hist[ob * a.n_hist + k] = h[k];
+        else if (h[k] != 0u)
+            atomicAdd(&a.hist[ob * a.n_hist + k], h[k]);
+    }
+    if (threadIdx.x == 0 && blockIdx.y == 0) a.p_max[ob] = pm;
 }
 
 hipError_t launch_exit_range(const RangeArgs& a, uint32_t n_segs, hipStream_t s)
 {
-    if (n_segs == 0 || a.n_hist == 0 || a.n_hist > (uint32_t)kMaxRangeBins)
+    if (n_segs == 0 || a.n_hist == 0 || a.n_hist > (uint32_t)kMaxRangeBins || a.parts == 0)
         return n_segs == 0 ? hipSuccess : hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_exit_range, dim3(n_segs), dim3(kReduceBlock), 0, s, a);
+    if (a.parts > 1)
+        hipLaunchKernelGGL(k_range_max, dim3(n_segs, a.parts), dim3(kReduceBlock), 0, s, a);
+    hipLaunchKernelGGL(k_exit_range, dim3(n_segs, a.parts), dim3(kReduceBlock), 0, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_reweight(const ReweightArgs& a, uint32_t n_segs, hipStream_t s)
 {
     if (n_segs == 0 || a.n_lis == 0) return hipSuccess;
+    if (a.parts == 0) return hipErrorInvalidValue;
     const uint32_t groups = (a.n_lis + kReweightGroup - 1) / kReweightGroup;
-    hipLaunchKernelGGL(k_reweight, dim3(n_segs, groups), dim3(kReduceBlock), 0, s, a);
+    hipLaunchKernelGGL(k_reweight, dim3(n_segs, groups, a.parts), dim3(kReduceBlock), 0, s, a);
+    if (a.parts > 1)
+        hipLaunchKernelGGL(k_reweight_sum,
+                           dim3((a.n_lis * n_segs + kReduceBlock - 1) / kReduceBlock),
+                           dim3(kReduceBlock), 0, s, a, n_segs);
     return hipGetLastError();
 }
 

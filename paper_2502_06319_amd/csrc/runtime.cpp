@@ -1207,6 +1207,26 @@ cosmica_status cosmica_plan_info(const cosmica_plan* p, uint64_t* total_bins,
 
 static_assert(kMaxLisKnots == COSMICA_MAX_LIS_KNOTS, "LDS table size and the ABI limit agree");
 
+// Splits the bins of a plan over workgroups: parts of at least `least` exits,
+// as many as give about 4 workgroups (of 256 threads) per CU with `groups`
+// workgroups per part; at most 64 parts a bin, 1 where the bins alone suffice.
+static void split_bins(const cosmica_plan* p, uint32_t groups, uint32_t least, uint32_t* part,
+                       uint32_t* parts)
+{
+    *part = ~0u;
+    *parts = 1;
+    const uint64_t want = (uint64_t)p->ctx->num_cus * 4;
+    if ((uint64_t)p->segs.size() * groups >= want) return;
+    uint64_t largest = 0;
+    for (const SegmentDev& s : p->segs) largest = std::max<uint64_t>(largest, s.count);
+    uint64_t c = p->total_particles * groups / want;
+    c = std::max<uint64_t>({c, least, (largest + 63) / 64});
+    c = (c + 255) / 256 * 256;
+    if (largest <= c) return;
+    *part = (uint32_t)c;
+    *parts = (uint32_t)((largest + c - 1) / c);
+}
+
 cosmica_status cosmica_plan_reweight(cosmica_plan* p, uint32_t n_lis, uint32_t n_knots,
                                      double lnP0, double dlnP, const double* lnJ, double* flux,
                                      double* flux_se)
@@ -1215,8 +1235,11 @@ cosmica_status cosmica_plan_reweight(cosmica_plan* p, uint32_t n_lis, uint32_t n
         n_knots < 2 || n_knots > (uint32_t)kMaxLisKnots || !std::isfinite(lnP0) ||
         !finite_pos(dlnP) || !p->executed)
         return COSMICA_EINVAL;
-    for (size_t i = 0; i < (size_t)n_lis * n_knots; ++i)
+    double largest = 0.0;
+    for (size_t i = 0; i < (size_t)n_lis * n_knots; ++i) {
         if (!std::isfinite(lnJ[i])) return COSMICA_EINVAL;
+        largest = std::max(largest, std::fabs(lnJ[i]));
+    }
     cosmica_ctx* ctx = p->ctx;
     HIP_TRY(hipSetDevice(ctx->device));
     const uint32_t nb = (uint32_t)p->segs.size();
@@ -1246,8 +1269,17 @@ cosmica_status cosmica_plan_reweight(cosmica_plan* p, uint32_t n_lis, uint32_t n
     a.seg_base = 0;
     a.out_base = 0;
     a.total_bins = nb;
+    a.small_tables = largest < 1e4 ? 1u : 0u;
     a.flux = fd;
     a.flux_se = sd;
+    // split bins where one workgroup per (bin, group of spectra) leaves CUs idle
+    const uint32_t groups = (n_lis + kReweightGroup - 1) / kReweightGroup;
+    split_bins(p, groups, 1024, &a.part, &a.parts);
+    if (a.parts > 1 && m.alloc(&a.partial, 4 * nout * a.parts) != COSMICA_OK) {
+        a.part = ~0u;  // no room for the parts' sums: whole bins
+        a.parts = 1;
+        a.partial = nullptr;
+    }
     HIP_TRY(launch_reweight(a, nb, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
     if (flux) HIP_TRY(hipMemcpy(flux, fd, nout * 8, hipMemcpyDeviceToHost));
@@ -1281,6 +1313,12 @@ cosmica_status cosmica_plan_exit_range(cosmica_plan* p, uint32_t n_hist, double*
     a.total_bins = nb;
     a.p_max = pm;
     a.hist = h;
+    split_bins(p, 1, 4096, &a.part, &a.parts);
+    if (a.parts > 1 && m.alloc(&a.part_max, (size_t)nb * a.parts) != COSMICA_OK) {
+        a.part = ~0u;
+        a.parts = 1;
+        a.part_max = nullptr;
+    }
     HIP_TRY(launch_exit_range(a, nb, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
     if (p_max) HIP_TRY(hipMemcpy(p_max, pm, (size_t)nb * 8, hipMemcpyDeviceToHost));
