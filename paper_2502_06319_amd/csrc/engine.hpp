@@ -114,6 +114,9 @@ struct SliceDev {
     uint32_t left_cap;            // entries of leftover
 };
 
+// Refill chunk of the default launch shape.
+constexpr uint32_t kSpreadChunk = 32;
+
 template <typename R>
 struct PropArgs {
     const JobDev<R>* jobs;
@@ -141,7 +144,7 @@ struct PropArgs {
     uint32_t energy;              // 1: some job of the launch is in the energy form
     uint32_t key_lo, key_hi;
     uint32_t latency;             // 1: run the kernel for few particles per SIMD
-    uint32_t lane_cap;            // lanes a wave of that kernel fills (1..64)
+    uint32_t lane_cap;            // lanes a wave of that kernel fills (1..64; 0: see k_latency)
     const uint32_t* job_cancel;   // optional per-job cancel flags
     uint32_t* job_done;           // optional per-job count of finished particles
 };

@@ -934,7 +934,7 @@ cosmica_status cosmica_create(cosmica_ctx** out, int device, uint64_t hbm_budget
     }
     for (int i = 0; i < 4; ++i) HIP_TRY(hipEventCreate(&ctx->ev[i]));
     for (int m = 0; m < 2; ++m)
-        for (int q = 0; q < 2; ++q) ctx->launch[m][q] = cosmica_launch{256, 0, 32, 2};
+        for (int q = 0; q < 2; ++q) ctx->launch[m][q] = cosmica_launch{256, 0, (int)kSpreadChunk, 2};
     *out = ctx.release();
     return COSMICA_OK;
 }
@@ -1945,7 +1945,7 @@ cosmica_status sweep(cosmica_ctx* ctx, const cosmica_job* jobs, int n_jobs, int 
     // paths kept out of the tail); the other orders are tried last.  Timings
     // of one shape vary by about 1% from run to run as the device warms, so
     // another shape replaces the best only when it is more than 1% faster.
-    cosmica_launch best{256, 0, 32, 2};
+    cosmica_launch best{256, 0, (int)kSpreadChunk, 2};
     double best_rate = -1.0;
     auto consider = [&](const cosmica_launch& c) -> cosmica_status {
         if (!launch_ok(c)) return COSMICA_OK;
@@ -2141,6 +2141,7 @@ struct ServeGroup {
     uint64_t q_head = 0, q_tail = 0;
     uint64_t seq = 0;            // slices enqueued
     uint64_t in_flight = 0;      // particles parked after the last slice read
+    uint64_t remainders = 0;     // chunk remainders left then
     uint64_t pool_cap = 0;
     double* exL = nullptr;  // energy form: allocated when the first energy-form request arrives
     double* exP = nullptr;
@@ -2533,8 +2534,14 @@ cosmica_status admit(cosmica_ctx* ctx)
         std::vector<double> cost(g->segs_h.size(), 0.0);
         for (size_t b = 0; b < q->job.rig.size(); ++b)
             cost[s0 + b] = expected_steps(q->job.helio, q->job.species, q->job.rig[b]);
+        // (small requests in smaller chunks, so that slices of the latency kernel
+        // can spread them over its waves)
+        int chunk = L.chunk;
+        if (ctx->auto_launch[q->model][q->prec])
+            chunk = (int)std::min<uint64_t>(
+                (uint64_t)chunk, std::max<uint64_t>(1, q->job.total / ((uint64_t)ctx->num_cus * 4)));
         std::vector<ChunkDev> chunks;
-        make_chunks(g->segs_h, ids, L.chunk, L.order, &chunks, &cost);
+        make_chunks(g->segs_h, ids, chunk, L.order, &chunks, &cost);
         cosmica_status st = q->prec == 1 ? upload_slot<float>(g, q) : upload_slot<double>(g, q);
         if (st != COSMICA_OK) return st;
         // the slot's counters start again (stream-ordered after every slice
@@ -2556,6 +2563,7 @@ template <typename R>
 cosmica_status launch_slice(ServeGroup* g)
 {
     cosmica_ctx* ctx = g->ctx;
+    const cosmica_launch& L = ctx->launch[g->model][g->prec];
     hipStream_t s = ctx->serve_stream;
     const int p = (int)(g->seq & 1u), o = p ^ 1;
     uint32_t* c = g->ctl_d;
@@ -2587,7 +2595,27 @@ cosmica_status launch_slice(ServeGroup* g)
     // The variants for a squashed heliosphere or the energy form may fit fewer
     // lanes than the previous slice parked particles: the closing kernel
     // carries what no wave claimed over to the next slice.
-    const int grid = g->grid_var[(a.shaped ? 1 : 0) | (a.energy ? 2 : 0)];
+    int grid = g->grid_var[(a.shaped ? 1 : 0) | (a.energy ? 2 : 0)];
+    if (ctx->auto_launch[g->model][g->prec]) {
+        // Slices run the latency kernel while every particle left finds a lane of
+        // it: at most what was parked or left over after the last slice read, and
+        // the queue.
+        // Bursts with the throughput kernel alone and so: 8 requests (5.7e10
+        // steps) 433 and 405 ms, 1 (1.2e10) 148 and 129 ms, 4 small ones (1.9e9)
+        // 98 and 68 ms, 3 small ones in binary64 (4.8e8) 408 and 268 ms.
+        const uint64_t queued = g->q_tail - g->q_head;
+        const uint64_t left = g->in_flight + (queued + g->remainders) * (uint64_t)L.chunk;
+        const uint64_t simd_waves = (uint64_t)ctx->num_cus * 4;
+        const uint64_t most = g->model == 1 && g->prec == COSMICA_PREC_FP64 ? 1 : 2;
+        if (left <= most * simd_waves * 64) {
+            const uint64_t bpc = left <= simd_waves * 64 ? 1 : most;
+            const uint64_t waves = simd_waves * bpc;
+            a.latency = 1u;
+            a.lane_cap = queued == 0 ? 0u
+                                     : (uint32_t)std::max<uint64_t>(1, (left + waves - 1) / waves);
+            grid = std::min<int>(grid, (int)(waves * 64 / (uint64_t)g->block));
+        }
+    }
     HIP_TRY(launch_model<R>(g->model, a, grid, g->block, s));
     CloseArgs k;
     std::memset(&k, 0, sizeof(k));
@@ -2746,6 +2774,7 @@ cosmica_status read_slice(ServeGroup* g, uint64_t seq)
     if (c[ServeGroup::kCtlOverflow] != 0u) return COSMICA_EDEVICE;
     g->q_head = (uint64_t)c[0] | ((uint64_t)c[1] << 32);
     g->in_flight = c[ServeGroup::park_word(p, 0)];
+    g->remainders = c[ServeGroup::park_word(p, 1)];
     for (auto it = g->resident.begin(); it != g->resident.end();) {
         Req* q = *it;
         if (q->first_slice <= seq && c[ServeGroup::kCtlDone + q->slot] >= q->job.total) {

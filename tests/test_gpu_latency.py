@@ -80,3 +80,26 @@ def test_latency_kernel_mixed_jobs_caps_and_non_finite(precision):
     r, _ = _both(jobs, precision)
     assert np.all(r[4]["n_capped"] == 70)
     assert r[5]["n_capped"].sum() > 0
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("explicit", [False, True])
+def test_served_slices_of_both_kernels(precision, explicit, monkeypatch):
+    """Requests too small for one particle a wave, of one chunk remainder, and
+    of both models, in slices short enough to park and resume many times, with
+    the latency kernel's slices (default shape) and without (explicit shape)."""
+    monkeypatch.setenv("COSMICA_SLICE_MS", "0.3")
+    jobs = [dict(_job("3d", 3, 7, seed=11, tag=1)), dict(_job("energy", 2, 700, seed=12, tag=2)),
+            dict(_job("heliosheath", 4, 411, seed=13, tag=3)), dict(_job("radial", 2, 33, seed=14)),
+            W.make_job(W.c2_helio(), W.species("e-"), [0.5, 5.0], 100, seed=3, job_tag=9)]
+    with C.Engine(0) as e:
+        if explicit:
+            for m in (0, 1):
+                e.set_launch(m, precision)
+        tickets = [e.submit(j, precision) for j in jobs]
+        for t in tickets:
+            assert t.wait(120000) == C.OK
+        for j, t in zip(jobs, tickets):
+            alone, got = e.run(j, precision)[0], t.result()
+            for k in KEYS:
+                np.testing.assert_array_equal(got[k], alone[k], err_msg=k)
