@@ -314,37 +314,94 @@ __device__ __forceinline__ bool outside_boundary(const JobReg<R>& J,
     return out;
 }
 
+// Binary64 elementary operations shared by the four lanes of a quad that hold
+// the same particle: each lane takes one of the operands, so up to four
+// divisions, square roots or sine-cosine pairs cost one and a few moves (819 ->
+// 640 VALU instructions a step; one particle: 1.56 -> 1.26 us per step).  The
+// operands' multiply-adds are written out as the fused ones that the compiler
+// forms in the other kernels, so the bits are the same.
+__device__ __forceinline__ double quad_pick(double a, double b, double c, double d)
+{
+    const uint32_t q = __lane_id() & 3u;
+    const double ab = q == 0u ? a : b, cd = q == 2u ? c : d;
+    return q < 2u ? ab : cd;
+}
+// The value that lane I of the quad holds.
+template <int I>
+__device__ __forceinline__ double quad_get(double v)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, 0x55 * I, 0xf, 0xf, true);
+    const uint32_t hi =
+        (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), 0x55 * I, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
 // Local coefficients, written to share every common factor:
 //   g = 1/(1+Gamma^2) = V^2/(V^2+w^2), Gamma g = V w/(V^2+w^2), Gamma^2 g = 1 - g
 //   (w = Omega r sin(theta)), B from one reciprocal square root of 2 K_rr with
 //   B_phiphi = 2 sqrt(kperp/kpar) kpar / sqrt(2 K_rr), B_thth = sqrt(2 kperp).
-template <typename R, bool FULL>
+// QUAD (binary64): the lanes of each quad hold the same particle and share the
+// divisions, square roots and sine-cosine pairs.
+template <typename R, bool FULL, bool QUAD = false>
 __device__ __forceinline__ void coeffs3d(const JobReg<R>& J, const RegionDev<R>& g, double rd,
                                          R P, R th, R ph, Coef3<R>& c)
 {
     using M = Mth<R>;
     const R r0 = (R)rd;
     const R r = r0 > M::kRFloor ? r0 : M::kRFloor;
-    R st, ct;
-    M::sincos_rad(th, &st, &ct);
+    R st, ct, sc, cc;  // of theta, and of the sheet's phase
+    if constexpr (QUAD) {
+        R sn, cs;
+        M::sincos_rad((__lane_id() & 1u) == 0u ? th : fma(g.om_vs, r, ph), &sn, &cs);
+        st = quad_get<0>(sn);
+        ct = quad_get<0>(cs);
+        sc = quad_get<1>(sn);
+        cc = quad_get<1>(cs);
+    } else {
+        M::sincos_rad(th, &st, &ct);
+    }
     st = st > M::kSinFloor ? st : M::kSinFloor;
-    const R invr = M::rcp(r);
-    const R invst = M::rcp(st);
-    const R cot = ct * invst;
-    const R irs = invr * invst;
+    R invr, invst, cot, irs, inve, invP, invV, invD, invy, invk;
+    if constexpr (!QUAD) {
+        invr = M::rcp(r);
+        invst = M::rcp(st);
+        cot = ct * invst;
+        irs = invr * invst;
+    }
     // wind: slow inside |latitude| <= tilt of the shell, fast outside
     const R lam = (R)(0.5 * kPi) - th;
     const R V = (fabs(lam) <= g.alpha) ? g.vs : g.vf;
     // diffusion tensor: k_par along b ~ (1, 0, -Gamma), k_perp across
     const R pc = J.abs_z * P;
-    const R beta = pc * M::rsqrt(pc * pc + J.mass2);
+    if constexpr (QUAD) {
+        const R q = M::rcp(quad_pick(r, M::sqrt(fma(pc, pc, J.mass2)), P, V + J.v_nodrift));
+        invr = quad_get<0>(q);
+        inve = quad_get<1>(q);
+        invP = quad_get<2>(q);
+        invV = quad_get<3>(q);
+    } else {
+        inve = M::rsqrt(pc * pc + J.mass2);
+    }
+    const R beta = pc * inve;
     const R bP = beta * P;
     const R kpar = g.k0 * bP;
     const R kperp = J.kfrac * kpar;
     const R dk = J.omf * kpar;
     const R w = (J.omega * r) * st;  // corotation speed; Gamma = w / V
     const R V2 = V * V;
-    const R invD = M::rcp(w * w + V2);
+    if constexpr (QUAD) {
+        const R y = g.tana * sc;
+        const R q = M::rcp(quad_pick(st, fma(w, w, V2), fma(y, y, (R)1.0), kpar));
+        invst = quad_get<0>(q);
+        invD = quad_get<1>(q);
+        invy = quad_get<2>(q);
+        invk = quad_get<3>(q);
+        cot = ct * invst;
+        irs = invr * invst;
+    } else {
+        invD = M::rcp(w * w + V2);
+    }
     const R gq = V2 * invD;          // 1 / (1 + Gamma^2)
     const R Gg = (V * invD) * w;     // Gamma / (1 + Gamma^2)
     const R GGg = (R)1.0 - gq;       // Gamma^2 / (1 + Gamma^2)
@@ -355,12 +412,20 @@ __device__ __forceinline__ void coeffs3d(const JobReg<R>& J, const RegionDev<R>&
     const R dKrr = q * GGg;
     const R dKrp = q * Gg;
     const R rr = r * r;
+    R sqG, sqK, Btt;  // square roots of 1 + Gamma^2 and 2 K_rr; B_thth
+    if constexpr (QUAD) {
+        const R Gam = w * invV, tK = Krr + Krr;
+        const R q = M::sqrt(quad_pick(fma(Gam, Gam, (R)1.0), tK, J.twof * kpar, tK));
+        sqG = quad_get<0>(q);
+        sqK = quad_get<1>(q);
+        Btt = quad_get<2>(q);
+    }
 
     R vdr = 0, vdt = 0, vdp = 0, Hw = 1;
     // binary32: computed for every lane, with sqA = 0 and a unit wind speed in
     // Gamma for jobs without drift (whose wind may be zero), so no branch
     if (std::is_same<R, float>::value || J.drift) {
-        const R invV = M::rcp(V + J.v_nodrift);
+        if constexpr (!QUAD) invV = M::rcp(V + J.v_nodrift);
         const R Gam = w * invV;
         const R Gam2 = Gam * Gam;
         // kappa_A / sqrt(1 + Gamma^2) with kappa_A = beta P / (3 |B|)
@@ -371,7 +436,6 @@ __device__ __forceinline__ void coeffs3d(const JobReg<R>& J, const RegionDev<R>&
         {
             // wavy sheet: latitude atan(tan(alpha) sin(phi + Omega r / Vs)),
             // polarity factor tanh((theta_cs - theta) / Delta), Delta = 2 r_L / r
-            R sc, cc;
             if constexpr (std::is_same<R, float>::value) {
                 // The phase Omega r / Vs reaches hundreds of radians, where a
                 // binary32 ulp is a visible part of the sheet's width: it is
@@ -379,18 +443,23 @@ __device__ __forceinline__ void coeffs3d(const JobReg<R>& J, const RegionDev<R>&
                 // binary64, so the sine sees [0, 2) revolutions at any wind speed.
                 const float frac = (float)__builtin_amdgcn_fract(g.om_rev * rd);  // v_fract_f64
                 M::sincos_rev(fmaf(ph, 0.159154943091895336f, frac), &sc, &cc);
-            } else {
+            } else if constexpr (!QUAD) {
                 M::sincos_rad(g.om_vs * r + ph, &sc, &cc);
             }
             const R y = g.tana * sc;
             const R u = lam - M::atan(y);
             // 1/Delta = r |B| / (2 r_L coefficient P), |B| = br0 sqrt(1+Gamma^2) / r^2
             // (in binary32 times 4, and Hp below over 4: their product is exact)
-            const R invDelta = (J.hb * M::sqrt((R)1.0 + Gam2)) * (invr * M::rcp(P));
+            if constexpr (!QUAD) {
+                sqG = M::sqrt((R)1.0 + Gam2);
+                invP = M::rcp(P);
+            }
+            const R invDelta = (J.hb * sqG) * (invr * invP);
             // without the sheet the argument is +inf: Hw = 1, Hp = 0, no sheet drift
             R Hp;
             M::tanh_sech2_x4(u * invDelta + J.sheet_off, &Hw, &Hp);
-            const R cs = (-g.tana * cc) * M::rcp(y * y + (R)1.0);
+            if constexpr (!QUAD) invy = M::rcp(y * y + (R)1.0);
+            const R cs = (-g.tana * cc) * invy;
             const R gr = cs * g.om_vs;  // d theta_cs / dr
             const R gph = cs * irs;     // (1/(r sin)) d theta_cs / dphi
             // grad Hw x W, grad Hw = (Hp/Delta)(grad u - u grad ln Delta)
@@ -415,23 +484,34 @@ __device__ __forceinline__ void coeffs3d(const JobReg<R>& J, const RegionDev<R>&
     // time step: min(dt_max, f_diff r^2 / k_par, f_adv r / |A_det|); fmin keeps
     // the running value when a limit is NaN, like the comparison d < dt would
     R dt = J.dt_max;
-    const R d1 = (J.diff_frac * rr) * M::rcp(kpar);
+    if constexpr (!QUAD) invk = M::rcp(kpar);
+    const R d1 = (J.diff_frac * rr) * invk;
     dt = fmin(d1, dt);
+    R rs;  // 1 / sqrt(2 K_rr)
     {
         // adv_frac is +inf when the limit is off, and a2 = 0 gives d2 = inf too
         const R at = r * c.At;
         const R ap = (r * st) * c.Ap;
         const R a2 = c.Ar * c.Ar + (at * at + ap * ap);
-        const R d2 = (J.adv_frac * r) * M::rsqrt(a2);
+        R inva;
+        if constexpr (QUAD) {
+            const R q = M::rcp((__lane_id() & 1u) == 0u ? M::sqrt(a2) : sqK);
+            inva = quad_get<0>(q);
+            rs = quad_get<1>(q);
+        } else {
+            inva = M::rsqrt(a2);
+        }
+        const R d2 = (J.adv_frac * r) * inva;
         dt = fmin(d2, dt);
     }
     c.dt = dt;
     const R tK = Krr + Krr;
-    const R rs = M::rsqrt(tK);
+    if constexpr (!QUAD) rs = M::rsqrt(tK);
     c.Brr = tK * rs;
     c.Bpr = (Krp + Krp) * rs;
     c.Bpp = (J.sqf2 * kpar) * rs;
-    c.Btt = M::sqrt(J.twof * kpar);
+    if constexpr (!QUAD) Btt = M::sqrt(J.twof * kpar);
+    c.Btt = Btt;
     c.invr = invr;
     c.invst = invst;
     if (FULL) {
@@ -481,7 +561,7 @@ __device__ __forceinline__ bool outside_turn(double x) { return !(x >= 0.0 && x 
 
 // One EM step of the 3D model with the normals z and the particle's region
 // entry g.  The caller applies the reflections and tests for the exit.
-template <typename R, bool ENERGY>
+template <typename R, bool ENERGY, bool QUAD = false>
 __device__ __forceinline__ void step3d(const JobReg<R>& J, const RegionDev<R>& g, PState<R>& s,
                                        const R* z)
 {
@@ -498,7 +578,7 @@ __device__ __forceinline__ void step3d(const JobReg<R>& J, const RegionDev<R>& g
         }
     }
     Coef3<R> c;
-    coeffs3d<R, false>(J, g, s.r, Pc, s.th, s.ph, c);
+    coeffs3d<R, false, QUAD>(J, g, s.r, Pc, s.th, s.ph, c);
     const R dt = c.dt;
     const R sdt = M::sqrt(dt);
     double r1;
@@ -973,6 +1053,7 @@ __device__ __forceinline__ void propagate(const PropArgs<R>& a)
         auto tail = [&](auto ah, auto sl) {
             constexpr bool AHEAD = decltype(ah)::value;
             constexpr bool SL = decltype(sl)::value;
+            constexpr bool QUAD = AHEAD && std::is_same<R, double>::value;
             constexpr bool WRAP = M3D && !AHEAD && std::is_same<R, float>::value;
             const uint64_t act = __builtin_amdgcn_ballot_w64(active);
             const uint32_t na = (uint32_t)__popcll(act);
@@ -1056,7 +1137,7 @@ __device__ __forceinline__ void propagate(const PropArgs<R>& a)
                                                  pid, bin, J.job_tag, z);
                         ++i;
                         if constexpr (M3D)
-                            step3d<R, ENERGY>(J, g, s, z);
+                            step3d<R, ENERGY, QUAD>(J, g, s, z);
                         else
                             step1d<R>(J, g, s, z);
                         int k = region_of(J, fabs(s.r));
