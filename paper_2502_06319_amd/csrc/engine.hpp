@@ -163,6 +163,12 @@ struct CloseArgs {
     uint32_t* next_counters;  // 4 words cleared at the end
 };
 
+// The per-bin reduction sums parts of kReducePart exits in order; bins of up to
+// kReduceMaxParts parts may be spread over workgroups, with kReducePartBytes of
+// device memory for each part.
+constexpr int kReducePart = 1024;
+constexpr int kReduceMaxParts = 4096;
+constexpr size_t kReducePartBytes = 576;
 struct ReduceArgs {
     const SegmentDev* segs;
     const LisDev* lis;  // per job
@@ -179,6 +185,8 @@ struct ReduceArgs {
     uint32_t* n_capped;
     uint32_t* n_nan;
     uint32_t out_base;  // output index of segment seg_base
+    uint32_t parts;     // parts of the largest bin, if spread over workgroups (else 0)
+    unsigned char* partial;  // segments of the launch * parts * kReducePartBytes
 };
 
 // Re-weighting of exit records with tabulated spectra.

@@ -1366,9 +1366,6 @@ hipError_t occupancy_propagate(int model, int prec, int block, int shaped, int e
 // Per-bin reduction.
 // ---------------------------------------------------------------------------
 constexpr int kReduceBlock = 256;
-// The reduction of one rigidity bin runs in one workgroup; a served request
-// reduces its few bins alone, so each one takes a whole CU's worth of waves.
-constexpr int kBinBlock = 1024;
 
 template <typename T, int B = kReduceBlock>
 __device__ __forceinline__ T block_sum(T v, T* sh)
@@ -1410,83 +1407,222 @@ __device__ __forceinline__ double energy_weight(const LisDev& L, double beta0, d
     return beta0 / beta_of(L, P) * (L.norm * ::pow(P, -L.index)) * ::exp(-loss);
 }
 
-__global__ void __launch_bounds__(kBinBlock) k_reduce(const ReduceArgs a)
+// The first exit of a segment that is neither capped nor non-finite (~0: none).
+__device__ __forceinline__ uint32_t first_used(const SegmentDev& sg, const uint32_t* exNF,
+                                               uint32_t* sh)
+{
+    if (threadIdx.x == 0) *sh = ~0u;
+    for (uint32_t i0 = 0; i0 < sg.count; i0 += kReduceBlock) {
+        const uint32_t i = i0 + threadIdx.x;
+        __syncthreads();
+        if (i < sg.count && (exNF[sg.out_offset + i] >> kFlagShift) == 0u) atomicMin(sh, i);
+        __syncthreads();
+        if (*sh != ~0u) break;
+    }
+    return *sh;
+}
+
+// Mean and standard error from the sums about s of n weights.
+__device__ __forceinline__ void mean_and_se(double n, double s, double s1, double s2,
+                                            double* mean, double* se)
+{
+    *mean = n > 0.0 ? s + s1 / n : 0.0;
+    double m2 = s2 - s1 * (s1 / n);
+    m2 = m2 < 0.0 ? 0.0 : m2;
+    *se = n > 1.0 ? ::sqrt(m2 / (n - 1.0) / n) : 0.0;
+}
+
+// Sums of one part (kReducePart exits) of a bin, or of its parts in order.
+struct BinSums {
+    double s1, s2, st;              // of w - s and its square, and of the exit times
+    unsigned long long sn;          // steps
+    unsigned long long used, capped, nan;
+    __device__ void add(const BinSums& o)
+    {
+        s1 += o.s1;
+        s2 += o.s2;
+        st += o.st;
+        sn += o.sn;
+        used += o.used;
+        capped += o.capped;
+        nan += o.nan;
+    }
+};
+static_assert(sizeof(BinSums) + (kNHist + 1) * sizeof(uint32_t) == kReducePartBytes, "partial layout");
+
+__device__ __forceinline__ void write_bin(const ReduceArgs& a, const SegmentDev& sg,
+                                          const LisDev& L, uint32_t ob, double about,
+                                          const BinSums& t)
+{
+    // momentum form: mean of f_LIS(P_ex) times P0^2; energy form: the mean
+    // contribution itself
+    const double p2 = L.energy ? 1.0 : sg.P0 * sg.P0;
+    const double n = (double)t.used;
+    double mean, se;
+    mean_and_se(n, about, t.s1, t.s2, &mean, &se);
+    if (a.flux) a.flux[ob] = p2 * mean;
+    if (a.flux_se) a.flux_se[ob] = p2 * se;
+    if (a.mean_t) a.mean_t[ob] = t.used > 0 ? t.st / n : 0.0;
+    if (a.steps) a.steps[ob] = t.sn;
+    if (a.n_capped) a.n_capped[ob] = (uint32_t)t.capped;
+    if (a.n_nan) a.n_nan[ob] = (uint32_t)t.nan;
+}
+
+// One pass over a bin's exits, in parts of kReducePart whose sums are added in
+// order, so the bits do not depend on how the parts are spread: one workgroup
+// per bin (SPLIT = false) where there are bins enough to fill the device, one
+// per part (a.partial, then k_reduce_sum) where there are few.  The weights are
+// summed about that of the bin's first used exit (see the re-weighting below):
+// one power per exit instead of one for the mean and one for the variance.
+// Bound by FP64 VALU and latency.  31 bins of 3,001 to 20,011 exits: 104 us in
+// one workgroup per bin with two passes, 28 us so; 20 of 5,000: 36 and
+// 21 us.
+template <bool SPLIT>
+__global__ void __launch_bounds__(kReduceBlock) k_reduce(const ReduceArgs a)
 {
     __shared__ uint32_t hist[kNHist];
-    __shared__ double shd[kBinBlock / 64];
-    __shared__ unsigned long long shu[kBinBlock / 64];
-    const uint32_t sidx = a.seg_base + blockIdx.x;
-    const SegmentDev sg = a.segs[sidx];
+    __shared__ double shd[3][kReduceBlock / 64];
+    __shared__ unsigned long long shu[2][kReduceBlock / 64];
+    __shared__ uint32_t pilot;
+    const SegmentDev sg = a.segs[a.seg_base + blockIdx.x];
+    const uint32_t first = SPLIT ? blockIdx.y * (uint32_t)kReducePart : 0u;
+    if (first >= sg.count) return;
+    const uint32_t last = SPLIT ? min(sg.count - first, (uint32_t)kReducePart) + first : sg.count;
     const LisDev L = a.lis[sg.job];
-    for (int i = threadIdx.x; i < kNHist; i += kBinBlock) hist[i] = 0u;
-    __syncthreads();
-    double sw = 0.0, st = 0.0;
-    unsigned long long sn = 0, ncap = 0, nnan = 0, nused = 0;
     const double inv_p0 = 1.0 / sg.P0;
     const double beta0 = L.energy ? beta_of(L, sg.P0) : 0.0;
-    for (uint32_t i = threadIdx.x; i < sg.count; i += kBinBlock) {
-        const uint32_t o = sg.out_offset + i;
-        const uint32_t nf = a.exNF[o];
-        const uint32_t fl = nf >> kFlagShift;
-        sn += nf & ((1u << kFlagShift) - 1u);
-        if (fl & kFlagCapped) {
-            ++ncap;
-            continue;
-        }
-        if (fl & kFlagNaN) {
-            ++nnan;
-            continue;
-        }
-        const double P = a.exP[o];
-        sw += L.energy ? energy_weight(L, beta0, P, a.exL[o]) : lis_weight(L, P);
-        st += a.exT[o];
-        ++nused;
-        int j = (int)::floor(128.0 * ::log10(P * inv_p0) / 3.0);
-        j = j < 0 ? 0 : (j > 128 ? 128 : j);
-        atomicAdd(&hist[j], 1u);
+    auto weight = [&](double P, uint32_t o) {
+        return L.energy ? energy_weight(L, beta0, P, a.exL[o]) : lis_weight(L, P);
+    };
+    for (int i = threadIdx.x; i < kNHist; i += kReduceBlock) hist[i] = 0u;
+    double about = 0.0;
+    if (const uint32_t p = first_used(sg, a.exNF, &pilot); p != ~0u) {
+        const uint32_t o = sg.out_offset + p;
+        about = weight(a.exP[o], o);
+        if (!(fabs(about) < __builtin_huge_val())) about = 0.0;
     }
-    const double SW = block_sum<double, kBinBlock>(sw, shd);
-    const double ST = block_sum<double, kBinBlock>(st, shd);
-    const unsigned long long SN = block_sum<unsigned long long, kBinBlock>(sn, shu);
-    const unsigned long long NC = block_sum<unsigned long long, kBinBlock>(ncap, shu);
-    const unsigned long long NN = block_sum<unsigned long long, kBinBlock>(nnan, shu);
-    const unsigned long long NU = block_sum<unsigned long long, kBinBlock>(nused, shu);
-    const double N = (double)NU;
-    const double mean = NU > 0 ? SW / N : 0.0;
-    double ss = 0.0;
-    if (NU > 1) {
-        for (uint32_t i = threadIdx.x; i < sg.count; i += kBinBlock) {
+    const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
+    BinSums total = {0.0, 0.0, 0.0, 0, 0, 0, 0};  // thread 0
+    for (uint32_t p0 = first; p0 < last; p0 += kReducePart) {
+        const uint32_t end = min(last - p0, (uint32_t)kReducePart) + p0;
+        double s1 = 0.0, s2 = 0.0, st = 0.0;
+        unsigned long long sn = 0, counts = 0;  // used, capped, non-finite: 16 bits each
+        for (uint32_t i = p0 + threadIdx.x; i < end; i += kReduceBlock) {
             const uint32_t o = sg.out_offset + i;
-            if ((a.exNF[o] >> kFlagShift) != 0u) continue;
-            const double w = L.energy ? energy_weight(L, beta0, a.exP[o], a.exL[o])
-                                      : lis_weight(L, a.exP[o]);
-            const double dw = w - mean;
-            ss += dw * dw;
+            const uint32_t nf = a.exNF[o];
+            const double P = a.exP[o], t = a.exT[o];
+            const uint32_t fl = nf >> kFlagShift;
+            sn += nf & ((1u << kFlagShift) - 1u);
+            if (fl != 0u) {
+                if (fl & kFlagCapped)
+                    counts += 1ull << 16;
+                else if (fl & kFlagNaN)
+                    counts += 1ull << 32;
+                continue;
+            }
+            const double d = weight(P, o) - about;
+            s1 += d;
+            s2 += d * d;
+            st += t;
+            ++counts;
+            int j = (int)::floor(128.0 * ::log10(P * inv_p0) / 3.0);
+            j = j < 0 ? 0 : (j > 128 ? 128 : j);
+            atomicAdd(&hist[j], 1u);
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            s1 += __shfl_down(s1, off, 64);
+            s2 += __shfl_down(s2, off, 64);
+            st += __shfl_down(st, off, 64);
+            sn += __shfl_down(sn, off, 64);
+            counts += __shfl_down(counts, off, 64);
+        }
+        __syncthreads();
+        if (lane == 0) {
+            shd[0][wid] = s1;
+            shd[1][wid] = s2;
+            shd[2][wid] = st;
+            shu[0][wid] = sn;
+            shu[1][wid] = counts;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            BinSums part = {0.0, 0.0, 0.0, 0, 0, 0, 0};
+            for (int w = 0; w < kReduceBlock / 64; ++w) {
+                const unsigned long long c = shu[1][w];
+                part.add(BinSums{shd[0][w], shd[1][w], shd[2][w], shu[0][w], c & 0xffffull,
+                                 (c >> 16) & 0xffffull, c >> 32});
+            }
+            total.add(part);
         }
     }
-    const double SS = block_sum<double, kBinBlock>(ss, shd);
     __syncthreads();
+    if constexpr (SPLIT) {
+        unsigned char* q = a.partial + (size_t)kReducePartBytes * ((size_t)blockIdx.x * a.parts + blockIdx.y);
+        if (threadIdx.x == 0) *(BinSums*)q = total;
+        uint32_t* h = (uint32_t*)(q + sizeof(BinSums));
+        for (int i = threadIdx.x; i < kNHist; i += kReduceBlock) h[i] = hist[i];
+    } else {
+        const uint32_t ob = a.out_base + blockIdx.x;
+        if (a.hist != nullptr)
+            for (int i = threadIdx.x; i < kNHist; i += kReduceBlock)
+                a.hist[(size_t)ob * kNHist + i] = hist[i];
+        if (threadIdx.x == 0) write_bin(a, sg, L, ob, about, total);
+    }
+}
+
+// The parts of a bin, in order: thread 0 adds the sums, the others the
+// histograms.
+__global__ void __launch_bounds__(kReduceBlock) k_reduce_sum(const ReduceArgs a)
+{
+    __shared__ BinSums sums[kReduceBlock];
+    __shared__ uint32_t pilot;
+    const SegmentDev sg = a.segs[a.seg_base + blockIdx.x];
+    const uint32_t np = (sg.count + (uint32_t)kReducePart - 1) / (uint32_t)kReducePart;
+    const unsigned char* q = a.partial + (size_t)kReducePartBytes * ((size_t)blockIdx.x * a.parts);
+    BinSums total = {0.0, 0.0, 0.0, 0, 0, 0, 0};
+    for (uint32_t z0 = 0; z0 < np; z0 += kReduceBlock) {
+        const uint32_t n = min(np - z0, (uint32_t)kReduceBlock);
+        __syncthreads();
+        if (threadIdx.x < n)
+            sums[threadIdx.x] = *(const BinSums*)(q + (size_t)kReducePartBytes * (z0 + threadIdx.x));
+        __syncthreads();
+        if (threadIdx.x == 0)
+            for (uint32_t z = 0; z < n; ++z) total.add(sums[z]);
+    }
+    const uint32_t p = first_used(sg, a.exNF, &pilot);
     const uint32_t ob = a.out_base + blockIdx.x;
-    if (a.hist != nullptr)
-        for (int i = threadIdx.x; i < kNHist; i += kBinBlock)
-            a.hist[(size_t)ob * kNHist + i] = hist[i];
+    if (a.hist != nullptr) {
+        for (uint32_t i = threadIdx.x; i < (uint32_t)kNHist; i += kReduceBlock) {
+            uint32_t t = 0;
+#pragma unroll 4
+            for (uint32_t z = 0; z < np; ++z)
+                t += ((const uint32_t*)(q + (size_t)kReducePartBytes * z + sizeof(BinSums)))[i];
+            a.hist[(size_t)ob * kNHist + i] = t;
+        }
+    }
     if (threadIdx.x == 0) {
-        // momentum form: mean of f_LIS(P_ex) times P0^2; energy form: the mean
-        // contribution itself
-        const double p2 = L.energy ? 1.0 : sg.P0 * sg.P0;
-        if (a.flux) a.flux[ob] = p2 * mean;
-        if (a.flux_se) a.flux_se[ob] = NU > 1 ? p2 * ::sqrt(SS / (N - 1.0) / N) : 0.0;
-        if (a.mean_t) a.mean_t[ob] = NU > 0 ? ST / N : 0.0;
-        if (a.steps) a.steps[ob] = SN;
-        if (a.n_capped) a.n_capped[ob] = (uint32_t)NC;
-        if (a.n_nan) a.n_nan[ob] = (uint32_t)NN;
+        const LisDev L = a.lis[sg.job];
+        const double beta0 = L.energy ? beta_of(L, sg.P0) : 0.0;
+        double about = 0.0;
+        if (p != ~0u) {
+            const uint32_t o = sg.out_offset + p;
+            const double P = a.exP[o];
+            about = L.energy ? energy_weight(L, beta0, P, a.exL[o]) : lis_weight(L, P);
+            if (!(fabs(about) < __builtin_huge_val())) about = 0.0;
+        }
+        write_bin(a, sg, L, ob, about, total);
     }
 }
 
 hipError_t launch_reduce(const ReduceArgs& a, uint32_t n_segs, hipStream_t s)
 {
     if (n_segs == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_reduce, dim3(n_segs), dim3(kBinBlock), 0, s, a);
+    if (a.parts > 1 && a.parts <= (uint32_t)kReduceMaxParts && a.partial != nullptr) {
+        hipLaunchKernelGGL(k_reduce<true>, dim3(n_segs, a.parts), dim3(kReduceBlock), 0, s, a);
+        hipLaunchKernelGGL(k_reduce_sum, dim3(n_segs), dim3(kReduceBlock), 0, s, a);
+    } else {
+        hipLaunchKernelGGL(k_reduce<false>, dim3(n_segs), dim3(kReduceBlock), 0, s, a);
+    }
     return hipGetLastError();
 }
 
@@ -1557,16 +1693,6 @@ struct LisStep {
     double at, d;  // ln J at a knot, and the difference to the next one
 };
 
-// Mean and standard error from the sums about s of n weights.
-__device__ __forceinline__ void mean_and_se(double n, double s, double s1, double s2,
-                                            double* mean, double* se)
-{
-    *mean = n > 0.0 ? s + s1 / n : 0.0;
-    double m2 = s2 - s1 * (s1 / n);
-    m2 = m2 < 0.0 ? 0.0 : m2;
-    *se = n > 1.0 ? ::sqrt(m2 / (n - 1.0) / n) : 0.0;
-}
-
 __global__ void __launch_bounds__(kReduceBlock) k_reweight(const ReweightArgs a)
 {
     __shared__ LisStep tab[kReweightGroup * (kMaxLisKnots - 1)];
@@ -1612,15 +1738,7 @@ __global__ void __launch_bounds__(kReduceBlock) k_reweight(const ReweightArgs a)
         *k = kk;
         *f = x - (double)kk;
     };
-    // the segment's first used particle
-    if (threadIdx.x == 0) pilot = ~0u;
-    for (uint32_t i0 = 0; i0 < sg.count; i0 += kReduceBlock) {
-        const uint32_t i = i0 + threadIdx.x;
-        __syncthreads();
-        if (i < sg.count && (a.exNF[sg.out_offset + i] >> kFlagShift) == 0u) atomicMin(&pilot, i);
-        __syncthreads();
-        if (pilot != ~0u) break;
-    }
+    (void)first_used(sg, a.exNF, &pilot);
     if (threadIdx.x < (uint32_t)kReweightGroup) {
         double w = 0.0;
         if (pilot != ~0u) {

@@ -663,6 +663,16 @@ PassShape pass_shape(cosmica_ctx* ctx, int model, int prec, const PassWork& w, b
     return s;
 }
 
+// Parts of the largest of n_bins bins if their reduction is spread over
+// workgroups, else 0: where one workgroup per bin would leave CUs idle.
+uint32_t reduce_parts(const cosmica_ctx* ctx, uint64_t n_bins, uint64_t largest)
+{
+    const uint64_t parts = (largest + kReducePart - 1) / kReducePart;
+    if (n_bins >= (uint64_t)ctx->num_cus * 4 || parts < 2 || parts > (uint64_t)kReduceMaxParts)
+        return 0;
+    return (uint32_t)parts;
+}
+
 template <typename R>
 hipError_t launch_model(int model, const PropArgs<R>& a, int grid, int block, hipStream_t s);
 template <>
@@ -718,6 +728,8 @@ struct cosmica_plan {
     uint64_t* steps = nullptr;
     uint32_t* ncap = nullptr;
     uint32_t* nnan = nullptr;
+    uint32_t reduce_parts = 0;  // parts of the reduction (0: a workgroup per bin)
+    unsigned char* reduce_partial = nullptr;
     bool executed = false;
     bool own_out = true;
     bool uniform_key = false;  // every job has the same seed
@@ -1023,6 +1035,12 @@ cosmica_status cosmica_plan_create(cosmica_ctx* ctx, const cosmica_job* jobs, in
     if ((st = p->mem.alloc(&p->steps, ns)) != COSMICA_OK) return st;
     if ((st = p->mem.alloc(&p->ncap, ns)) != COSMICA_OK) return st;
     if ((st = p->mem.alloc(&p->nnan, ns)) != COSMICA_OK) return st;
+    uint64_t largest = 0;
+    for (const SegmentDev& s : p->segs) largest = std::max<uint64_t>(largest, s.count);
+    p->reduce_parts = reduce_parts(ctx, ns, largest);
+    if (p->reduce_parts != 0 &&
+        p->mem.alloc(&p->reduce_partial, ns * p->reduce_parts * kReducePartBytes) != COSMICA_OK)
+        p->reduce_parts = 0;  // no room: a workgroup per bin
     HIP_TRY(hipMemcpyAsync(p->segs_d, p->segs.data(), ns * sizeof(SegmentDev),
                            hipMemcpyHostToDevice, ctx->stream));
     for (int m = 0; m < 2; ++m)
@@ -1057,6 +1075,8 @@ cosmica_status cosmica_plan_execute(cosmica_plan* p, const cosmica_bins_dev* out
     r.exL = p->exL;
     r.seg_base = 0;
     r.out_base = 0;
+    r.parts = p->reduce_parts;
+    r.partial = p->reduce_partial;
     if (out == nullptr) {
         r.hist = p->hist;
         r.flux = p->flux;
@@ -1419,7 +1439,7 @@ cosmica_status run_static(cosmica_ctx* ctx, const cosmica_job* jobs, uint32_t n_
     StaticHost& H = *ctx->stat;
     // sizes of the work
     uint32_t n_bins = 0, n_orbit = 0;
-    uint64_t total = 0;
+    uint64_t total = 0, largest = 0;
     PassWork work[2];
     PassShape shape[2];
     bool energy = false, shaped = false, exits = false, ukey = true;
@@ -1452,6 +1472,7 @@ cosmica_status run_static(cosmica_ctx* ctx, const cosmica_job* jobs, uint32_t n_
             off += J.particles_per_bin[b];
             H.cost[ns] = expected_steps(*J.helio, *J.species, J.rigidity_gv[b]);
             work[J.helio->model].add(g.count, H.cost[ns]);
+            largest = std::max<uint64_t>(largest, g.count);
         }
     }
     // refill chunks of each model group in the launch's queue order; the chunk
@@ -1569,6 +1590,10 @@ cosmica_status run_static(cosmica_ctx* ctx, const cosmica_job* jobs, uint32_t n_
     r.exL = d.exL;
     r.seg_base = 0;
     r.out_base = 0;
+    // the parts' sums where the array has room past the work's buffers
+    r.parts = reduce_parts(ctx, n_bins, largest);
+    r.partial = (unsigned char*)at(Lo.total);
+    if (Lo.total + (size_t)n_bins * r.parts * kReducePartBytes > COSMICA_STATIC_BYTES) r.parts = 0;
     r.hist = (uint32_t*)at(Lo.hist);
     r.flux = (double*)at(Lo.flux);
     r.flux_se = (double*)at(Lo.se);
@@ -2160,6 +2185,8 @@ struct ServeGroup {
     uint64_t* r_steps = nullptr;
     uint32_t* r_ncap = nullptr;
     uint32_t* r_nnan = nullptr;
+    static constexpr uint32_t kReduceParts = 64 * kBinsPerSlot;  // parts of one request
+    unsigned char* r_partial = nullptr;
     std::vector<int> free_slots;
     std::vector<SegmentDev> segs_h;
     std::map<uint64_t, uint64_t> free_ranges;  // offset -> length of free pool ranges
@@ -2348,6 +2375,8 @@ cosmica_status group_create(cosmica_ctx* ctx, int model, int prec, ServeGroup** 
     if ((st = g->mem.alloc(&g->r_steps, B)) != COSMICA_OK) return st;
     if ((st = g->mem.alloc(&g->r_ncap, B)) != COSMICA_OK) return st;
     if ((st = g->mem.alloc(&g->r_nnan, B)) != COSMICA_OK) return st;
+    if (g->mem.alloc(&g->r_partial, ServeGroup::kReduceParts * kReducePartBytes) != COSMICA_OK)
+        g->r_partial = nullptr;  // no room: a workgroup per bin
     g->pool_cap = pool_particles(ctx);
     if (g->pool_cap < 1024) return COSMICA_ENOMEM;
     if ((st = g->mem.alloc(&g->exP, g->pool_cap)) != COSMICA_OK) return st;
@@ -2665,6 +2694,11 @@ cosmica_status finish_request(ServeGroup* g, Req* q)
     r.steps = g->r_steps;
     r.n_capped = g->r_ncap;
     r.n_nan = g->r_nnan;
+    uint64_t largest = 0;
+    for (uint32_t c : q->job.cnt) largest = std::max<uint64_t>(largest, c);
+    r.parts = reduce_parts(ctx, nb, largest);
+    r.partial = g->r_partial;
+    if (g->r_partial == nullptr || nb * r.parts > ServeGroup::kReduceParts) r.parts = 0;
     HIP_TRY(launch_reduce(r, nb, s));
     if (H.free_blocks.empty()) {
         unsigned char* b = nullptr;

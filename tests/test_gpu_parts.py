@@ -1,4 +1,4 @@
-"""Bins split over workgroups (re-weighting and exit ranges) at the edges of
+"""Bins split over workgroups (reduction, re-weighting, exit ranges) at the edges of
 the split: 1 exit, one workgroup's stride, the smallest part and one more, a
 remainder, flagged exits at a bin's start; against numpy over the plan's own
 exit records.  Sums of at most 2e4 FP64 terms: 1e-12 for the mean, 1e-9 for
@@ -60,3 +60,34 @@ def test_split_bins_of_equal_weights(eng):
     np.testing.assert_array_equal(se, 0.0)
     np.testing.assert_allclose(flux, np.tile([np.exp(9.0), np.exp(9.0 - 1.5 * np.log(4.0) / 0.5)],
                                              (5, 1)), rtol=1e-12)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_reduction_does_not_depend_on_the_split(eng, precision):
+    """A few bins at the edges of the reduction's parts (1,024 exits), alone (a
+    workgroup per part) and among 1,100 one-particle bins (a workgroup per
+    bin): the same bits; and numpy's statistics of the exit records."""
+    counts = [1, 1023, 1024, 1025, 2048, 3073, 7000]
+    job = W.make_job(W.helio_1d(), W.species("p"), W.log_bins(0.5, 20.0, len(counts)), counts)
+    many = [dict(job, rigidity_gv=[3.0] * 55, particles_per_bin=[1] * 55, job_tag=i + 1)
+            for i in range(20)]
+    for cap in (10_000_000, 500):
+        job["step_cap"] = cap
+        alone = eng.run(job, precision, exits=True)[0]
+        mixed = eng.run([job] + many, precision)[0]
+        for k in mixed:
+            np.testing.assert_array_equal(alone[k], mixed[k], err_msg=k)
+        at = 0
+        for b, (P0, n) in enumerate(zip(job["rigidity_gv"], counts)):
+            ex = alone["exits"][at:at + n]
+            at += n
+            P = ex["P"][ex["flags"] == 0]
+            w = W.LIS_NORM * P ** -W.LIS_INDEX * (P0 / P) ** 2
+            assert alone["steps"][b] == ex["n"].sum() and alone["hist"][b].sum() == len(P)
+            assert alone["n_capped"][b] == n - len(P)
+            if len(P) > 1:
+                np.testing.assert_allclose(alone["flux"][b], w.mean(), rtol=1e-12)
+                np.testing.assert_allclose(alone["flux_se"][b], w.std(ddof=1) / np.sqrt(len(P)),
+                                           rtol=1e-9)
+                np.testing.assert_allclose(alone["mean_exit_time_s"][b],
+                                           ex["t"][ex["flags"] == 0].mean(), rtol=1e-12)
