@@ -380,7 +380,6 @@ struct StaticHost {
     SegmentDev segs[COSMICA_STATIC_MAX_BINS];
     double cost[COSMICA_STATIC_MAX_BINS];
     uint32_t ids[COSMICA_STATIC_MAX_BINS];
-    uint32_t ncap[COSMICA_STATIC_MAX_BINS];
     ChunkDev chunks[kStaticMaxChunks];
 };
 
@@ -425,6 +424,14 @@ struct cosmica_ctx {
     std::unique_ptr<ServeHost> serve_host;  // the worker's pinned buffers and events
     cosmica_status serve_error = COSMICA_OK;
     std::unique_ptr<StaticHost> stat;  // host staging of cosmica_run_static
+    // Pinned staging of a call's tables and results, so that each crosses in one
+    // copy: a pageable source or target costs a stop per array (13 copies and 4
+    // stream waits made 180 of the 540 us of a radial check; 90 us so).  Larger
+    // tables or results go from and to pageable memory.
+    static constexpr size_t kUpBytes = 2u << 20, kDownBytes = 5u << 20;
+    unsigned char* up = nullptr;
+    unsigned char* down = nullptr;
+    hipEvent_t up_ev = nullptr;  // the last copy from `up`
     cosmica_ctx() = default;
     ~cosmica_ctx();  // defined once the serving types are complete
 };
@@ -695,6 +702,27 @@ hipError_t launch_model<double>(int model, const PropArgs<double>& a, int grid, 
 // ---------------------------------------------------------------------------
 // Plans.
 // ---------------------------------------------------------------------------
+// Offsets of a plan's per-bin results in their block.
+struct ResultAt {
+    size_t hist = 0, flux = 0, se = 0, mt = 0, steps = 0, ncap = 0, nnan = 0, total = 0;
+    ResultAt() = default;
+    explicit ResultAt(size_t bins)
+    {
+        auto take = [&](size_t bytes) {
+            const size_t o = total;
+            total += (bytes + 255) & ~(size_t)255;
+            return o;
+        };
+        hist = take(bins * kNHist * 4);
+        flux = take(bins * 8);
+        se = take(bins * 8);
+        mt = take(bins * 8);
+        steps = take(bins * 8);
+        ncap = take(bins * 4);
+        nnan = take(bins * 4);
+    }
+};
+
 struct cosmica_plan {
     cosmica_ctx* ctx = nullptr;
     int prec = 0;
@@ -705,7 +733,7 @@ struct cosmica_plan {
     uint64_t total_particles = 0;
     PassWork work[2];      // of the radial and the 3D particles
     PassShape shape[2];
-    std::vector<ChunkDev> chunks_h[2];
+    uint32_t n_chunks[2] = {0, 0};
     DevSet mem;
     void* jobs_d = nullptr;
     void* regions_d = nullptr;
@@ -728,6 +756,8 @@ struct cosmica_plan {
     uint64_t* steps = nullptr;
     uint32_t* ncap = nullptr;
     uint32_t* nnan = nullptr;
+    unsigned char* res = nullptr;  // the block that holds them
+    ResultAt res_at;
     uint32_t reduce_parts = 0;  // parts of the reduction (0: a workgroup per bin)
     unsigned char* reduce_partial = nullptr;
     bool executed = false;
@@ -742,41 +772,99 @@ struct cosmica_plan {
 
 namespace {
 
-template <typename R>
-cosmica_status upload_tables(cosmica_plan* p)
+// Offsets of arrays carved from one block, 256-byte aligned.
+struct Carve {
+    size_t at = 0;
+    size_t take(size_t bytes)
+    {
+        const size_t o = at;
+        at += (bytes + 255) & ~(size_t)255;
+        return o;
+    }
+};
+
+// Copies `bytes` to the device on the context's stream, filled in by `fill`
+// (from host memory that the copy may still read when this returns).
+template <typename F>
+cosmica_status upload_block(cosmica_ctx* ctx, void* dst, size_t bytes, F fill)
 {
-    const size_t nj = p->jobs.size();
-    std::vector<JobDev<R>> jh(nj);
-    std::vector<RegionDev<R>> rh(nj * kRegionStride);
-    std::vector<LisDev> lh(nj);
-    std::vector<OrbitDev> oh;
-    for (size_t j = 0; j < nj; ++j) {
-        make_tables<R>(head_of(p->jobs[j]), &jh[j], &rh[j * kRegionStride], &lh[j]);
-        jh[j].orbit_off = (uint32_t)oh.size();
-        const std::vector<double>& o = p->jobs[j].orbit;
-        for (size_t k = 0; k + 2 < o.size(); k += 3) oh.push_back(OrbitDev{o[k], o[k + 1], o[k + 2], 0.0});
+    if (bytes <= cosmica_ctx::kUpBytes) {
+        HIP_TRY(hipEventSynchronize(ctx->up_ev));
+        fill(ctx->up);
+        HIP_TRY(hipMemcpyAsync(dst, ctx->up, bytes, hipMemcpyHostToDevice, ctx->stream));
+        HIP_TRY(hipEventRecord(ctx->up_ev, ctx->stream));
+        return COSMICA_OK;
     }
-    JobDev<R>* jd = nullptr;
-    RegionDev<R>* rd = nullptr;
-    cosmica_status st;
-    if (!oh.empty()) {
-        if ((st = p->mem.alloc(&p->orbit_d, oh.size())) != COSMICA_OK) return st;
-        HIP_TRY(hipMemcpyAsync(p->orbit_d, oh.data(), oh.size() * sizeof(OrbitDev),
-                               hipMemcpyHostToDevice, p->ctx->stream));
+    std::vector<std::max_align_t> host((bytes + sizeof(std::max_align_t) - 1) /
+                                       sizeof(std::max_align_t));
+    fill((unsigned char*)host.data());
+    HIP_TRY(hipMemcpyAsync(dst, host.data(), bytes, hipMemcpyHostToDevice, ctx->stream));
+    HIP_TRY(hipStreamSynchronize(ctx->stream));  // pageable and local
+    return COSMICA_OK;
+}
+
+// Copies `bytes` of the device to host memory, after everything enqueued on the
+// context's stream; *host stays valid until the next download (`spill` holds
+// what does not fit the pinned staging).
+cosmica_status download_block(cosmica_ctx* ctx, const void* src, size_t bytes,
+                              std::vector<unsigned char>* spill, const unsigned char** host)
+{
+    unsigned char* h = ctx->down;
+    if (bytes > cosmica_ctx::kDownBytes) {
+        spill->resize(bytes);
+        h = spill->data();
     }
-    if ((st = p->mem.alloc(&jd, nj)) != COSMICA_OK) return st;
-    if ((st = p->mem.alloc(&rd, rh.size())) != COSMICA_OK) return st;
-    if ((st = p->mem.alloc(&p->lis_d, nj)) != COSMICA_OK) return st;
-    HIP_TRY(hipMemcpyAsync(jd, jh.data(), nj * sizeof(JobDev<R>), hipMemcpyHostToDevice,
-                           p->ctx->stream));
-    HIP_TRY(hipMemcpyAsync(rd, rh.data(), rh.size() * sizeof(RegionDev<R>),
-                           hipMemcpyHostToDevice, p->ctx->stream));
-    HIP_TRY(hipMemcpyAsync(p->lis_d, lh.data(), nj * sizeof(LisDev), hipMemcpyHostToDevice,
-                           p->ctx->stream));
-    // the host tables are pageable and local: the copies must be complete
-    HIP_TRY(hipStreamSynchronize(p->ctx->stream));
-    p->jobs_d = jd;
-    p->regions_d = rd;
+    HIP_TRY(hipMemcpyAsync(h, src, bytes, hipMemcpyDeviceToHost, ctx->stream));
+    HIP_TRY(hipStreamSynchronize(ctx->stream));
+    *host = h;
+    return COSMICA_OK;
+}
+
+// The plan's tables, segments and queues in one block.
+template <typename R>
+cosmica_status upload_tables(cosmica_plan* p, const std::vector<ChunkDev>* chunks)
+{
+    const size_t nj = p->jobs.size(), ns = p->segs.size();
+    size_t n_orbit = 0;
+    for (const JobCopy& j : p->jobs) n_orbit += j.orbit.size() / 3;
+    Carve c;
+    const size_t o_jobs = c.take(nj * sizeof(JobDev<R>));
+    const size_t o_reg = c.take(nj * kRegionStride * sizeof(RegionDev<R>));
+    const size_t o_lis = c.take(nj * sizeof(LisDev));
+    const size_t o_orbit = c.take(n_orbit * sizeof(OrbitDev));
+    const size_t o_segs = c.take(ns * sizeof(SegmentDev));
+    size_t o_ch[2];
+    for (int m = 0; m < 2; ++m) o_ch[m] = c.take(chunks[m].size() * sizeof(ChunkDev));
+    unsigned char* d = nullptr;
+    cosmica_status st = p->mem.alloc(&d, c.at);
+    if (st != COSMICA_OK) return st;
+    st = upload_block(p->ctx, d, c.at, [&](unsigned char* h) {
+        JobDev<R>* jh = (JobDev<R>*)(h + o_jobs);
+        RegionDev<R>* rh = (RegionDev<R>*)(h + o_reg);
+        LisDev* lh = (LisDev*)(h + o_lis);
+        OrbitDev* oh = (OrbitDev*)(h + o_orbit);
+        size_t no = 0;
+        for (size_t j = 0; j < nj; ++j) {
+            make_tables<R>(head_of(p->jobs[j]), &jh[j], &rh[j * kRegionStride], &lh[j]);
+            jh[j].orbit_off = (uint32_t)no;
+            const std::vector<double>& o = p->jobs[j].orbit;
+            for (size_t k = 0; k + 2 < o.size(); k += 3) oh[no++] = OrbitDev{o[k], o[k + 1], o[k + 2], 0.0};
+        }
+        std::memcpy(h + o_segs, p->segs.data(), ns * sizeof(SegmentDev));
+        for (int m = 0; m < 2; ++m)
+            if (!chunks[m].empty())
+                std::memcpy(h + o_ch[m], chunks[m].data(), chunks[m].size() * sizeof(ChunkDev));
+    });
+    if (st != COSMICA_OK) return st;
+    p->jobs_d = d + o_jobs;
+    p->regions_d = d + o_reg;
+    p->lis_d = (LisDev*)(d + o_lis);
+    p->orbit_d = (OrbitDev*)(d + o_orbit);
+    p->segs_d = (SegmentDev*)(d + o_segs);
+    for (int m = 0; m < 2; ++m) {
+        p->chunks_d[m] = (ChunkDev*)(d + o_ch[m]);
+        p->n_chunks[m] = (uint32_t)chunks[m].size();
+    }
     return COSMICA_OK;
 }
 
@@ -862,7 +950,7 @@ PassDev pass_of(const cosmica_plan* p)
     d.segs = p->segs_d;
     for (int m = 0; m < 2; ++m) {
         d.chunks[m] = p->chunks_d[m];
-        d.n_chunks[m] = (uint32_t)p->chunks_h[m].size();
+        d.n_chunks[m] = p->n_chunks[m];
         d.work[m] = p->work[m];
         d.shape[m] = p->shape[m];
     }
@@ -945,6 +1033,9 @@ cosmica_status cosmica_create(cosmica_ctx** out, int device, uint64_t hbm_budget
         ctx->own_stream = true;
     }
     for (int i = 0; i < 4; ++i) HIP_TRY(hipEventCreate(&ctx->ev[i]));
+    HIP_TRY(hipHostMalloc((void**)&ctx->up, cosmica_ctx::kUpBytes, hipHostMallocDefault));
+    HIP_TRY(hipHostMalloc((void**)&ctx->down, cosmica_ctx::kDownBytes, hipHostMallocDefault));
+    HIP_TRY(hipEventCreateWithFlags(&ctx->up_ev, hipEventDisableTiming));
     for (int m = 0; m < 2; ++m)
         for (int q = 0; q < 2; ++q) ctx->launch[m][q] = cosmica_launch{256, 0, (int)kSpreadChunk, 2};
     *out = ctx.release();
@@ -1003,21 +1094,17 @@ cosmica_status cosmica_plan_create(cosmica_ctx* ctx, const cosmica_job* jobs, in
     for (const JobCopy& jc : p->jobs) p->uniform_key &= jc.seed == p->key;
     for (const JobCopy& jc : p->jobs) p->shaped |= job_shaped(jc);
     for (const JobCopy& jc : p->jobs) p->energy |= jc.formulation == 1;
+    std::vector<ChunkDev> chunks[2];
     for (int m = 0; m < 2; ++m) {
         p->shape[m] =
             pass_shape(ctx, m, precision, p->work[m], p->shaped, p->energy, p->uniform_key);
         make_chunks(p->segs, ids[m], p->shape[m].chunk, ctx->launch[m][precision].order,
-                    &p->chunks_h[m], &cost);
+                    &chunks[m], &cost);
     }
-    cosmica_status st = precision == COSMICA_PREC_MIXED ? upload_tables<float>(p.get())
-                                                         : upload_tables<double>(p.get());
+    cosmica_status st = precision == COSMICA_PREC_MIXED ? upload_tables<float>(p.get(), chunks)
+                                                         : upload_tables<double>(p.get(), chunks);
     if (st != COSMICA_OK) return st;
     const size_t ns = p->segs.size();
-    if ((st = p->mem.alloc(&p->segs_d, ns)) != COSMICA_OK) return st;
-    for (int m = 0; m < 2; ++m)
-        if (!p->chunks_h[m].empty() &&
-            (st = p->mem.alloc(&p->chunks_d[m], p->chunks_h[m].size())) != COSMICA_OK)
-            return st;
     if ((st = p->mem.alloc(&p->counters_d, 8)) != COSMICA_OK) return st;
     if ((st = p->mem.alloc(&p->exP, total)) != COSMICA_OK) return st;
     if ((st = p->mem.alloc(&p->exT, total)) != COSMICA_OK) return st;
@@ -1028,27 +1115,21 @@ cosmica_status cosmica_plan_create(cosmica_ctx* ctx, const cosmica_job* jobs, in
         if ((st = p->mem.alloc(&p->exTh, total)) != COSMICA_OK) return st;
         if ((st = p->mem.alloc(&p->exPh, total)) != COSMICA_OK) return st;
     }
-    if ((st = p->mem.alloc(&p->hist, ns * kNHist)) != COSMICA_OK) return st;
-    if ((st = p->mem.alloc(&p->flux, ns)) != COSMICA_OK) return st;
-    if ((st = p->mem.alloc(&p->se, ns)) != COSMICA_OK) return st;
-    if ((st = p->mem.alloc(&p->mt, ns)) != COSMICA_OK) return st;
-    if ((st = p->mem.alloc(&p->steps, ns)) != COSMICA_OK) return st;
-    if ((st = p->mem.alloc(&p->ncap, ns)) != COSMICA_OK) return st;
-    if ((st = p->mem.alloc(&p->nnan, ns)) != COSMICA_OK) return st;
+    p->res_at = ResultAt(ns);
+    if ((st = p->mem.alloc(&p->res, p->res_at.total)) != COSMICA_OK) return st;
+    p->hist = (uint32_t*)(p->res + p->res_at.hist);
+    p->flux = (double*)(p->res + p->res_at.flux);
+    p->se = (double*)(p->res + p->res_at.se);
+    p->mt = (double*)(p->res + p->res_at.mt);
+    p->steps = (uint64_t*)(p->res + p->res_at.steps);
+    p->ncap = (uint32_t*)(p->res + p->res_at.ncap);
+    p->nnan = (uint32_t*)(p->res + p->res_at.nnan);
     uint64_t largest = 0;
     for (const SegmentDev& s : p->segs) largest = std::max<uint64_t>(largest, s.count);
     p->reduce_parts = reduce_parts(ctx, ns, largest);
     if (p->reduce_parts != 0 &&
         p->mem.alloc(&p->reduce_partial, ns * p->reduce_parts * kReducePartBytes) != COSMICA_OK)
         p->reduce_parts = 0;  // no room: a workgroup per bin
-    HIP_TRY(hipMemcpyAsync(p->segs_d, p->segs.data(), ns * sizeof(SegmentDev),
-                           hipMemcpyHostToDevice, ctx->stream));
-    for (int m = 0; m < 2; ++m)
-        if (!p->chunks_h[m].empty())
-            HIP_TRY(hipMemcpyAsync(p->chunks_d[m], p->chunks_h[m].data(),
-                                   p->chunks_h[m].size() * sizeof(ChunkDev),
-                                   hipMemcpyHostToDevice, ctx->stream));
-    HIP_TRY(hipStreamSynchronize(ctx->stream));
     *out = p.release();
     return COSMICA_OK;
 }
@@ -1111,7 +1192,9 @@ cosmica_status cosmica_plan_execute(cosmica_plan* p, const cosmica_bins_dev* out
     return COSMICA_OK;
 }
 
-static cosmica_status finish_timings(cosmica_ctx* ctx)
+// Section timings of the last execution; steps: its step counts on the host, if
+// they are there already.
+static cosmica_status finish_timings(cosmica_ctx* ctx, const uint64_t* steps = nullptr)
 {
     if (!ctx->timings_pending) return COSMICA_OK;
     HIP_TRY(hipEventSynchronize(ctx->ev[2]));
@@ -1121,11 +1204,15 @@ static cosmica_status finish_timings(cosmica_ctx* ctx)
     ctx->timings.propagate_ms = a;
     ctx->timings.reduce_ms = b;
     if (ctx->last_steps && ctx->last_nsteps) {
-        std::vector<uint64_t> s(ctx->last_nsteps);
-        HIP_TRY(hipMemcpy(s.data(), ctx->last_steps, s.size() * sizeof(uint64_t),
-                          hipMemcpyDeviceToHost));
+        std::vector<uint64_t> s;
+        if (steps == nullptr) {
+            s.resize(ctx->last_nsteps);
+            HIP_TRY(hipMemcpy(s.data(), ctx->last_steps, s.size() * sizeof(uint64_t),
+                              hipMemcpyDeviceToHost));
+            steps = s.data();
+        }
         uint64_t t = 0;
-        for (uint64_t v : s) t += v;
+        for (uint32_t i = 0; i < ctx->last_nsteps; ++i) t += steps[i];
         ctx->timings.steps = t;
     }
     ctx->timings_pending = false;
@@ -1138,21 +1225,21 @@ cosmica_status cosmica_plan_read(cosmica_plan* p, cosmica_result* results)
     if (!p->executed || !p->own_out) return COSMICA_EINVAL;
     cosmica_ctx* ctx = p->ctx;
     HIP_TRY(hipSetDevice(ctx->device));
-    HIP_TRY(hipStreamSynchronize(ctx->stream));
-    cosmica_status st = finish_timings(ctx);
-    if (st != COSMICA_OK) return st;
+    HIP_TRY(hipEventSynchronize(ctx->ev[2]));
     const auto t0 = std::chrono::steady_clock::now();
-    const size_t ns = p->segs.size();
-    std::vector<uint32_t> hist(ns * kNHist), ncap(ns), nnan(ns);
-    std::vector<double> flux(ns), se(ns), mt(ns);
-    std::vector<uint64_t> steps(ns);
-    HIP_TRY(hipMemcpy(hist.data(), p->hist, hist.size() * 4, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(flux.data(), p->flux, ns * 8, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(se.data(), p->se, ns * 8, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(mt.data(), p->mt, ns * 8, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(steps.data(), p->steps, ns * 8, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(ncap.data(), p->ncap, ns * 4, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(nnan.data(), p->nnan, ns * 4, hipMemcpyDeviceToHost));
+    std::vector<unsigned char> spill;
+    const unsigned char* h = nullptr;
+    cosmica_status st = download_block(ctx, p->res, p->res_at.total, &spill, &h);
+    if (st != COSMICA_OK) return st;
+    const uint32_t* hist = (const uint32_t*)(h + p->res_at.hist);
+    const double* flux = (const double*)(h + p->res_at.flux);
+    const double* se = (const double*)(h + p->res_at.se);
+    const double* mt = (const double*)(h + p->res_at.mt);
+    const uint64_t* steps = (const uint64_t*)(h + p->res_at.steps);
+    const uint32_t* ncap = (const uint32_t*)(h + p->res_at.ncap);
+    const uint32_t* nnan = (const uint32_t*)(h + p->res_at.nnan);
+    if ((st = finish_timings(ctx, ctx->last_steps == p->steps ? steps : nullptr)) != COSMICA_OK)
+        return st;
     bool capped = false;
     bool need_exits = false;
     for (size_t j = 0; j < p->jobs.size(); ++j) need_exits |= results[j].exits != nullptr;
@@ -1270,10 +1357,12 @@ cosmica_status cosmica_plan_reweight(cosmica_plan* p, uint32_t n_lis, uint32_t n
     cosmica_status st;
     const size_t nout = (size_t)n_lis * nb;
     if ((st = m.alloc(&tab, (size_t)n_lis * n_knots)) != COSMICA_OK) return st;
-    if ((st = m.alloc(&fd, nout)) != COSMICA_OK) return st;
-    if ((st = m.alloc(&sd, nout)) != COSMICA_OK) return st;
-    HIP_TRY(hipMemcpyAsync(tab, lnJ, (size_t)n_lis * n_knots * 8, hipMemcpyHostToDevice,
-                           ctx->stream));
+    if ((st = m.alloc(&fd, 2 * nout)) != COSMICA_OK) return st;
+    sd = fd + nout;
+    const size_t tab_bytes = (size_t)n_lis * n_knots * 8;
+    st = upload_block(ctx, tab, tab_bytes,
+                      [&](unsigned char* h) { std::memcpy(h, lnJ, tab_bytes); });
+    if (st != COSMICA_OK) return st;
     ReweightArgs a;
     std::memset(&a, 0, sizeof(a));
     a.segs = p->segs_d;
@@ -1301,9 +1390,11 @@ cosmica_status cosmica_plan_reweight(cosmica_plan* p, uint32_t n_lis, uint32_t n
         a.partial = nullptr;
     }
     HIP_TRY(launch_reweight(a, nb, ctx->stream));
-    HIP_TRY(hipStreamSynchronize(ctx->stream));
-    if (flux) HIP_TRY(hipMemcpy(flux, fd, nout * 8, hipMemcpyDeviceToHost));
-    if (flux_se) HIP_TRY(hipMemcpy(flux_se, sd, nout * 8, hipMemcpyDeviceToHost));
+    std::vector<unsigned char> spill;
+    const unsigned char* got = nullptr;
+    if ((st = download_block(ctx, fd, 2 * nout * 8, &spill, &got)) != COSMICA_OK) return st;
+    if (flux) std::memcpy(flux, got, nout * 8);
+    if (flux_se) std::memcpy(flux_se, got + nout * 8, nout * 8);
     return COSMICA_OK;
 }
 
@@ -1320,8 +1411,11 @@ cosmica_status cosmica_plan_exit_range(cosmica_plan* p, uint32_t n_hist, double*
     double* pm = nullptr;
     uint32_t* h = nullptr;
     cosmica_status st;
-    if ((st = m.alloc(&pm, nb)) != COSMICA_OK) return st;
-    if ((st = m.alloc(&h, (size_t)nb * n_hist)) != COSMICA_OK) return st;
+    const size_t hist_bytes = (size_t)nb * n_hist * 4;
+    unsigned char* out_d = nullptr;
+    if ((st = m.alloc(&out_d, (size_t)nb * 8 + hist_bytes)) != COSMICA_OK) return st;
+    pm = (double*)out_d;
+    h = (uint32_t*)(out_d + (size_t)nb * 8);
     RangeArgs a;
     std::memset(&a, 0, sizeof(a));
     a.segs = p->segs_d;
@@ -1340,9 +1434,12 @@ cosmica_status cosmica_plan_exit_range(cosmica_plan* p, uint32_t n_hist, double*
         a.part_max = nullptr;
     }
     HIP_TRY(launch_exit_range(a, nb, ctx->stream));
-    HIP_TRY(hipStreamSynchronize(ctx->stream));
-    if (p_max) HIP_TRY(hipMemcpy(p_max, pm, (size_t)nb * 8, hipMemcpyDeviceToHost));
-    if (hist) HIP_TRY(hipMemcpy(hist, h, (size_t)nb * n_hist * 4, hipMemcpyDeviceToHost));
+    std::vector<unsigned char> spill;
+    const unsigned char* got = nullptr;
+    if ((st = download_block(ctx, out_d, (size_t)nb * 8 + hist_bytes, &spill, &got)) != COSMICA_OK)
+        return st;
+    if (p_max) std::memcpy(p_max, got, (size_t)nb * 8);
+    if (hist) std::memcpy(hist, got + (size_t)nb * 8, hist_bytes);
     return COSMICA_OK;
 }
 
@@ -1536,18 +1633,19 @@ cosmica_status run_static(cosmica_ctx* ctx, const cosmica_job* jobs, uint32_t n_
     hipStream_t st = ctx->stream;
     const auto t0 = std::chrono::steady_clock::now();
     auto at = [&](size_t offset) { return (void*)(base + offset); };
-    HIP_TRY(hipMemcpyAsync(at(Lo.jobs), jh, n_jobs * sizeof(JobDev<R>), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(at(Lo.regions), rh, (size_t)n_jobs * kRegionStride * sizeof(RegionDev<R>),
-                           hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(at(Lo.lis), H.lis, n_jobs * sizeof(LisDev), hipMemcpyHostToDevice, st));
-    if (n_orbit)
-        HIP_TRY(hipMemcpyAsync(at(Lo.orbit), H.orbit, n_orbit * sizeof(OrbitDev),
-                               hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(at(Lo.segs), H.segs, n_bins * sizeof(SegmentDev), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(at(Lo.chunks), H.chunks, nc * sizeof(ChunkDev), hipMemcpyHostToDevice, st));
-    // the array keeps the last call's contents: the queue cursors start at
-    // zero, and momentum-form particles leave the loss records unwritten
-    HIP_TRY(launch_fill_u32((uint32_t*)at(Lo.counters), 0u, 8, st));
+    // tables, queues and zeroed queue cursors in one copy (the array keeps the
+    // last call's contents)
+    cosmica_status s = upload_block(ctx, base, Lo.exP, [&](unsigned char* h) {
+        std::memcpy(h + Lo.jobs, jh, n_jobs * sizeof(JobDev<R>));
+        std::memcpy(h + Lo.regions, rh, (size_t)n_jobs * kRegionStride * sizeof(RegionDev<R>));
+        std::memcpy(h + Lo.lis, H.lis, n_jobs * sizeof(LisDev));
+        if (n_orbit) std::memcpy(h + Lo.orbit, H.orbit, n_orbit * sizeof(OrbitDev));
+        std::memcpy(h + Lo.segs, H.segs, n_bins * sizeof(SegmentDev));
+        std::memcpy(h + Lo.chunks, H.chunks, nc * sizeof(ChunkDev));
+        std::memset(h + Lo.counters, 0, Lo.exP - Lo.counters);
+    });
+    if (s != COSMICA_OK) return s;
+    // momentum-form particles leave the loss records unwritten
     if (energy) HIP_TRY(launch_fill_u32((uint32_t*)at(Lo.exL), 0u, (uint32_t)(2 * total), st));
     const double up =
         std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
@@ -1577,8 +1675,7 @@ cosmica_status run_static(cosmica_ctx* ctx, const cosmica_job* jobs, uint32_t n_
     d.key = jobs[0].seed;
     d.prec = prec;
     HIP_TRY(hipEventRecord(ctx->ev[0], st));
-    cosmica_status s = execute_prop<R>(ctx, d);
-    if (s != COSMICA_OK) return s;
+    if ((s = execute_prop<R>(ctx, d)) != COSMICA_OK) return s;
     HIP_TRY(hipEventRecord(ctx->ev[1], st));
     ReduceArgs r;
     std::memset(&r, 0, sizeof(r));
@@ -1607,27 +1704,33 @@ cosmica_status run_static(cosmica_ctx* ctx, const cosmica_job* jobs, uint32_t n_
     if (exits)
         HIP_TRY(launch_pack_exits(d.exP, d.exT, d.exNF, d.exL, d.exR, d.exTh, d.exPh,
                                   (uint32_t)total, ex, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    // results straight into the caller's buffers (a job's bins and particles
-    // are contiguous)
+    HIP_TRY(hipEventSynchronize(ctx->ev[2]));
+    // results in one copy, then into the caller's buffers (a job's bins are
+    // contiguous)
     const auto t1 = std::chrono::steady_clock::now();
-    HIP_TRY(hipMemcpy(H.ncap, r.n_capped, n_bins * 4, hipMemcpyDeviceToHost));
+    static_assert(COSMICA_STATIC_MAX_BINS * (kNHist * 4 + 40) + 8 * 256 <= cosmica_ctx::kDownBytes &&
+                      sizeof(StaticHost) - sizeof(StaticHost::cost) <= cosmica_ctx::kUpBytes,
+                  "the pinned staging holds the largest call");
+    std::vector<unsigned char> none;
+    const unsigned char* h = nullptr;
+    if ((s = download_block(ctx, r.hist, Lo.total - Lo.hist, &none, &h)) != COSMICA_OK) return s;
+    auto got = [&](size_t offset) { return (const void*)(h + (offset - Lo.hist)); };
+    const uint32_t* ncap = (const uint32_t*)got(Lo.ncap);
     bool capped = false;
     for (uint32_t j = 0; j < n_jobs; ++j) {
         const cosmica_result& R_ = results[j];
         const uint32_t s0 = H.seg_first[j];
         const size_t nb = (size_t)jobs[j].n_bins;
         if (R_.hist)
-            HIP_TRY(hipMemcpy(R_.hist, r.hist + (size_t)s0 * kNHist, nb * kNHist * 4,
-                              hipMemcpyDeviceToHost));
-        if (R_.flux) HIP_TRY(hipMemcpy(R_.flux, r.flux + s0, nb * 8, hipMemcpyDeviceToHost));
-        if (R_.flux_se) HIP_TRY(hipMemcpy(R_.flux_se, r.flux_se + s0, nb * 8, hipMemcpyDeviceToHost));
+            std::memcpy(R_.hist, (const uint32_t*)got(Lo.hist) + (size_t)s0 * kNHist, nb * kNHist * 4);
+        if (R_.flux) std::memcpy(R_.flux, (const double*)got(Lo.flux) + s0, nb * 8);
+        if (R_.flux_se) std::memcpy(R_.flux_se, (const double*)got(Lo.se) + s0, nb * 8);
         if (R_.mean_exit_time_s)
-            HIP_TRY(hipMemcpy(R_.mean_exit_time_s, r.mean_t + s0, nb * 8, hipMemcpyDeviceToHost));
-        if (R_.steps) HIP_TRY(hipMemcpy(R_.steps, r.steps + s0, nb * 8, hipMemcpyDeviceToHost));
-        if (R_.n_nan) HIP_TRY(hipMemcpy(R_.n_nan, r.n_nan + s0, nb * 4, hipMemcpyDeviceToHost));
-        if (R_.n_capped) std::memcpy(R_.n_capped, H.ncap + s0, nb * 4);
-        for (size_t b = 0; b < nb; ++b) capped |= H.ncap[s0 + b] > 0;
+            std::memcpy(R_.mean_exit_time_s, (const double*)got(Lo.mt) + s0, nb * 8);
+        if (R_.steps) std::memcpy(R_.steps, (const uint64_t*)got(Lo.steps) + s0, nb * 8);
+        if (R_.n_nan) std::memcpy(R_.n_nan, (const uint32_t*)got(Lo.nnan) + s0, nb * 4);
+        if (R_.n_capped) std::memcpy(R_.n_capped, ncap + s0, nb * 4);
+        for (size_t b = 0; b < nb; ++b) capped |= ncap[s0 + b] > 0;
         if (R_.exits) {
             uint64_t n = 0;
             for (size_t b = 0; b < nb; ++b) n += jobs[j].particles_per_bin[b];
@@ -3062,6 +3165,9 @@ void cosmica_destroy(cosmica_ctx* ctx)
     if (ctx->serve_stream) (void)hipStreamDestroy(ctx->serve_stream);
     for (int i = 0; i < 4; ++i)
         if (ctx->ev[i]) (void)hipEventDestroy(ctx->ev[i]);
+    if (ctx->up_ev) (void)hipEventDestroy(ctx->up_ev);
+    if (ctx->up) (void)hipHostFree(ctx->up);
+    if (ctx->down) (void)hipHostFree(ctx->down);
     cache_trim(ctx, ~0ull);
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;
