@@ -143,6 +143,7 @@ struct PropArgs {
     uint32_t shaped;              // 1: some job of the launch has a squashed boundary or a heliosheath
     uint32_t energy;              // 1: some job of the launch is in the energy form
     uint32_t key_lo, key_hi;
+    uint32_t hand_over;           // 1: park a wave's particles once the queue is empty
     uint32_t latency;             // 1: run the kernel for few particles per SIMD
     uint32_t lane_cap;            // lanes a wave of that kernel fills (1..64; 0: see k_latency)
     const uint32_t* job_cancel;   // optional per-job cancel flags

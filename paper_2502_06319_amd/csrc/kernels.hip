@@ -1213,7 +1213,9 @@ __device__ __forceinline__ void propagate(const PropArgs<R>& a)
             if (a.job_done != nullptr) atomicAdd(&a.job_done[job], 1u);
             active = false;
         }
-        if (slice_over) {
+        // hand_over: once the queue has nothing left for this wave, its particles are
+        // parked (at its next exit) for the launch that follows
+        if (slice_over || (!TAIL && a.hand_over != 0u && !queue_open)) {
             // slice over (wave-uniform): park the wave's particles in
             // consecutive entries for the next launch and stop taking work
             const uint64_t parked = __ballot(active);

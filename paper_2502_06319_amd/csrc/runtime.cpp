@@ -432,6 +432,16 @@ struct cosmica_ctx {
     unsigned char* up = nullptr;
     unsigned char* down = nullptr;
     hipEvent_t up_ev = nullptr;  // the last copy from `up`
+    // Particles that a pass hands from the throughput to the latency kernel: one
+    // list for the passes on the context's stream, made when a plan that can use it
+    // is created (68 B per lane of the largest grid: 22 MB in binary32) and given back
+    // when an allocation needs the room.
+    std::recursive_mutex hand_mu;  // held while launches that use it are enqueued
+    unsigned char* hand = nullptr;
+    size_t hand_bytes = 0;
+    uint32_t hand_cap = 0;        // particles it holds
+    uint32_t* hand_ctl = nullptr;  // its counters (within the block)
+    SliceDev* hand_sl = nullptr;   // descriptors of the two launches (within the block)
     cosmica_ctx() = default;
     ~cosmica_ctx();  // defined once the serving types are complete
 };
@@ -452,6 +462,19 @@ void cache_trim(cosmica_ctx* ctx, uint64_t need)
     }
 }
 
+// Gives the hand-over list back to the device.
+void hand_release(cosmica_ctx* ctx)
+{
+    std::lock_guard<std::recursive_mutex> lk(ctx->hand_mu);
+    if (ctx->hand == nullptr) return;
+    (void)hipStreamSynchronize(ctx->stream);
+    (void)hipFree(ctx->hand);
+    ctx->in_use.fetch_sub(ctx->hand_bytes);
+    ctx->hand = nullptr;
+    ctx->hand_bytes = 0;
+    ctx->hand_cap = 0;
+}
+
 cosmica_status dalloc(cosmica_ctx* ctx, size_t bytes, void** p)
 {
     *p = nullptr;
@@ -468,12 +491,19 @@ cosmica_status dalloc(cosmica_ctx* ctx, size_t bytes, void** p)
         }
     }
     if (ctx->in_use.load() + bytes > ctx->budget) cache_trim(ctx, bytes);
+    if (ctx->in_use.load() + bytes > ctx->budget) hand_release(ctx);
     const uint64_t cur = ctx->in_use.fetch_add(bytes);
     if (cur + bytes > ctx->budget) {
         ctx->in_use.fetch_sub(bytes);
         return COSMICA_ENOMEM;
     }
-    if (hipMalloc(p, bytes) != hipSuccess) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        hand_release(ctx);
+        e = hipMalloc(p, bytes);
+    }
+    if (e != hipSuccess) {
         ctx->in_use.fetch_sub(bytes);
         *p = nullptr;
         (void)hipGetLastError();
@@ -614,6 +644,8 @@ struct PassWork {
     uint64_t particles = 0;
     double steps = 0.0;    // expected, all particles
     double longest = 0.0;  // largest expected steps per particle of a bin
+    // paths long enough that a pass hands its last ones to the latency kernel
+    bool long_paths() const { return longest >= 4000.0; }
     void add(uint64_t count, double per_particle)
     {
         particles += count;
@@ -637,12 +669,16 @@ struct PassShape {
 // throughput is 10% lower.  The pass is bound by the longest path while the
 // work per lane of the full grid is below a few times the longest expected
 // path.  Measured crossings, as work per lane over the largest expected mean
-// of a bin: 3D binary32 12 (no particle on the current sheet) and 8 (the
-// batched mix), 3D binary64 12; radial binary32 7, binary64 20.  At 1e8 steps
-// (306,000 particles, 3D binary32) the throughput kernel takes 5.1 ms, the
-// latency kernel 3.1 ms; at 9e9 steps 56 and 72 ms.
+// of a bin: 3D without particles on the current sheet 12 in both precisions
+// (at 1e8 steps, binary32, the throughput kernel takes 5.1 ms and the latency
+// kernel 3.1 ms; at 9e9 steps 56 and 72 ms); radial binary32 7, binary64 20.
+// With particles on the sheet the throughput kernel hands its last paths over
+// (hand_over) and crosses at 2: the batched mix with 4 parameter sets takes 178 ms
+// so and 157 ms in the latency kernel, 12 sets 627 and 640 ms, 24 sets 973 and
+// 1032 ms, 12 with a heliosheath 1643 and 1873 ms; 16 quarter sets in binary64
+// 986 and 1139 ms.
 PassShape pass_shape(cosmica_ctx* ctx, int model, int prec, const PassWork& w, bool shaped,
-                     bool energy, bool ukey)
+                     bool energy, bool ukey, bool hand)
 {
     const cosmica_launch& L = ctx->launch[model][prec];
     PassShape s;
@@ -650,7 +686,7 @@ PassShape pass_shape(cosmica_ctx* ctx, int model, int prec, const PassWork& w, b
     if (!ctx->auto_launch[model][prec] || w.particles == 0) return s;
     const uint64_t lanes =
         (uint64_t)grid_for(ctx, model, prec, L, ~0ull >> 8, shaped, energy, ukey) * (uint64_t)L.block;
-    const double crossing = model == 1 ? 10.0 : (prec == COSMICA_PREC_MIXED ? 6.0 : 20.0);
+    const double crossing = model == 1 ? (hand && w.long_paths() ? 2.0 : 10.0) : (prec == COSMICA_PREC_MIXED ? 6.0 : 20.0);
     if (w.steps >= crossing * (double)lanes * w.longest) return s;
     s.latency = true;
     // One wave per SIMD while every particle finds a lane (a step then costs its
@@ -883,9 +919,81 @@ struct PassDev {
     double *exP, *exT, *exL, *exR, *exTh, *exPh;
     uint32_t* exNF;
     bool uniform_key, shaped, energy;
+    bool hand;  // the context may hold a hand-over list for it
     uint64_t key;
     int prec;
 };
+
+// The hand-over list of the context for `lanes` particles, made if need be; false
+// where there is no room for it.  The caller holds hand_mu.
+bool hand_ready(cosmica_ctx* ctx, uint32_t lanes)
+{
+    if (ctx->hand != nullptr && ctx->hand_cap >= lanes) return true;
+    hand_release(ctx);
+    Carve c;
+    const size_t o_f = c.take((size_t)lanes * 7 * sizeof(double));
+    const size_t o_u = c.take((size_t)lanes * 3 * sizeof(uint32_t));
+    const size_t o_ctl = c.take(16 * sizeof(uint32_t));
+    const size_t o_sl = c.take(2 * sizeof(SliceDev));
+    void* q = nullptr;
+    if (dalloc(ctx, c.at, &q) != COSMICA_OK) return false;
+    ctx->hand = (unsigned char*)q;
+    ctx->hand_bytes = c.at;
+    ctx->hand_cap = lanes;
+    ctx->hand_ctl = (uint32_t*)(ctx->hand + o_ctl);
+    ctx->hand_sl = (SliceDev*)(ctx->hand + o_sl);
+    double* f = (double*)(ctx->hand + o_f);
+    uint32_t* u = (uint32_t*)(ctx->hand + o_u);
+    ParkDev pk;
+    double** fields[7] = {&pk.r, &pk.P, &pk.t, &pk.th, &pk.ph, &pk.T, &pk.lam};
+    for (int k = 0; k < 7; ++k) *fields[k] = f + (size_t)k * lanes;
+    uint32_t** words[3] = {&pk.n, &pk.seg, &pk.pid};
+    for (int k = 0; k < 3; ++k) *words[k] = u + (size_t)k * lanes;
+    // Counters: 0 particles parked, 1 cursor of the second launch over them, 2 an
+    // always empty list's count, 3-5 cursors and counts of empty lists, 6 overflow.
+    uint32_t* ctl = ctx->hand_ctl;
+    SliceDev sl[2];
+    std::memset(sl, 0, sizeof(sl));
+    for (int k = 0; k < 2; ++k) {
+        sl[k].resume = pk;
+        sl[k].suspend = pk;
+        sl[k].n_resume = k == 0 ? ctl + 2 : ctl + 0;
+        sl[k].resume_head = k == 0 ? ctl + 3 : ctl + 1;
+        sl[k].suspend_count = ctl + 0;
+        sl[k].n_left_in = ctl + 2;
+        sl[k].left_in_head = ctl + 4;
+        sl[k].leftover_count = ctl + 5;
+        sl[k].overflow = ctl + 6;
+        sl[k].park_cap = lanes;
+    }
+    return upload_block(ctx, ctx->hand_sl, sizeof(sl),
+                        [&](unsigned char* h) { std::memcpy(h, sl, sizeof(sl)); }) == COSMICA_OK;
+}
+
+// Whether a pass in the throughput kernel ends in the latency kernel: the waves
+// park what they hold once the queue is empty, and the last paths run at 0.4 to
+// 0.55 us a step instead of 2.1 falling to 0.6.  Only where the queue outlasts
+// the first particles by far (the throughput kernel's share) and paths are long:
+// the batched mix with 12 parameter sets took 662 ms without and 627 ms with it,
+// 24 sets 1009 and 973 ms, 16 quarter sets in binary64 1219 and 986 ms; 64 sets
+// without particles on the sheet 31 and 37 ms.
+bool hand_over(int model, const PassWork& w, uint64_t lanes)
+{
+    return model == 1 && w.long_paths() && w.particles >= 2 * lanes;
+}
+
+// Workgroups of a pass in the throughput kernel.
+int throughput_grid(cosmica_ctx* ctx, int model, int prec, const PassWork& w, bool shaped,
+                    bool energy, bool ukey)
+{
+    cosmica_launch L = ctx->launch[model][prec];
+    // 4 waves per SIMD: a step of the longest paths takes less time than with 5
+    // (batched mix, 12, 24 and 64 parameter sets: 634 and 617, 970 and 956, 2858
+    // and 2807 ms with 5 and 4)
+    if (ctx->auto_launch[model][prec] && model == 1 && prec == COSMICA_PREC_MIXED)
+        L.blocks_per_cu = 4;
+    return grid_for(ctx, model, prec, L, w.particles, shaped, energy, ukey);
+}
 
 template <typename R>
 cosmica_status execute_prop(cosmica_ctx* ctx, const PassDev& d)
@@ -931,11 +1039,29 @@ cosmica_status execute_prop(cosmica_ctx* ctx, const PassDev& d)
             grid = (int)std::min<uint64_t>((uint64_t)ctx->num_cus * (uint64_t)f.blocks_per_cu,
                                            (d.work[model].particles + per_block - 1) / per_block);
         } else {
-            grid = grid_for(ctx, model, d.prec, L, d.work[model].particles, d.shaped, d.energy,
-                            d.uniform_key);
+            grid = throughput_grid(ctx, model, d.prec, d.work[model], d.shaped, d.energy,
+                                   d.uniform_key);
         }
         ctx->timings.grid_blocks = grid;
         ctx->timings.block = block;
+        // (a graph under capture may outlive the list)
+        std::lock_guard<std::recursive_mutex> lk(ctx->hand_mu);
+        const uint64_t lanes = (uint64_t)grid * (uint64_t)block;
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (a.latency == 0u && d.hand && hand_over(model, d.work[model], lanes) &&
+            ctx->hand != nullptr && ctx->hand_cap >= lanes &&
+            hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess &&
+            cap == hipStreamCaptureStatusNone) {
+            HIP_TRY(launch_fill_u32(ctx->hand_ctl, 0u, 16, ctx->stream));
+            a.slice = ctx->hand_sl;
+            a.hand_over = 1u;
+            HIP_TRY(launch_model<R>(model, a, grid, block, ctx->stream));
+            a.slice = ctx->hand_sl + 1;
+            a.hand_over = 0u;
+            a.latency = 1u;
+            a.lane_cap = 64u;
+            grid = std::min(grid, ctx->num_cus * (d.prec == COSMICA_PREC_FP64 ? 1 : 2) * 256 / block);
+        }
         HIP_TRY(launch_model<R>(model, a, grid, block, ctx->stream));
     }
     return COSMICA_OK;
@@ -965,6 +1091,7 @@ PassDev pass_of(const cosmica_plan* p)
     d.uniform_key = p->uniform_key;
     d.shaped = p->shaped;
     d.energy = p->energy;
+    d.hand = true;
     d.key = p->key;
     d.prec = p->prec;
     return d;
@@ -1097,9 +1224,18 @@ cosmica_status cosmica_plan_create(cosmica_ctx* ctx, const cosmica_job* jobs, in
     std::vector<ChunkDev> chunks[2];
     for (int m = 0; m < 2; ++m) {
         p->shape[m] =
-            pass_shape(ctx, m, precision, p->work[m], p->shaped, p->energy, p->uniform_key);
+            pass_shape(ctx, m, precision, p->work[m], p->shaped, p->energy, p->uniform_key, true);
         make_chunks(p->segs, ids[m], p->shape[m].chunk, ctx->launch[m][precision].order,
                     &chunks[m], &cost);
+        if (p->shape[m].latency || p->work[m].particles == 0) continue;
+        const uint64_t lanes =
+            (uint64_t)throughput_grid(ctx, m, precision, p->work[m], p->shaped, p->energy,
+                                      p->uniform_key) *
+            (uint64_t)ctx->launch[m][precision].block;
+        if (hand_over(m, p->work[m], lanes)) {
+            std::lock_guard<std::recursive_mutex> lk(ctx->hand_mu);
+            (void)hand_ready(ctx, (uint32_t)lanes);  // without room: no hand-over
+        }
     }
     cosmica_status st = precision == COSMICA_PREC_MIXED ? upload_tables<float>(p.get(), chunks)
                                                          : upload_tables<double>(p.get(), chunks);
@@ -1579,7 +1715,7 @@ cosmica_status run_static(cosmica_ctx* ctx, const cosmica_job* jobs, uint32_t n_
     uint32_t nc = 0, first[2] = {0, 0}, nch[2] = {0, 0};
     for (int m = 0; m < 2; ++m) {
         const cosmica_launch& L = ctx->launch[m][prec];
-        shape[m] = pass_shape(ctx, m, prec, work[m], shaped, energy, ukey);
+        shape[m] = pass_shape(ctx, m, prec, work[m], shaped, energy, ukey, false);
         const uint32_t c = (uint32_t)std::max<uint64_t>((uint64_t)std::max(1, shape[m].chunk),
                                                         (total + room - 1) / room);
         uint32_t k = 0;
@@ -1672,6 +1808,7 @@ cosmica_status run_static(cosmica_ctx* ctx, const cosmica_job* jobs, uint32_t n_
     d.uniform_key = ukey;
     d.shaped = shaped;
     d.energy = energy;
+    d.hand = false;  // (nothing is allocated)
     d.key = jobs[0].seed;
     d.prec = prec;
     HIP_TRY(hipEventRecord(ctx->ev[0], st));
@@ -3168,6 +3305,7 @@ void cosmica_destroy(cosmica_ctx* ctx)
     if (ctx->up_ev) (void)hipEventDestroy(ctx->up_ev);
     if (ctx->up) (void)hipHostFree(ctx->up);
     if (ctx->down) (void)hipHostFree(ctx->down);
+    hand_release(ctx);
     cache_trim(ctx, ~0ull);
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;

@@ -103,3 +103,28 @@ def test_served_slices_of_both_kernels(precision, explicit, monkeypatch):
             alone, got = e.run(j, precision)[0], t.result()
             for k in KEYS:
                 np.testing.assert_array_equal(got[k], alone[k], err_msg=k)
+
+
+@pytest.mark.parametrize("precision,energy", [("mixed", 0), ("mixed", 1), ("fp64", 0)])
+def test_hand_over_to_the_latency_kernel(precision, energy):
+    """A pass with more than twice as many particles as lanes and paths along the
+    sheet parks its last particles for the latency kernel: the same bits as in
+    run_static, which has no list to hand over with.  The cap keeps paths short
+    (and caps most of them)."""
+    per = 30000
+    job = W.make_job(W.c2_helio(), W.species("e-"), W.log_bins(0.3, 30.0, 10), per, seed=21)
+    job.update(step_cap=300, formulation=energy)
+    extra = dict(_job("heliosheath", 2, 40, seed=22, tag=3), formulation=energy)
+    with C.Engine(0) as e:
+        e.set_launch(1, precision, block=256, blocks_per_cu=2)
+        before = e.serve_stats()["bytes_in_use"]
+        got = e.run([job, extra], precision)
+        assert e.serve_stats()["bytes_in_use"] > before
+        lanes = e.timings()["grid_blocks"] * 256
+        assert 10 * per >= 2 * lanes
+        want = e.run_static([job, extra], precision)
+        again = e.run([job, extra], precision)
+        for a, b, c in zip(got, want, again):
+            for k in KEYS:
+                np.testing.assert_array_equal(a[k], b[k], err_msg=k)
+                np.testing.assert_array_equal(c[k], b[k], err_msg=k)
