@@ -1041,8 +1041,8 @@ __device__ __forceinline__ void propagate(const PropArgs<R>& a)
         // VALU instruction (dependent or not), 8 per transcendental and 30 to 50 per
         // compare-and-branch, so the rare events of a step (reflections, phi past a
         // turn, the exit) share one test.  One particle, us per step, the throughput
-        // kernel's loop and this one: 3D binary32 0.603 and 0.397, binary64 2.56 and
-        // 1.56; radial 0.261 and 0.144, 0.724 and 0.315.  With 64 particles a wave:
+        // kernel's loop and this one: 3D binary32 0.603 and 0.402, binary64 2.56 and
+        // 1.26; radial 0.261 and 0.144, 0.724 and 0.311.  With 64 particles a wave:
         // 0.609 and 0.547, 2.70 and 2.56, 0.266 and 0.228, 0.734 and 0.571.
         // Idle lanes hold copies of the wave's particles, so every lane runs the loop
         // and its control flow is the wave's.

@@ -686,7 +686,8 @@ PassShape pass_shape(cosmica_ctx* ctx, int model, int prec, const PassWork& w, b
     if (!ctx->auto_launch[model][prec] || w.particles == 0) return s;
     const uint64_t lanes =
         (uint64_t)grid_for(ctx, model, prec, L, ~0ull >> 8, shaped, energy, ukey) * (uint64_t)L.block;
-    const double crossing = model == 1 ? (hand && w.long_paths() ? 2.0 : 10.0) : (prec == COSMICA_PREC_MIXED ? 6.0 : 20.0);
+    const double crossing = model == 1 ? (hand && w.long_paths() ? 2.0 : 10.0)
+                                       : (prec == COSMICA_PREC_MIXED ? 6.0 : 20.0);
     if (w.steps >= crossing * (double)lanes * w.longest) return s;
     s.latency = true;
     // One wave per SIMD while every particle finds a lane (a step then costs its
@@ -966,8 +967,11 @@ bool hand_ready(cosmica_ctx* ctx, uint32_t lanes)
         sl[k].overflow = ctl + 6;
         sl[k].park_cap = lanes;
     }
-    return upload_block(ctx, ctx->hand_sl, sizeof(sl),
-                        [&](unsigned char* h) { std::memcpy(h, sl, sizeof(sl)); }) == COSMICA_OK;
+    if (upload_block(ctx, ctx->hand_sl, sizeof(sl),
+                     [&](unsigned char* h) { std::memcpy(h, sl, sizeof(sl)); }) == COSMICA_OK)
+        return true;
+    hand_release(ctx);  // a list without its descriptors must not be found
+    return false;
 }
 
 // Whether a pass in the throughput kernel ends in the latency kernel: the waves
