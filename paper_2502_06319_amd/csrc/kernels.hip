@@ -1439,58 +1439,127 @@ __device__ __forceinline__ void mean_and_se(double n, double s, double s1, doubl
     *se = n > 1.0 ? ::sqrt(m2 / (n - 1.0) / n) : 0.0;
 }
 
-// Sums of one part (kReducePart exits) of a bin, or of its parts in order.
+// What a part of a bin (kReducePart exits), a group of parts or the whole bin
+// holds of its used exits.
 struct BinSums {
-    double s1, s2, st;              // of w - s and its square, and of the exit times
+    double mean, m2, st;            // weights: mean, squared deviations from it; exit times
     unsigned long long sn;          // steps
     unsigned long long used, capped, nan;
-    __device__ void add(const BinSums& o)
-    {
-        s1 += o.s1;
-        s2 += o.s2;
-        st += o.st;
-        sn += o.sn;
-        used += o.used;
-        capped += o.capped;
-        nan += o.nan;
-    }
 };
 static_assert(sizeof(BinSums) + (kNHist + 1) * sizeof(uint32_t) == kReducePartBytes, "partial layout");
 
+// Mean and squared deviations of n values with the sum s, whose deviations from
+// s / n (rounded) sum to c1 and their squares to c2: the deviations' sum
+// corrects both, so that equal values give exactly their mean and 0.
+__device__ __forceinline__ void corrected(double n, double c1, double c2, double* mean, double* m2)
+{
+    const double c = c1 / n;
+    if (fabs(*mean) < __builtin_huge_val() && fabs(c) < __builtin_huge_val()) {
+        *mean += c;
+        c2 -= c1 * c;
+    }
+    *m2 = c2 < 0.0 ? 0.0 : c2;
+}
+
+// Sum over the workgroup in a fixed order (wave tree, then the waves in order),
+// for every thread.  sh: one word per wave, not in use by an earlier call.
+template <typename T>
+__device__ __forceinline__ void wave_to(T v, T* sh)
+{
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+    if ((threadIdx.x & 63u) == 0) sh[threadIdx.x >> 6] = v;
+}
+template <typename T>
+__device__ __forceinline__ T waves_sum(const T* sh)
+{
+    T t = sh[0];
+    for (int w = 1; w < kReduceBlock / 64; ++w) t += sh[w];
+    return t;
+}
+
+struct ReduceScratch {
+    double d[5][kReduceBlock / 64];
+    unsigned long long u[4][kReduceBlock / 64];
+};
+
+// Adds up to kReduceBlock parts in LDS to the bin's sums (the same in every
+// thread): the parts' deviations are taken from the group's mean, then the
+// group's from the bin's (Chan, Golub and LeVeque 1979).
+__device__ __forceinline__ void merge_parts(const BinSums* parts, uint32_t n, BinSums& total,
+                                            ReduceScratch& sh)
+{
+    BinSums g = parts[0];
+    if (n > 1) {
+        BinSums v = {0.0, 0.0, 0.0, 0, 0, 0, 0};
+        if (threadIdx.x < n) v = parts[threadIdx.x];
+        const double k = (double)v.used;
+        wave_to(k * v.mean, sh.d[0]);
+        wave_to(v.st, sh.d[1]);
+        wave_to(v.sn, sh.u[0]);
+        wave_to(v.used, sh.u[1]);
+        wave_to(v.capped, sh.u[2]);
+        wave_to(v.nan, sh.u[3]);
+        __syncthreads();
+        g.st = waves_sum(sh.d[1]);
+        g.sn = waves_sum(sh.u[0]);
+        g.used = waves_sum(sh.u[1]);
+        g.capped = waves_sum(sh.u[2]);
+        g.nan = waves_sum(sh.u[3]);
+        const double N = (double)g.used;
+        g.mean = g.used > 0 ? waves_sum(sh.d[0]) / N : 0.0;
+        const double d = v.mean - g.mean;
+        wave_to(v.used > 0 ? k * d : 0.0, sh.d[2]);
+        wave_to(v.used > 0 ? v.m2 + k * (d * d) : 0.0, sh.d[3]);
+        __syncthreads();
+        g.m2 = 0.0;
+        if (g.used > 0) corrected(N, waves_sum(sh.d[2]), waves_sum(sh.d[3]), &g.mean, &g.m2);
+        __syncthreads();
+    }
+    if (total.used == 0) {
+        total.mean = g.mean;
+        total.m2 = g.m2;
+    } else if (g.used > 0) {
+        const double n1 = (double)total.used, n2 = (double)g.used, d = g.mean - total.mean;
+        total.mean = fabs(d) < __builtin_huge_val() ? total.mean + d * (n2 / (n1 + n2))
+                                                    : total.mean + g.mean;
+        total.m2 = total.m2 + (g.m2 + d * d * (n1 * (n2 / (n1 + n2))));
+    }
+    total.st += g.st;
+    total.sn += g.sn;
+    total.used += g.used;
+    total.capped += g.capped;
+    total.nan += g.nan;
+}
+
 __device__ __forceinline__ void write_bin(const ReduceArgs& a, const SegmentDev& sg,
-                                          const LisDev& L, uint32_t ob, double about,
-                                          const BinSums& t)
+                                          const LisDev& L, uint32_t ob, const BinSums& t)
 {
     // momentum form: mean of f_LIS(P_ex) times P0^2; energy form: the mean
     // contribution itself
     const double p2 = L.energy ? 1.0 : sg.P0 * sg.P0;
     const double n = (double)t.used;
-    double mean, se;
-    mean_and_se(n, about, t.s1, t.s2, &mean, &se);
-    if (a.flux) a.flux[ob] = p2 * mean;
-    if (a.flux_se) a.flux_se[ob] = p2 * se;
+    if (a.flux) a.flux[ob] = p2 * t.mean;
+    if (a.flux_se) a.flux_se[ob] = n > 1.0 ? p2 * ::sqrt(t.m2 / (n - 1.0) / n) : 0.0;
     if (a.mean_t) a.mean_t[ob] = t.used > 0 ? t.st / n : 0.0;
     if (a.steps) a.steps[ob] = t.sn;
     if (a.n_capped) a.n_capped[ob] = (uint32_t)t.capped;
     if (a.n_nan) a.n_nan[ob] = (uint32_t)t.nan;
 }
 
-// One pass over a bin's exits, in parts of kReducePart whose sums are added in
-// order, so the bits do not depend on how the parts are spread: one workgroup
-// per bin (SPLIT = false) where there are bins enough to fill the device, one
-// per part (a.partial, then k_reduce_sum) where there are few.  The weights are
-// summed about that of the bin's first used exit (see the re-weighting below):
-// one power per exit instead of one for the mean and one for the variance.
-// Bound by FP64 VALU and latency.  31 bins of 3,001 to 20,011 exits: 104 us in
-// one workgroup per bin with two passes, 28 us so; 20 of 5,000: 36 and
-// 21 us.
+// One pass over a bin's exits, in parts of kReducePart whose sums are put
+// together in groups of kReduceBlock parts, so the bits do not depend on how
+// the parts are spread: one workgroup per bin (SPLIT = false) where there are
+// bins enough to fill the device, one per part (a.partial, then k_reduce_sum)
+// where there are few.  A part's weights stay in registers, four a thread:
+// their mean first, then the deviations from it, one power per exit and no
+// cancellation whatever the weights.
 template <bool SPLIT>
 __global__ void __launch_bounds__(kReduceBlock) k_reduce(const ReduceArgs a)
 {
+    constexpr int kEach = kReducePart / kReduceBlock;
     __shared__ uint32_t hist[kNHist];
-    __shared__ double shd[3][kReduceBlock / 64];
-    __shared__ unsigned long long shu[2][kReduceBlock / 64];
-    __shared__ uint32_t pilot;
+    __shared__ ReduceScratch sh;
+    __shared__ BinSums parts[SPLIT ? 1 : kReduceBlock];
     const SegmentDev sg = a.segs[a.seg_base + blockIdx.x];
     const uint32_t first = SPLIT ? blockIdx.y * (uint32_t)kReducePart : 0u;
     if (first >= sg.count) return;
@@ -1498,24 +1567,22 @@ __global__ void __launch_bounds__(kReduceBlock) k_reduce(const ReduceArgs a)
     const LisDev L = a.lis[sg.job];
     const double inv_p0 = 1.0 / sg.P0;
     const double beta0 = L.energy ? beta_of(L, sg.P0) : 0.0;
-    auto weight = [&](double P, uint32_t o) {
-        return L.energy ? energy_weight(L, beta0, P, a.exL[o]) : lis_weight(L, P);
-    };
     for (int i = threadIdx.x; i < kNHist; i += kReduceBlock) hist[i] = 0u;
-    double about = 0.0;
-    if (const uint32_t p = first_used(sg, a.exNF, &pilot); p != ~0u) {
-        const uint32_t o = sg.out_offset + p;
-        about = weight(a.exP[o], o);
-        if (!(fabs(about) < __builtin_huge_val())) about = 0.0;
-    }
-    const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
-    BinSums total = {0.0, 0.0, 0.0, 0, 0, 0, 0};  // thread 0
-    for (uint32_t p0 = first; p0 < last; p0 += kReducePart) {
-        const uint32_t end = min(last - p0, (uint32_t)kReducePart) + p0;
-        double s1 = 0.0, s2 = 0.0, st = 0.0;
+    __syncthreads();
+    BinSums total = {0.0, 0.0, 0.0, 0, 0, 0, 0};
+    uint32_t np = 0;  // parts in LDS
+    for (uint64_t p0 = first; p0 < last; p0 += kReducePart) {
+        double w[kEach];
+        bool used[kEach];
+        double s = 0.0, st = 0.0;
         unsigned long long sn = 0, counts = 0;  // used, capped, non-finite: 16 bits each
-        for (uint32_t i = p0 + threadIdx.x; i < end; i += kReduceBlock) {
-            const uint32_t o = sg.out_offset + i;
+#pragma unroll
+        for (int j = 0; j < kEach; ++j) {
+            const uint64_t i = p0 + threadIdx.x + (uint64_t)j * kReduceBlock;
+            used[j] = false;
+            w[j] = 0.0;
+            if (i >= last) continue;
+            const uint32_t o = sg.out_offset + (uint32_t)i;
             const uint32_t nf = a.exNF[o];
             const double P = a.exP[o], t = a.exT[o];
             const uint32_t fl = nf >> kFlagShift;
@@ -1527,42 +1594,54 @@ __global__ void __launch_bounds__(kReduceBlock) k_reduce(const ReduceArgs a)
                     counts += 1ull << 32;
                 continue;
             }
-            const double d = weight(P, o) - about;
-            s1 += d;
-            s2 += d * d;
+            used[j] = true;
+            w[j] = L.energy ? energy_weight(L, beta0, P, a.exL[o]) : lis_weight(L, P);
+            s += w[j];
             st += t;
             ++counts;
-            int j = (int)::floor(128.0 * ::log10(P * inv_p0) / 3.0);
-            j = j < 0 ? 0 : (j > 128 ? 128 : j);
-            atomicAdd(&hist[j], 1u);
+            int h = (int)::floor(128.0 * ::log10(P * inv_p0) / 3.0);
+            h = h < 0 ? 0 : (h > 128 ? 128 : h);
+            atomicAdd(&hist[h], 1u);
         }
-        for (int off = 32; off > 0; off >>= 1) {
-            s1 += __shfl_down(s1, off, 64);
-            s2 += __shfl_down(s2, off, 64);
-            st += __shfl_down(st, off, 64);
-            sn += __shfl_down(sn, off, 64);
-            counts += __shfl_down(counts, off, 64);
-        }
+        wave_to(s, sh.d[0]);
+        wave_to(st, sh.d[1]);
+        wave_to(sn, sh.u[0]);
+        wave_to(counts, sh.u[1]);
         __syncthreads();
-        if (lane == 0) {
-            shd[0][wid] = s1;
-            shd[1][wid] = s2;
-            shd[2][wid] = st;
-            shu[0][wid] = sn;
-            shu[1][wid] = counts;
+        const unsigned long long c = waves_sum(sh.u[1]);
+        BinSums part;
+        part.st = waves_sum(sh.d[1]);
+        part.sn = waves_sum(sh.u[0]);
+        part.used = c & 0xffffull;
+        part.capped = (c >> 16) & 0xffffull;
+        part.nan = c >> 32;
+        const double n = (double)part.used;
+        part.mean = part.used > 0 ? waves_sum(sh.d[0]) / n : 0.0;
+        double c1 = 0.0, c2 = 0.0;
+#pragma unroll
+        for (int j = 0; j < kEach; ++j) {
+            const double d = used[j] ? w[j] - part.mean : 0.0;
+            c1 += d;
+            c2 += d * d;
         }
+        wave_to(c1, sh.d[2]);
+        wave_to(c2, sh.d[3]);
         __syncthreads();
-        if (threadIdx.x == 0) {
-            BinSums part = {0.0, 0.0, 0.0, 0, 0, 0, 0};
-            for (int w = 0; w < kReduceBlock / 64; ++w) {
-                const unsigned long long c = shu[1][w];
-                part.add(BinSums{shd[0][w], shd[1][w], shd[2][w], shu[0][w], c & 0xffffull,
-                                 (c >> 16) & 0xffffull, c >> 32});
+        part.m2 = 0.0;
+        if (part.used > 0) corrected(n, waves_sum(sh.d[2]), waves_sum(sh.d[3]), &part.mean, &part.m2);
+        if constexpr (SPLIT) {
+            total = part;
+        } else {
+            if (threadIdx.x == 0) parts[np] = part;
+            ++np;
+            __syncthreads();
+            if (np == kReduceBlock || p0 + kReducePart >= last) {
+                merge_parts(parts, np, total, sh);
+                np = 0;
+                __syncthreads();
             }
-            total.add(part);
         }
     }
-    __syncthreads();
     if constexpr (SPLIT) {
         unsigned char* q = a.partial + (size_t)kReducePartBytes * ((size_t)blockIdx.x * a.parts + blockIdx.y);
         if (threadIdx.x == 0) *(BinSums*)q = total;
@@ -1573,30 +1652,27 @@ __global__ void __launch_bounds__(kReduceBlock) k_reduce(const ReduceArgs a)
         if (a.hist != nullptr)
             for (int i = threadIdx.x; i < kNHist; i += kReduceBlock)
                 a.hist[(size_t)ob * kNHist + i] = hist[i];
-        if (threadIdx.x == 0) write_bin(a, sg, L, ob, about, total);
+        if (threadIdx.x == 0) write_bin(a, sg, L, ob, total);
     }
 }
 
-// The parts of a bin, in order: thread 0 adds the sums, the others the
-// histograms.
+// The parts of a bin.
 __global__ void __launch_bounds__(kReduceBlock) k_reduce_sum(const ReduceArgs a)
 {
     __shared__ BinSums sums[kReduceBlock];
-    __shared__ uint32_t pilot;
+    __shared__ ReduceScratch sh;
     const SegmentDev sg = a.segs[a.seg_base + blockIdx.x];
     const uint32_t np = (sg.count + (uint32_t)kReducePart - 1) / (uint32_t)kReducePart;
     const unsigned char* q = a.partial + (size_t)kReducePartBytes * ((size_t)blockIdx.x * a.parts);
     BinSums total = {0.0, 0.0, 0.0, 0, 0, 0, 0};
     for (uint32_t z0 = 0; z0 < np; z0 += kReduceBlock) {
         const uint32_t n = min(np - z0, (uint32_t)kReduceBlock);
-        __syncthreads();
         if (threadIdx.x < n)
             sums[threadIdx.x] = *(const BinSums*)(q + (size_t)kReducePartBytes * (z0 + threadIdx.x));
         __syncthreads();
-        if (threadIdx.x == 0)
-            for (uint32_t z = 0; z < n; ++z) total.add(sums[z]);
+        merge_parts(sums, n, total, sh);
+        __syncthreads();
     }
-    const uint32_t p = first_used(sg, a.exNF, &pilot);
     const uint32_t ob = a.out_base + blockIdx.x;
     if (a.hist != nullptr) {
         for (uint32_t i = threadIdx.x; i < (uint32_t)kNHist; i += kReduceBlock) {
@@ -1607,18 +1683,7 @@ __global__ void __launch_bounds__(kReduceBlock) k_reduce_sum(const ReduceArgs a)
             a.hist[(size_t)ob * kNHist + i] = t;
         }
     }
-    if (threadIdx.x == 0) {
-        const LisDev L = a.lis[sg.job];
-        const double beta0 = L.energy ? beta_of(L, sg.P0) : 0.0;
-        double about = 0.0;
-        if (p != ~0u) {
-            const uint32_t o = sg.out_offset + p;
-            const double P = a.exP[o];
-            about = L.energy ? energy_weight(L, beta0, P, a.exL[o]) : lis_weight(L, P);
-            if (!(fabs(about) < __builtin_huge_val())) about = 0.0;
-        }
-        write_bin(a, sg, L, ob, about, total);
-    }
+    if (threadIdx.x == 0) write_bin(a, sg, a.lis[sg.job], ob, total);
 }
 
 hipError_t launch_reduce(const ReduceArgs& a, uint32_t n_segs, hipStream_t s)
