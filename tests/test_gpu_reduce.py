@@ -1,9 +1,10 @@
-"""The per-bin reduction where its sums or its time could go wrong: standard
-errors of bins whose first exit is far from the mean, bins whose exits are
-nearly all capped."""
+"""The per-bin reduction where its sums, its time or its memory could go wrong:
+standard errors of bins whose first exit is far from the mean, bins whose exits
+are nearly all capped, bins of very different sizes."""
 import numpy as np
 import pytest
 
+from paper_2502_06319_amd import cosmica as C
 from paper_2502_06319_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -51,3 +52,65 @@ def test_capped_exits_cost_no_more_than_others(eng):
     job = W.make_job(W.helio_1d(), W.species("p"), [2.0], [2_000_000])
     full = _reduce_ms(eng, job)
     assert _reduce_ms(eng, dict(job, step_cap=1)) < 1.5 * full + 0.05
+
+
+def test_memory_follows_the_exits_of_each_bin():
+    """1,000 bins of 50 exits and one of 600,000: the plan holds 20 B an exit,
+    its tables and results, and a few bytes for the parts of each bin."""
+    job = W.make_job(W.helio_1d(), W.species("p"), [2.0] * 1001, [50] * 1000 + [600_000])
+    with C.Engine(0) as e:
+        before = e.serve_stats()["bytes_in_use"]
+        plan = e.plan(job, "mixed")
+        held = e.serve_stats()["bytes_in_use"] - before
+        plan.destroy()
+    assert held < 1.25 * 20 * 650_000
+
+
+@pytest.mark.parametrize("small,large", [([], [4_194_304, 4_300_000]),
+                                         ([50], [600_000, 600_000])])
+def test_one_large_bin_is_spread(eng, small, large):
+    """A bin just past 2^22 exits takes about as long as one of 2^22, and a large
+    one among 1,100 small ones as long as among 1,000."""
+    ms = []
+    for n_small, n in zip((1000, 1100), large):
+        counts = small * n_small + [n]
+        job = W.make_job(W.helio_1d(), W.species("p"), [2.0] * len(counts), counts)
+        ms.append(_reduce_ms(eng, job))
+    assert ms[1] < 1.5 * ms[0] + 0.05
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_a_workgroup_per_bin_and_per_part_give_the_same_bits(eng, precision):
+    """Bins at the edges of the parts, alone (spread) and among 5,000 one-exit
+    bins, where a workgroup takes a whole bin."""
+    counts = [1, 1023, 1024, 1025, 2048, 3073, 7000]
+    job = W.make_job(W.helio_1d(), W.species("p"), W.log_bins(0.5, 20.0, len(counts)), counts)
+    many = [dict(job, rigidity_gv=[3.0] * 500, particles_per_bin=[1] * 500, job_tag=i + 1)
+            for i in range(10)]
+    for cap in (10_000_000, 500):
+        job["step_cap"] = cap
+        alone = eng.run(job, precision)[0]
+        among = eng.run([job] + many, precision)[0]
+        for k in among:
+            np.testing.assert_array_equal(alone[k], among[k], err_msg=k)
+
+
+def test_more_parts_than_a_group(eng):
+    """300,000 and 262,145 exits: two groups of parts, against 64-bit two-pass
+    sums of the exit records (the weights' 2.5 ulps and a few more for the
+    sums: 16 units of 2^-53, on the standard error times sqrt(1 + n mean^2 /
+    m2))."""
+    counts = [300_000, 262_145]
+    job = W.make_job(W.helio_1d(), W.species("p"), [1.0, 4.0], counts)
+    r = eng.run(job, "mixed", exits=True)[0]
+    at = 0
+    for b, (P0, n) in enumerate(zip(job["rigidity_gv"], counts)):
+        ex = r["exits"][at:at + n]
+        at += n
+        w = LD(W.LIS_NORM) * ex["P"].astype(LD) ** LD(-W.LIS_INDEX - 2.0) * LD(P0) ** 2
+        m2 = ((w - w.mean()) ** 2).sum()
+        u = LD(2.0) ** -53
+        assert abs(r["flux"][b] / w.mean() - 1) < 16 * u
+        assert abs(r["flux_se"][b] / np.sqrt(m2 / (n - 1) / n) - 1) < (
+            16 * u * np.sqrt(1 + n * w.mean() ** 2 / m2))
+        assert r["hist"][b].sum() == n and r["steps"][b] == ex["n"].sum()
