@@ -210,7 +210,7 @@ struct ReweightArgs {
     uint32_t small_tables;  // 1: every |ln J| < 1e4
     // a segment's exits in parts of `part`, at most `parts` of them (1: whole)
     uint32_t part, parts;
-    double* partial;    // 4 * n_lis * total_bins * parts (null when parts is 1)
+    double* partial;    // 3 * n_lis * total_bins * parts (null when parts is 1)
     double* flux;       // n_lis * total_bins
     double* flux_se;
 };

@@ -1414,31 +1414,6 @@ __device__ __forceinline__ double energy_weight(const LisDev& L, double beta0, d
     return beta0 / beta_of(L, P) * (L.norm * ::pow(P, -L.index)) * ::exp(-loss);
 }
 
-// The first exit of a segment that is neither capped nor non-finite (~0: none).
-__device__ __forceinline__ uint32_t first_used(const SegmentDev& sg, const uint32_t* exNF,
-                                               uint32_t* sh)
-{
-    if (threadIdx.x == 0) *sh = ~0u;
-    for (uint32_t i0 = 0; i0 < sg.count; i0 += kReduceBlock) {
-        const uint32_t i = i0 + threadIdx.x;
-        __syncthreads();
-        if (i < sg.count && (exNF[sg.out_offset + i] >> kFlagShift) == 0u) atomicMin(sh, i);
-        __syncthreads();
-        if (*sh != ~0u) break;
-    }
-    return *sh;
-}
-
-// Mean and standard error from the sums about s of n weights.
-__device__ __forceinline__ void mean_and_se(double n, double s, double s1, double s2,
-                                            double* mean, double* se)
-{
-    *mean = n > 0.0 ? s + s1 / n : 0.0;
-    double m2 = s2 - s1 * (s1 / n);
-    m2 = m2 < 0.0 ? 0.0 : m2;
-    *se = n > 1.0 ? ::sqrt(m2 / (n - 1.0) / n) : 0.0;
-}
-
 // What a part of a bin (kReducePart exits), a group of parts or the whole bin
 // holds of its used exits.
 struct BinSums {
@@ -1726,9 +1701,12 @@ hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s)
 // are computed once for the whole group.
 //
 // Bound by FP64 VALU: one exponential per particle and spectrum.  One pass
-// accumulates w - s and (w - s)^2 with s the weight of the segment's first used
-// particle: |s - mean| is at most sqrt(N) standard deviations, so the variance
-// keeps all but N ulps, and N equal weights give a standard error of exactly 0.
+// accumulates w - s and (w - s)^2 with s the mean weight of the first used
+// particles of the part (those of its first 256 that has any): an error of the
+// variance grows with the squared distance of s from the mean, at most N / 2^16
+// variances for a part of N, so parts end at 2^16.  N equal weights give a
+// standard error of exactly 0.  The parts' deviations are then taken from the
+// mean of all.
 // Segments are split over workgroups where segments and groups alone would
 // leave CUs idle.  64 spectra x 516,000 exits of 30 bins: 521 us with two passes
 // of the library's exp in 120 workgroups, 73 us so.
@@ -1784,13 +1762,20 @@ struct LisStep {
     double at, d;  // ln J at a knot, and the difference to the next one
 };
 
+// Mean weight and its standard error from n weights' mean and squared
+// deviations.
+__device__ __forceinline__ void write_mean(double n, double mean, double m2, double* out, double* se)
+{
+    *out = mean;
+    *se = n > 1.0 ? ::sqrt(m2 / (n - 1.0) / n) : 0.0;
+}
+
 __global__ void __launch_bounds__(kReduceBlock) k_reweight(const ReweightArgs a)
 {
     __shared__ LisStep tab[kReweightGroup * (kMaxLisKnots - 1)];
     __shared__ double sums[2][kReduceBlock / 64][kReweightGroup];
     __shared__ double about[kReweightGroup];
     __shared__ unsigned long long shu[kReduceBlock / 64];
-    __shared__ uint32_t pilot;
     const uint32_t sidx = a.seg_base + blockIdx.x;
     const uint32_t l0 = blockIdx.y * kReweightGroup;
     const uint32_t nl = a.n_lis - l0 < (uint32_t)kReweightGroup ? a.n_lis - l0
@@ -1829,34 +1814,11 @@ __global__ void __launch_bounds__(kReduceBlock) k_reweight(const ReweightArgs a)
         *k = kk;
         *f = x - (double)kk;
     };
-    (void)first_used(sg, a.exNF, &pilot);
-    if (threadIdx.x < (uint32_t)kReweightGroup) {
-        double w = 0.0;
-        if (pilot != ~0u) {
-            double fac, f;
-            int k;
-            factor_and_pos(sg.out_offset + pilot, &fac, &k, &f);
-            const LisStep t = tab[threadIdx.x * ns + (uint32_t)k];
-            w = fac * ::exp(t.at + f * t.d);
-            if (!(fabs(w) < __builtin_huge_val())) w = 0.0;
-        }
-        about[threadIdx.x] = w;
-    }
-    __syncthreads();
-    double s1[kReweightGroup], s2[kReweightGroup], about_r[kReweightGroup];
-#pragma unroll
-    for (int l = 0; l < kReweightGroup; ++l) {
-        s1[l] = s2[l] = 0.0;
-        about_r[l] = about[l];
-    }
-    unsigned long long nused = 0;
-    for (uint32_t i = first + threadIdx.x; i < end; i += kReduceBlock) {
-        const uint32_t o = sg.out_offset + i;
-        if ((a.exNF[o] >> kFlagShift) != 0u) continue;  // capped or non-finite
+    // use(l, w) for the weight w of particle o with each spectrum of the group
+    auto weights = [&](uint32_t o, auto use) {
         double fac, f;
         int k;
         factor_and_pos(o, &fac, &k, &f);
-        ++nused;
         const LisStep* t = tab + k;
         // (tables and positions of any use keep the argument far inside the
         // range of exp_taylor)
@@ -1864,19 +1826,59 @@ __global__ void __launch_bounds__(kReduceBlock) k_reweight(const ReweightArgs a)
 #pragma unroll
             for (int l = 0; l < kReweightGroup; ++l) {
                 const LisStep q = t[(uint32_t)l * ns];
-                const double d = fac * exp_taylor(fma(f, q.d, q.at)) - about_r[l];
-                s1[l] += d;
-                s2[l] += d * d;
+                use(l, fac * exp_taylor(fma(f, q.d, q.at)));
             }
         } else {
 #pragma unroll
             for (int l = 0; l < kReweightGroup; ++l) {
                 const LisStep q = t[(uint32_t)l * ns];
-                const double d = fac * ::exp(q.at + f * q.d) - about_r[l];
-                s1[l] += d;
-                s2[l] += d * d;
+                use(l, fac * ::exp(q.at + f * q.d));
             }
         }
+    };
+    double s1[kReweightGroup], s2[kReweightGroup], about_r[kReweightGroup];
+#pragma unroll
+    for (int l = 0; l < kReweightGroup; ++l) s1[l] = 0.0;
+    // the first particles' weights, then their deviations from their mean
+    bool mine = false;
+    uint32_t n0 = 0;
+    uint64_t next = first;
+    __syncthreads();  // the tables
+    while (n0 == 0 && next < end) {
+        const uint64_t i = next + threadIdx.x;
+        mine = i < end && (a.exNF[sg.out_offset + (uint32_t)i] >> kFlagShift) == 0u;
+        n0 = (uint32_t)__syncthreads_count(mine ? 1 : 0);
+        next += kReduceBlock;
+        if (mine) weights(sg.out_offset + (uint32_t)i, [&](int l, double w) { s1[l] = w; });
+    }
+    {
+        const double v = wave_sum16(s1, lane);
+        if ((lane & 3u) == 0) sums[0][wid][lane >> 2] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < (uint32_t)kReweightGroup) {
+        double t = 0.0;
+        for (int w = 0; w < kReduceBlock / 64; ++w) t += sums[0][w][threadIdx.x];
+        t = n0 > 0 ? t / (double)n0 : 0.0;
+        about[threadIdx.x] = fabs(t) < __builtin_huge_val() ? t : 0.0;
+    }
+    __syncthreads();
+    unsigned long long nused = mine ? 1 : 0;
+#pragma unroll
+    for (int l = 0; l < kReweightGroup; ++l) {
+        about_r[l] = about[l];
+        s1[l] = mine ? s1[l] - about_r[l] : 0.0;
+        s2[l] = s1[l] * s1[l];
+    }
+    for (uint64_t i = next + threadIdx.x; i < end; i += kReduceBlock) {
+        const uint32_t o = sg.out_offset + (uint32_t)i;
+        if ((a.exNF[o] >> kFlagShift) != 0u) continue;  // capped or non-finite
+        ++nused;
+        weights(o, [&](int l, double w) {
+            const double d = w - about_r[l];
+            s1[l] += d;
+            s2[l] += d * d;
+        });
     }
     const double v1 = wave_sum16(s1, lane), v2 = wave_sum16(s2, lane);
     if ((lane & 3u) == 0) {
@@ -1892,14 +1894,16 @@ __global__ void __launch_bounds__(kReduceBlock) k_reweight(const ReweightArgs a)
             t2 += sums[1][w][l];
         }
         const size_t ob = (size_t)(l0 + l) * a.total_bins + a.out_base + blockIdx.x;
+        const double mean = n > 0.0 ? about[l] + t1 / n : 0.0;
+        double m2 = n > 0.0 ? t2 - t1 * (t1 / n) : 0.0;
+        m2 = m2 < 0.0 ? 0.0 : m2;
         if (a.parts == 1) {
-            mean_and_se(n, about[l], t1, t2, &a.flux[ob], &a.flux_se[ob]);
+            write_mean(n, mean, m2, &a.flux[ob], &a.flux_se[ob]);
         } else {
-            double* q = a.partial + 4 * (ob * a.parts + blockIdx.z);
+            double* q = a.partial + 3 * (ob * a.parts + blockIdx.z);
             q[0] = n;
-            q[1] = about[l];
-            q[2] = t1;
-            q[3] = t2;
+            q[1] = mean;
+            q[2] = m2;
         }
     }
 }
@@ -1913,16 +1917,22 @@ __global__ void __launch_bounds__(kReduceBlock) k_reweight_sum(const ReweightArg
     const size_t ob = (size_t)l * a.total_bins + a.out_base + b;
     const uint32_t count = a.segs[a.seg_base + b].count;
     const uint32_t np = (count + a.part - 1) / a.part;
-    double n = 0.0, s = 0.0, s1 = 0.0, s2 = 0.0;
+    const double* const q = a.partial + 3 * (ob * a.parts);
+    double n = 0.0, s = 0.0;
 #pragma unroll 4
     for (uint32_t z = 0; z < np; ++z) {
-        const double* q = a.partial + 4 * (ob * a.parts + z);
-        n += q[0];
-        s = q[1];
-        s1 += q[2];
-        s2 += q[3];
+        n += q[3 * z];
+        s += q[3 * z] * q[3 * z + 1];
     }
-    mean_and_se(n, s, s1, s2, &a.flux[ob], &a.flux_se[ob]);
+    double mean = n > 0.0 ? s / n : 0.0, c1 = 0.0, c2 = 0.0, m2 = 0.0;
+#pragma unroll 4
+    for (uint32_t z = 0; z < np; ++z) {
+        const double k = q[3 * z], d = q[3 * z + 1] - mean;
+        c1 += k > 0.0 ? k * d : 0.0;
+        c2 += k > 0.0 ? q[3 * z + 2] + k * (d * d) : 0.0;
+    }
+    if (n > 0.0) corrected(n, c1, c2, &mean, &m2);
+    write_mean(n, mean, m2, &a.flux[ob], &a.flux_se[ob]);
 }
 
 // ---------------------------------------------------------------------------

@@ -1463,21 +1463,22 @@ cosmica_status cosmica_plan_info(const cosmica_plan* p, uint64_t* total_bins,
 
 static_assert(kMaxLisKnots == COSMICA_MAX_LIS_KNOTS, "LDS table size and the ABI limit agree");
 
-// Splits the bins of a plan over workgroups: parts of at least `least` exits,
+// Splits the bins of a plan over workgroups: parts of `least` to `most` exits,
 // as many as give about 4 workgroups (of 256 threads) per CU with `groups`
-// workgroups per part; at most 64 parts a bin, 1 where the bins alone suffice.
-static void split_bins(const cosmica_plan* p, uint32_t groups, uint32_t least, uint32_t* part,
-                       uint32_t* parts)
+// workgroups per part; 64 parts a bin where that allows it, 1 where the bins
+// alone suffice.
+static void split_bins(const cosmica_plan* p, uint32_t groups, uint32_t least, uint32_t most,
+                       uint32_t* part, uint32_t* parts)
 {
     *part = ~0u;
     *parts = 1;
     const uint64_t want = (uint64_t)p->ctx->num_cus * 4;
-    if ((uint64_t)p->segs.size() * groups >= want) return;
     uint64_t largest = 0;
     for (const SegmentDev& s : p->segs) largest = std::max<uint64_t>(largest, s.count);
+    if ((uint64_t)p->segs.size() * groups >= want && largest <= most) return;
     uint64_t c = p->total_particles * groups / want;
     c = std::max<uint64_t>({c, least, (largest + 63) / 64});
-    c = (c + 255) / 256 * 256;
+    c = (std::min<uint64_t>(c, most) + 255) / 256 * 256;
     if (largest <= c) return;
     *part = (uint32_t)c;
     *parts = (uint32_t)((largest + c - 1) / c);
@@ -1532,8 +1533,8 @@ cosmica_status cosmica_plan_reweight(cosmica_plan* p, uint32_t n_lis, uint32_t n
     a.flux_se = sd;
     // split bins where one workgroup per (bin, group of spectra) leaves CUs idle
     const uint32_t groups = (n_lis + kReweightGroup - 1) / kReweightGroup;
-    split_bins(p, groups, 1024, &a.part, &a.parts);
-    if (a.parts > 1 && m.alloc(&a.partial, 4 * nout * a.parts) != COSMICA_OK) {
+    split_bins(p, groups, 1024, 65536, &a.part, &a.parts);
+    if (a.parts > 1 && m.alloc(&a.partial, 3 * nout * a.parts) != COSMICA_OK) {
         a.part = ~0u;  // no room for the parts' sums: whole bins
         a.parts = 1;
         a.partial = nullptr;
@@ -1576,7 +1577,7 @@ cosmica_status cosmica_plan_exit_range(cosmica_plan* p, uint32_t n_hist, double*
     a.total_bins = nb;
     a.p_max = pm;
     a.hist = h;
-    split_bins(p, 1, 4096, &a.part, &a.parts);
+    split_bins(p, 1, 4096, ~0u & ~255u, &a.part, &a.parts);
     if (a.parts > 1 && m.alloc(&a.part_max, (size_t)nb * a.parts) != COSMICA_OK) {
         a.part = ~0u;
         a.parts = 1;

@@ -1,6 +1,8 @@
 """The per-bin reduction where its sums, its time or its memory could go wrong:
 standard errors of bins whose first exit is far from the mean, bins whose exits
 are nearly all capped, bins of very different sizes."""
+import time
+
 import numpy as np
 import pytest
 
@@ -114,3 +116,76 @@ def test_more_parts_than_a_group(eng):
         assert abs(r["flux_se"][b] / np.sqrt(m2 / (n - 1) / n) - 1) < (
             16 * u * np.sqrt(1 + n * w.mean() ** 2 / m2))
         assert r["hist"][b].sum() == n and r["steps"][b] == ex["n"].sum()
+
+
+@pytest.mark.parametrize("bins,per_bin,seed,z2_least", [(1100, 300, 4, 280), (200, 5000, 14, 2900)])
+def test_reweighted_standard_error_does_not_depend_on_the_first_exit(eng, bins, per_bin, seed,
+                                                                     z2_least):
+    """As above for tabulated spectra, whole bins and split ones.  ln J = 8 ln P
+    from two knots 4 apart in ln P: with ln P < 2.8 the logarithm, the position
+    and the interpolation leave 8e-15 in the exponent, 72 units of 2^-53; 128
+    with the exponential and the sums."""
+    job = W.make_job(W.helio_1d(), W.species("p"), [1.0] * bins, [per_bin] * bins, seed=seed)
+    plan = eng.plan(job, "fp64", exits=True)
+    plan.execute()
+    P = plan.read(exits=True)[0]["exits"]["P"].reshape(bins, per_bin).astype(LD)
+    flux, se = plan.reweight(0.0, 4.0, [[0.0, 32.0]])
+    plan.destroy()
+    w = P ** LD(6.0)
+    mean = w.mean(1)
+    m2 = ((w - mean[:, None]) ** 2).sum(1)
+    assert ((w[:, 0] - mean) ** 2 / (m2 / per_bin)).max() > z2_least
+    u = LD(2.0) ** -53
+    np.testing.assert_array_less(np.abs(flux[0] / mean - 1), 128 * u)
+    np.testing.assert_array_less(np.abs(se[0] / np.sqrt(m2 / (per_bin - 1) / per_bin) - 1),
+                                 128 * u * np.sqrt(1 + per_bin * mean**2 / m2))
+
+
+def test_reweighting_of_capped_exits_costs_no_more_than_of_others(eng):
+    """16 spectra over 2,000,000 exits of one bin: all capped, and none."""
+    ms = []
+    for cap in (0, 1):
+        job = W.make_job(W.helio_1d(), W.species("p"), [2.0], [2_000_000])
+        job["step_cap"] = cap
+        plan = eng.plan(job, "mixed")
+        plan.execute()
+        plan.read()
+        t = []
+        for _ in range(4):
+            t0 = time.perf_counter()
+            plan.reweight(-3.0, 0.25, np.zeros((16, 40)))
+            t.append(1e3 * (time.perf_counter() - t0))
+        plan.destroy()
+        ms.append(min(t))
+    assert ms[1] < 1.5 * ms[0] + 0.2
+
+
+@pytest.mark.parametrize("counts", [[255, 256, 257, 1], [65536, 65537, 131073, 5]])
+def test_reweighting_at_the_edges_of_its_parts(eng, counts):
+    """Flagged exits at a part's start (half of the exits capped) and parts of
+    2^16 among so many spectra that whole bins would fill the device."""
+    n_lis = 4096 if max(counts) > 1000 else 17
+    job = W.make_job(W.helio_1d(), W.species("p"), [0.7, 2.0, 9.0, 3.0], counts)
+    rng = np.random.default_rng(1)
+    x = -2.0 + 0.5 * np.arange(17)
+    rows = rng.uniform(8, 10, (n_lis, 1)) - rng.uniform(2.3, 3.3, (n_lis, 1)) * x
+    for cap in (0, 500):
+        job["step_cap"] = cap
+        plan = eng.plan(job, "mixed", exits=True)
+        plan.execute()
+        ex = plan.read(exits=True)[0]["exits"]
+        flux, se = plan.reweight(-2.0, 0.5, rows)
+        plan.destroy()
+        at = 0
+        for b, (P0, n) in enumerate(zip(job["rigidity_gv"], counts)):
+            e = ex[at:at + n]
+            at += n
+            P = e["P"][e["flags"] == 0]
+            if len(P) < 2:
+                continue
+            for l in (0, n_lis - 1):
+                # a power law: exact between the knots
+                g = (rows[l, 0] - rows[l, -1]) / 8.0
+                w = np.exp(rows[l, 0] - g * (np.log(P) + 2.0)) * (P0 / P) ** 2
+                np.testing.assert_allclose(flux[l, b], w.mean(), rtol=1e-12)
+                np.testing.assert_allclose(se[l, b], w.std(ddof=1) / np.sqrt(len(P)), rtol=1e-12)
