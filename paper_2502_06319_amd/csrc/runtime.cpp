@@ -385,6 +385,18 @@ struct StaticHost {
 
 }  // namespace
 
+struct cosmica_plan;
+
+// Particles that a pass hands from the throughput to the latency kernel (68 B
+// per lane of the largest grid: 22 MB in binary32).
+struct HandList {
+    unsigned char* block = nullptr;
+    size_t bytes = 0;
+    uint32_t cap = 0;         // particles it holds
+    uint32_t* ctl = nullptr;  // its counters (within the block)
+    SliceDev* sl = nullptr;   // descriptors of the two launches (within the block)
+};
+
 struct cosmica_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -432,16 +444,16 @@ struct cosmica_ctx {
     unsigned char* up = nullptr;
     unsigned char* down = nullptr;
     hipEvent_t up_ev = nullptr;  // the last copy from `up`
-    // Particles that a pass hands from the throughput to the latency kernel: one
-    // list for the passes on the context's stream, made when a plan that can use it
-    // is created (68 B per lane of the largest grid: 22 MB in binary32) and given back
-    // when an allocation needs the room.
-    std::recursive_mutex hand_mu;  // held while launches that use it are enqueued
-    unsigned char* hand = nullptr;
-    size_t hand_bytes = 0;
-    uint32_t hand_cap = 0;        // particles it holds
-    uint32_t* hand_ctl = nullptr;  // its counters (within the block)
-    SliceDev* hand_sl = nullptr;   // descriptors of the two launches (within the block)
+    // Scratch that passes on the context's stream use where there is room for it:
+    // the hand-over list (one, made when a plan that can use it is created) and
+    // the partial sums of plans (`lenders` have them).  An allocation that needs
+    // the room takes it back.
+    std::recursive_mutex scratch_mu;  // held while launches that use it are enqueued
+    HandList hand;
+    std::vector<cosmica_plan*> lenders;
+    std::atomic<uint64_t> scratch_bytes{0};  // of all of it; counted in in_use
+    hipEvent_t scratch_ev = nullptr;  // the end of the last pass that used some (never captured)
+    bool scratch_open = false;        // launches use it that the event does not cover yet
     cosmica_ctx() = default;
     ~cosmica_ctx();  // defined once the serving types are complete
 };
@@ -462,20 +474,10 @@ void cache_trim(cosmica_ctx* ctx, uint64_t need)
     }
 }
 
-// Gives the hand-over list back to the device.
-void hand_release(cosmica_ctx* ctx)
-{
-    std::lock_guard<std::recursive_mutex> lk(ctx->hand_mu);
-    if (ctx->hand == nullptr) return;
-    (void)hipStreamSynchronize(ctx->stream);
-    (void)hipFree(ctx->hand);
-    ctx->in_use.fetch_sub(ctx->hand_bytes);
-    ctx->hand = nullptr;
-    ctx->hand_bytes = 0;
-    ctx->hand_cap = 0;
-}
+void scratch_release(cosmica_ctx* ctx);
 
-cosmica_status dalloc(cosmica_ctx* ctx, size_t bytes, void** p)
+// optional: fails where there is no room, without taking scratch back for it.
+cosmica_status dalloc(cosmica_ctx* ctx, size_t bytes, void** p, bool optional = false)
 {
     *p = nullptr;
     if (bytes == 0) return COSMICA_OK;
@@ -491,16 +493,16 @@ cosmica_status dalloc(cosmica_ctx* ctx, size_t bytes, void** p)
         }
     }
     if (ctx->in_use.load() + bytes > ctx->budget) cache_trim(ctx, bytes);
-    if (ctx->in_use.load() + bytes > ctx->budget) hand_release(ctx);
+    if (!optional && ctx->in_use.load() + bytes > ctx->budget) scratch_release(ctx);
     const uint64_t cur = ctx->in_use.fetch_add(bytes);
     if (cur + bytes > ctx->budget) {
         ctx->in_use.fetch_sub(bytes);
         return COSMICA_ENOMEM;
     }
     hipError_t e = hipMalloc(p, bytes);
-    if (e != hipSuccess) {
+    if (e != hipSuccess && !optional) {
         (void)hipGetLastError();
-        hand_release(ctx);
+        scratch_release(ctx);
         e = hipMalloc(p, bytes);
     }
     if (e != hipSuccess) {
@@ -545,10 +547,10 @@ struct DevSet {
         blocks.clear();
     }
     template <typename T>
-    cosmica_status alloc(T** p, size_t n)
+    cosmica_status alloc(T** p, size_t n, bool optional = false)
     {
         void* q = nullptr;
-        cosmica_status st = dalloc(ctx, n * sizeof(T), &q);
+        cosmica_status st = dalloc(ctx, n * sizeof(T), &q, optional);
         if (st != COSMICA_OK) return st;
         if (q) blocks.emplace_back(q, n * sizeof(T));
         *p = (T*)q;
@@ -806,7 +808,9 @@ struct cosmica_plan {
     unsigned char* res = nullptr;  // the block that holds them
     ResultAt res_at;
     uint32_t reduce_parts = 0;  // parts of the reduction (0: a workgroup per bin)
-    unsigned char* reduce_partial = nullptr;  // their sums
+    unsigned char* reduce_partial = nullptr;  // their sums (null: a workgroup per bin)
+    size_t partial_bytes = 0;
+    bool partial_captured = false;  // a graph holds its address: not taken back
     bool executed = false;
     bool own_out = true;
     bool uniform_key = false;  // every job has the same seed
@@ -815,9 +819,71 @@ struct cosmica_plan {
     double* exL = nullptr;     // energy form: summed loss per particle
     uint64_t key = 0;
     explicit cosmica_plan(cosmica_ctx* c) : ctx(c), mem(c) {}
+    ~cosmica_plan();
 };
 
 namespace {
+
+// Takes the context's scratch back for an allocation that needs the room, on
+// whichever thread that runs: no pass finds it from here on, and those enqueued
+// with it are waited for, by an event of their own and without the lock, so
+// that neither later passes nor a capture of the stream are held up.
+void scratch_release(cosmica_ctx* ctx)
+{
+    HandList hand;
+    std::vector<std::pair<cosmica_plan*, unsigned char*>> parts;
+    std::vector<size_t> bytes;
+    bool open = false;
+    {
+        std::lock_guard<std::recursive_mutex> lk(ctx->scratch_mu);
+        std::swap(hand, ctx->hand);
+        for (cosmica_plan* p : ctx->lenders) {
+            if (p->reduce_partial == nullptr || p->partial_captured) continue;
+            parts.emplace_back(p, p->reduce_partial);
+            bytes.push_back(p->partial_bytes);
+            p->reduce_partial = nullptr;
+        }
+        open = ctx->scratch_open;
+    }
+    if (hand.block == nullptr && parts.empty()) return;
+    const hipError_t e =
+        open ? hipStreamSynchronize(ctx->stream) : hipEventSynchronize(ctx->scratch_ev);
+    if (e != hipSuccess) {  // it may be in use: it stays where it was
+        (void)hipGetLastError();
+        std::lock_guard<std::recursive_mutex> lk(ctx->scratch_mu);
+        if (ctx->hand.block == nullptr) std::swap(hand, ctx->hand);
+        for (auto& q : parts)
+            if (std::find(ctx->lenders.begin(), ctx->lenders.end(), q.first) != ctx->lenders.end())
+                q.first->reduce_partial = q.second;
+        return;
+    }
+    uint64_t freed = hand.bytes;
+    if (hand.block != nullptr) (void)hipFree(hand.block);
+    for (size_t k = 0; k < parts.size(); ++k) {
+        (void)hipFree(parts[k].second);
+        freed += bytes[k];
+    }
+    ctx->scratch_bytes -= freed;
+    ctx->in_use.fetch_sub(freed);
+}
+
+// Scratch of at most `bytes`, if there is room for it.
+bool scratch_take(cosmica_ctx* ctx, size_t bytes, unsigned char** p)
+{
+    void* q = nullptr;
+    if (dalloc(ctx, bytes, &q, true) != COSMICA_OK) return false;
+    *p = (unsigned char*)q;
+    ctx->scratch_bytes += bytes;
+    return true;
+}
+
+// Gives scratch that nothing uses any more back to the block cache.
+void scratch_give(cosmica_ctx* ctx, unsigned char* p, size_t bytes)
+{
+    if (p == nullptr) return;
+    ctx->scratch_bytes -= bytes;
+    dfree(ctx, p, bytes);
+}
 
 // Offsets of arrays carved from one block, 256-byte aligned.
 struct Carve {
@@ -936,25 +1002,31 @@ struct PassDev {
 };
 
 // The hand-over list of the context for `lanes` particles, made if need be; false
-// where there is no room for it.  The caller holds hand_mu.
+// where there is no room for it.  The caller holds scratch_mu.
 bool hand_ready(cosmica_ctx* ctx, uint32_t lanes)
 {
-    if (ctx->hand != nullptr && ctx->hand_cap >= lanes) return true;
-    hand_release(ctx);
+    if (ctx->hand.block != nullptr && ctx->hand.cap >= lanes) return true;
+    if (ctx->hand.block != nullptr) {  // too small: no longer used once the stream is through
+        if (hipStreamSynchronize(ctx->stream) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        scratch_give(ctx, ctx->hand.block, ctx->hand.bytes);
+        ctx->hand = HandList{};
+    }
     Carve c;
     const size_t o_f = c.take((size_t)lanes * 7 * sizeof(double));
     const size_t o_u = c.take((size_t)lanes * 3 * sizeof(uint32_t));
     const size_t o_ctl = c.take(16 * sizeof(uint32_t));
     const size_t o_sl = c.take(2 * sizeof(SliceDev));
-    void* q = nullptr;
-    if (dalloc(ctx, c.at, &q) != COSMICA_OK) return false;
-    ctx->hand = (unsigned char*)q;
-    ctx->hand_bytes = c.at;
-    ctx->hand_cap = lanes;
-    ctx->hand_ctl = (uint32_t*)(ctx->hand + o_ctl);
-    ctx->hand_sl = (SliceDev*)(ctx->hand + o_sl);
-    double* f = (double*)(ctx->hand + o_f);
-    uint32_t* u = (uint32_t*)(ctx->hand + o_u);
+    HandList h;
+    if (!scratch_take(ctx, c.at, &h.block)) return false;
+    h.bytes = c.at;
+    h.cap = lanes;
+    h.ctl = (uint32_t*)(h.block + o_ctl);
+    h.sl = (SliceDev*)(h.block + o_sl);
+    double* f = (double*)(h.block + o_f);
+    uint32_t* u = (uint32_t*)(h.block + o_u);
     ParkDev pk;
     double** fields[7] = {&pk.r, &pk.P, &pk.t, &pk.th, &pk.ph, &pk.T, &pk.lam};
     for (int k = 0; k < 7; ++k) *fields[k] = f + (size_t)k * lanes;
@@ -962,7 +1034,7 @@ bool hand_ready(cosmica_ctx* ctx, uint32_t lanes)
     for (int k = 0; k < 3; ++k) *words[k] = u + (size_t)k * lanes;
     // Counters: 0 particles parked, 1 cursor of the second launch over them, 2 an
     // always empty list's count, 3-5 cursors and counts of empty lists, 6 overflow.
-    uint32_t* ctl = ctx->hand_ctl;
+    uint32_t* ctl = h.ctl;
     SliceDev sl[2];
     std::memset(sl, 0, sizeof(sl));
     for (int k = 0; k < 2; ++k) {
@@ -977,11 +1049,26 @@ bool hand_ready(cosmica_ctx* ctx, uint32_t lanes)
         sl[k].overflow = ctl + 6;
         sl[k].park_cap = lanes;
     }
-    if (upload_block(ctx, ctx->hand_sl, sizeof(sl),
-                     [&](unsigned char* h) { std::memcpy(h, sl, sizeof(sl)); }) == COSMICA_OK)
+    if (upload_block(ctx, h.sl, sizeof(sl),
+                     [&](unsigned char* m) { std::memcpy(m, sl, sizeof(sl)); }) != COSMICA_OK) {
+        // a list without its descriptors must not be found
+        (void)hipStreamSynchronize(ctx->stream);
+        scratch_give(ctx, h.block, h.bytes);
+        return false;
+    }
+    ctx->hand = h;
+    return true;
+}
+
+// Whether the context's stream is under capture (or cannot be asked).
+bool capturing(cosmica_ctx* ctx)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();
         return true;
-    hand_release(ctx);  // a list without its descriptors must not be found
-    return false;
+    }
+    return cap != hipStreamCaptureStatusNone;
 }
 
 // Whether a pass in the throughput kernel ends in the latency kernel: the waves
@@ -1058,19 +1145,17 @@ cosmica_status execute_prop(cosmica_ctx* ctx, const PassDev& d)
         }
         ctx->timings.grid_blocks = grid;
         ctx->timings.block = block;
-        // (a graph under capture may outlive the list)
-        std::lock_guard<std::recursive_mutex> lk(ctx->hand_mu);
         const uint64_t lanes = (uint64_t)grid * (uint64_t)block;
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        // (d.hand: the caller holds scratch_mu; a graph under capture may outlive
+        // the list)
         if (a.latency == 0u && d.hand && hand_over(model, d.work[model], lanes) &&
-            ctx->hand != nullptr && ctx->hand_cap >= lanes &&
-            hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess &&
-            cap == hipStreamCaptureStatusNone) {
-            HIP_TRY(launch_fill_u32(ctx->hand_ctl, 0u, 16, ctx->stream));
-            a.slice = ctx->hand_sl;
+            ctx->hand.block != nullptr && ctx->hand.cap >= lanes && !capturing(ctx)) {
+            ctx->scratch_open = true;
+            HIP_TRY(launch_fill_u32(ctx->hand.ctl, 0u, 16, ctx->stream));
+            a.slice = ctx->hand.sl;
             a.hand_over = 1u;
             HIP_TRY(launch_model<R>(model, a, grid, block, ctx->stream));
-            a.slice = ctx->hand_sl + 1;
+            a.slice = ctx->hand.sl + 1;
             a.hand_over = 0u;
             a.latency = 1u;
             a.lane_cap = 64u;
@@ -1177,6 +1262,7 @@ cosmica_status cosmica_create(cosmica_ctx** out, int device, uint64_t hbm_budget
     HIP_TRY(hipHostMalloc((void**)&ctx->up, cosmica_ctx::kUpBytes, hipHostMallocDefault));
     HIP_TRY(hipHostMalloc((void**)&ctx->down, cosmica_ctx::kDownBytes, hipHostMallocDefault));
     HIP_TRY(hipEventCreateWithFlags(&ctx->up_ev, hipEventDisableTiming));
+    HIP_TRY(hipEventCreateWithFlags(&ctx->scratch_ev, hipEventDisableTiming));
     for (int m = 0; m < 2; ++m)
         for (int q = 0; q < 2; ++q) ctx->launch[m][q] = cosmica_launch{256, 0, (int)kSpreadChunk, 2};
     *out = ctx.release();
@@ -1247,7 +1333,7 @@ cosmica_status cosmica_plan_create(cosmica_ctx* ctx, const cosmica_job* jobs, in
                                       p->uniform_key) *
             (uint64_t)ctx->launch[m][precision].block;
         if (hand_over(m, p->work[m], lanes)) {
-            std::lock_guard<std::recursive_mutex> lk(ctx->hand_mu);
+            std::lock_guard<std::recursive_mutex> lk(ctx->scratch_mu);
             (void)hand_ready(ctx, (uint32_t)lanes);  // without room: no hand-over
         }
     }
@@ -1275,9 +1361,11 @@ cosmica_status cosmica_plan_create(cosmica_ctx* ctx, const cosmica_job* jobs, in
     p->steps = (uint64_t*)(p->res + p->res_at.steps);
     p->ncap = (uint32_t*)(p->res + p->res_at.ncap);
     p->nnan = (uint32_t*)(p->res + p->res_at.nnan);
-    if (p->reduce_parts != 0 &&
-        p->mem.alloc(&p->reduce_partial, p->reduce_parts * kReducePartBytes) != COSMICA_OK)
-        p->reduce_partial = nullptr;  // no room: a workgroup per bin
+    p->partial_bytes = ((size_t)p->reduce_parts * kReducePartBytes + 255) & ~(size_t)255;
+    if (p->reduce_parts != 0 && scratch_take(ctx, p->partial_bytes, &p->reduce_partial)) {
+        std::lock_guard<std::recursive_mutex> lk(ctx->scratch_mu);
+        ctx->lenders.push_back(p.get());
+    }
     *out = p.release();
     return COSMICA_OK;
 }
@@ -1289,6 +1377,7 @@ cosmica_status cosmica_plan_execute(cosmica_plan* p, const cosmica_bins_dev* out
     HIP_TRY(hipSetDevice(ctx->device));
     HIP_TRY(hipEventRecord(ctx->ev[0], ctx->stream));
     HIP_TRY(launch_fill_u32(p->counters_d, 0u, 8, ctx->stream));
+    std::lock_guard<std::recursive_mutex> lk(ctx->scratch_mu);
     const PassDev d = pass_of(p);
     cosmica_status st = p->prec == COSMICA_PREC_MIXED ? execute_prop<float>(ctx, d)
                                                        : execute_prop<double>(ctx, d);
@@ -1307,6 +1396,12 @@ cosmica_status cosmica_plan_execute(cosmica_plan* p, const cosmica_bins_dev* out
     r.n_segs = (uint32_t)p->segs.size();
     r.n_parts = p->reduce_parts;
     r.partial = p->reduce_partial;
+    if (p->reduce_partial != nullptr) {
+        if (capturing(ctx))
+            p->partial_captured = true;
+        else
+            ctx->scratch_open = true;
+    }
     if (out == nullptr) {
         r.hist = p->hist;
         r.flux = p->flux;
@@ -1330,6 +1425,10 @@ cosmica_status cosmica_plan_execute(cosmica_plan* p, const cosmica_bins_dev* out
         HIP_TRY(hipMemcpyAsync(p->steps, r.steps, p->segs.size() * 8, hipMemcpyDeviceToDevice,
                                ctx->stream));
     HIP_TRY(hipEventRecord(ctx->ev[2], ctx->stream));
+    if (ctx->scratch_open) {
+        HIP_TRY(hipEventRecord(ctx->scratch_ev, ctx->stream));
+        ctx->scratch_open = false;
+    }
     p->executed = true;
     p->own_out = out == nullptr;
     ctx->last_steps = r.steps;
@@ -1534,7 +1633,7 @@ cosmica_status cosmica_plan_reweight(cosmica_plan* p, uint32_t n_lis, uint32_t n
     // split bins where one workgroup per (bin, group of spectra) leaves CUs idle
     const uint32_t groups = (n_lis + kReweightGroup - 1) / kReweightGroup;
     split_bins(p, groups, 1024, 65536, &a.part, &a.parts);
-    if (a.parts > 1 && m.alloc(&a.partial, 3 * nout * a.parts) != COSMICA_OK) {
+    if (a.parts > 1 && m.alloc(&a.partial, 3 * nout * a.parts, true) != COSMICA_OK) {
         a.part = ~0u;  // no room for the parts' sums: whole bins
         a.parts = 1;
         a.partial = nullptr;
@@ -1578,7 +1677,7 @@ cosmica_status cosmica_plan_exit_range(cosmica_plan* p, uint32_t n_hist, double*
     a.p_max = pm;
     a.hist = h;
     split_bins(p, 1, 4096, ~0u & ~255u, &a.part, &a.parts);
-    if (a.parts > 1 && m.alloc(&a.part_max, (size_t)nb * a.parts) != COSMICA_OK) {
+    if (a.parts > 1 && m.alloc(&a.part_max, (size_t)nb * a.parts, true) != COSMICA_OK) {
         a.part = ~0u;
         a.parts = 1;
         a.part_max = nullptr;
@@ -1591,6 +1690,19 @@ cosmica_status cosmica_plan_exit_range(cosmica_plan* p, uint32_t n_hist, double*
     if (p_max) std::memcpy(p_max, got, (size_t)nb * 8);
     if (hist) std::memcpy(hist, got + (size_t)nb * 8, hist_bytes);
     return COSMICA_OK;
+}
+
+// (the caller has waited for the plan's passes)
+cosmica_plan::~cosmica_plan()
+{
+    unsigned char* q = nullptr;
+    {
+        std::lock_guard<std::recursive_mutex> lk(ctx->scratch_mu);
+        auto it = std::find(ctx->lenders.begin(), ctx->lenders.end(), this);
+        if (it != ctx->lenders.end()) ctx->lenders.erase(it);
+        std::swap(q, reduce_partial);
+    }
+    scratch_give(ctx, q, partial_bytes);
 }
 
 void cosmica_plan_destroy(cosmica_plan* p)
@@ -2632,15 +2744,15 @@ cosmica_status group_create(cosmica_ctx* ctx, int model, int prec, ServeGroup** 
     if ((st = g->mem.alloc(&g->r_nnan, B)) != COSMICA_OK) return st;
     g->pool_cap = pool_particles(ctx);
     if (g->pool_cap < 1024) return COSMICA_ENOMEM;
-    g->parts_cap = (uint32_t)(g->pool_cap / kReducePart) + B;
-    if (g->mem.alloc(&g->r_partial, g->parts_cap * kReducePartBytes) != COSMICA_OK)
-        g->r_partial = nullptr;  // no room: a workgroup per bin
     if ((st = g->mem.alloc(&g->exP, g->pool_cap)) != COSMICA_OK) return st;
     if ((st = g->mem.alloc(&g->exT, g->pool_cap)) != COSMICA_OK) return st;
     if ((st = g->mem.alloc(&g->exNF, g->pool_cap)) != COSMICA_OK) return st;
     g->ring_cap = ring_initial();
     if ((st = dalloc(ctx, g->ring_cap * sizeof(ChunkDev), (void**)&g->ring_d)) != COSMICA_OK)
         return st;
+    g->parts_cap = (uint32_t)(g->pool_cap / kReducePart) + B;
+    if (g->mem.alloc(&g->r_partial, g->parts_cap * kReducePartBytes, true) != COSMICA_OK)
+        g->r_partial = nullptr;  // no room: a workgroup per bin
     g->free_ranges[0] = g->pool_cap;
     for (int s = (int)S - 1; s >= 0; --s) g->free_slots.push_back(s);
     g->segs_h.resize((size_t)S * B);
@@ -3318,9 +3430,10 @@ void cosmica_destroy(cosmica_ctx* ctx)
     for (int i = 0; i < 4; ++i)
         if (ctx->ev[i]) (void)hipEventDestroy(ctx->ev[i]);
     if (ctx->up_ev) (void)hipEventDestroy(ctx->up_ev);
+    if (ctx->scratch_ev) (void)hipEventDestroy(ctx->scratch_ev);
     if (ctx->up) (void)hipHostFree(ctx->up);
     if (ctx->down) (void)hipHostFree(ctx->down);
-    hand_release(ctx);
+    if (ctx->hand.block) (void)hipFree(ctx->hand.block);  // (its last pass has ended)
     cache_trim(ctx, ~0ull);
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;

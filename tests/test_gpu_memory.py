@@ -1,0 +1,182 @@
+"""Device memory a context can do without (the hand-over list, partial sums of a
+reduction): it makes way for what needs the room, takes nothing from others,
+and changes no result."""
+import importlib.util
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2502_06319_amd import cosmica as C
+from paper_2502_06319_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("hist", "flux", "flux_se", "mean_exit_time_s", "steps", "n_capped", "n_nan")
+
+
+def _held(e):
+    return e.serve_stats()["bytes_in_use"]
+
+
+def _sheet():
+    """Paths along the sheet, more than twice the lanes of the shape below."""
+    return dict(W.make_job(W.c2_helio(), W.species("e-"), W.log_bins(0.3, 30.0, 10), 4000, seed=21),
+                step_cap=300)
+
+
+def _engine(budget=0):
+    e = C.Engine(0, hbm_budget_bytes=budget)
+    e.set_launch(1, "mixed", block=64, blocks_per_cu=1)
+    return e
+
+
+def _sizes(*jobs):
+    """Bytes the plans of the jobs hold, one after the other."""
+    with _engine() as e:
+        at, plans = [0], []
+        for j in jobs:
+            plans.append(e.plan(j, "mixed"))
+            at.append(_held(e))
+        for p in plans:
+            p.destroy()
+    return np.diff(at).tolist()
+
+
+def _same(a, b):
+    for x, y in zip(a, b):
+        for k in KEYS:
+            np.testing.assert_array_equal(x[k], y[k], err_msg=k)
+
+
+def _radial(n):
+    return W.make_job(W.helio_1d(), W.species("p"), [2.0, 5.0], [n, 300], seed=7)
+
+
+def test_a_plan_gets_the_room_of_partial_sums():
+    """Two plans of 300,300 and 400,300 exits in a budget that holds both (20.5 B
+    an exit, tables and results of 3 KB and roundings) and not their partial
+    sums (16 and 22 KB): both run, with the same bits."""
+    jobs = [_radial(300_000), _radial(400_000)]
+    with C.Engine(0) as e:
+        want = [e.run(j, "mixed") for j in jobs]
+    with _engine(int(20.5 * 700_600) + (14 << 10)) as e:
+        plans = []
+        try:
+            for j in jobs:
+                plans.append(e.plan(j, "mixed"))
+            for _ in range(2):
+                for p, w in zip(plans, want):
+                    p.execute()
+                    _same(p.read(), w)
+        finally:
+            for p in plans:
+                p.destroy()
+
+
+def test_the_hand_over_list_makes_way_while_a_pass_uses_it():
+    sheet, radial = _sheet(), _radial(300_000)
+    with _engine() as e:
+        want, want_r = e.run(sheet, "mixed"), e.run(radial, "mixed")
+    held, more = _sizes(sheet, radial)
+    with _engine(held + more - (1 << 19)) as e:
+        p = e.plan(sheet, "mixed")
+        assert _held(e) == held
+        p.execute()  # in flight
+        q = e.plan(radial, "mixed")
+        q.execute()
+        assert _held(e) < held + more - (1 << 20)  # the list's 1.1 MB are gone
+        _same(p.read(), want)
+        p.execute()  # without a list
+        _same(p.read(), want)
+        q.execute()
+        _same(q.read(), want_r)
+        p.destroy()
+        q.destroy()
+
+
+def test_partial_sums_take_nothing_from_the_hand_over_list():
+    """A plan that fits but for its partial sums does without them."""
+    sheet, radial = _sheet(), _radial(600_000)
+    with C.Engine(0) as e:
+        want = e.run(radial, "mixed")
+    held, more = _sizes(sheet, radial)
+    partial = 256 * -(-56 * 587 // 256)
+    with _engine(held + more - partial + 1024) as e:
+        p, q = e.plan(sheet, "mixed"), e.plan(radial, "mixed")
+        assert _held(e) == held + more - partial
+        q.execute()
+        _same(q.read(), want)
+        p.destroy()
+        q.destroy()
+
+
+def test_reduction_under_capture_keeps_its_partial_sums():
+    """A graph holds the address of the plan's partial sums: they stay with the
+    plan when another one needs room, and replays between the context's own
+    passes give the eager result."""
+    if importlib.util.find_spec("torch") is None:
+        pytest.skip("torch not available")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", CAPTURE_CHILD, root], capture_output=True, text=True,
+                         timeout=100)
+    assert out.returncode == 0, out.stderr[-2000:]
+    assert "capture-ok" in out.stdout
+
+
+CAPTURE_CHILD = r"""
+import sys, numpy as np
+import torch
+sys.path.insert(0, sys.argv[1])
+from paper_2502_06319_amd import cosmica as C, workloads as W
+def radial(n):
+    return W.make_job(W.helio_1d(), W.species("p"), [2.0, 5.0], [n, 300], seed=7)
+stream = torch.cuda.Stream()
+held = []
+with C.Engine(0, stream=stream) as e:
+    for n in (300000, 400000):
+        p = e.plan(radial(n), "mixed")
+        held.append(e.serve_stats()["bytes_in_use"])
+        if n == 300000:
+            p.execute(); want = p.read()[0]
+            keep = p
+    q = p
+    q.destroy(); keep.destroy()
+# room for both plans but for the second one's partial sums and a little more
+e = C.Engine(0, hbm_budget_bytes=held[1] - 56 * 390 - 4096, stream=stream)
+plan = e.plan(radial(300000), "mixed")
+dev = torch.device("cuda:0")
+out = {"hist": torch.zeros((2, C.NHIST), dtype=torch.int32, device=dev)}
+for k in ("flux", "flux_se", "mean_exit_time_s"):
+    out[k] = torch.zeros(2, dtype=torch.float64, device=dev)
+torch.cuda.synchronize()
+g = torch.cuda.CUDAGraph()
+with torch.cuda.graph(g, stream=stream, capture_error_mode="relaxed"):
+    plan.execute(out)
+try:
+    other = e.plan(radial(400000), "mixed")
+except C.CosmicaError as err:
+    other = None
+assert other is None     # what the graph uses is not taken back
+other = e.plan(radial(100000), "mixed")
+for i in range(4):
+    for t in out.values():
+        t.zero_()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        g.replay()
+    stream.synchronize()
+    np.testing.assert_array_equal(out["hist"].cpu().numpy().astype(np.uint32), want["hist"])
+    for k in ("flux", "flux_se", "mean_exit_time_s"):
+        np.testing.assert_array_equal(out[k].cpu().numpy(), want[k])
+    other.execute()
+    other.read()
+    plan.execute()
+    np.testing.assert_array_equal(plan.read()[0]["flux"], want["flux"])
+other.destroy()
+plan.destroy()
+e.close()
+print("capture-ok")
+"""
