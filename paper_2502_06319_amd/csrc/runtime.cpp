@@ -2597,7 +2597,8 @@ uint64_t pool_particles(cosmica_ctx* ctx)
     const char* e = std::getenv("COSMICA_SERVE_POOL");
     long long v = e ? std::strtoll(e, nullptr, 10) : 0;
     uint64_t want = v > 0 ? (uint64_t)v : (256ull << 20);
-    const uint64_t used = ctx->in_use.load() - ctx->cached.load();  // cached blocks give way
+    // cached blocks and scratch give way
+    const uint64_t used = ctx->in_use.load() - ctx->cached.load() - ctx->scratch_bytes.load();
     const uint64_t room = ctx->budget > used + (512ull << 20) ? ctx->budget - used - (512ull << 20) : 0;
     return std::min<uint64_t>(want, room / 20);
 }

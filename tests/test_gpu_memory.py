@@ -113,6 +113,23 @@ def test_partial_sums_take_nothing_from_the_hand_over_list():
         q.destroy()
 
 
+def test_serving_pool_does_not_shrink_for_scratch():
+    """The admission pool of a context that holds a hand-over list (17 MB) is
+    that of one without: its first request adds as many bytes.  Both contexts
+    had the same plan (and keep its blocks); 600,000 particles are more than
+    twice the lanes of 4 workgroups a CU, and fewer than those of 5."""
+    grown = []
+    for per_cu in (5, 4):
+        with C.Engine(0, hbm_budget_bytes=800 << 20) as e:
+            e.set_launch(1, "mixed", block=256, blocks_per_cu=per_cu)
+            e.plan(dict(_sheet(), particles_per_bin=[60_000] * 10), "mixed").destroy()
+            before = _held(e)
+            t = e.submit(_radial(100), "mixed")
+            assert t.wait(60000) == C.OK
+            grown.append(_held(e) - before)
+    assert grown[1] == grown[0]
+
+
 def test_reduction_under_capture_keeps_its_partial_sums():
     """A graph holds the address of the plan's partial sums: they stay with the
     plan when another one needs room, and replays between the context's own
