@@ -1273,9 +1273,11 @@ cosmica_status cosmica_create(cosmica_ctx** out, int device, uint64_t hbm_budget
 static_assert((uint64_t)COSMICA_MAX_JOBS * kRegionStride * sizeof(RegionDev<double>) <= (1ull << 32),
               "region offsets must fit 32 bits");
 
-cosmica_status cosmica_plan_create(cosmica_ctx* ctx, const cosmica_job* jobs, int32_t n_jobs,
-                                   cosmica_precision precision, int32_t want_exits,
-                                   cosmica_plan** out)
+// cosmica_plan_create, with the plan's tables still on their way to the device
+// (in stream order).
+static cosmica_status plan_create(cosmica_ctx* ctx, const cosmica_job* jobs, int32_t n_jobs,
+                                  cosmica_precision precision, int32_t want_exits,
+                                  cosmica_plan** out)
 {
     if (ctx == nullptr || out == nullptr || jobs == nullptr || n_jobs < 1 ||
         n_jobs > COSMICA_MAX_JOBS)
@@ -1368,6 +1370,22 @@ cosmica_status cosmica_plan_create(cosmica_ctx* ctx, const cosmica_job* jobs, in
     }
     *out = p.release();
     return COSMICA_OK;
+}
+
+// The tables are on the device when it returns: a graph of the plan may be
+// launched on any stream.
+cosmica_status cosmica_plan_create(cosmica_ctx* ctx, const cosmica_job* jobs, int32_t n_jobs,
+                                   cosmica_precision precision, int32_t want_exits,
+                                   cosmica_plan** out)
+{
+    const cosmica_status st = plan_create(ctx, jobs, n_jobs, precision, want_exits, out);
+    if (st != COSMICA_OK) return st;
+    const hipError_t e = hipEventSynchronize(ctx->up_ev);
+    if (e == hipSuccess) return COSMICA_OK;
+    last_hip_error() = e;
+    cosmica_plan_destroy(*out);
+    *out = nullptr;
+    return COSMICA_EDEVICE;
 }
 
 cosmica_status cosmica_plan_execute(cosmica_plan* p, const cosmica_bins_dev* out)
@@ -1728,7 +1746,7 @@ cosmica_status cosmica_run(cosmica_ctx* ctx, const cosmica_job* jobs, int32_t n_
     for (int j = 0; j < n_jobs; ++j) want |= results[j].exits != nullptr;
     const auto t0 = std::chrono::steady_clock::now();
     cosmica_plan* p = nullptr;
-    cosmica_status st = cosmica_plan_create(ctx, jobs, n_jobs, precision, want ? 1 : 0, &p);
+    cosmica_status st = plan_create(ctx, jobs, n_jobs, precision, want ? 1 : 0, &p);
     if (st != COSMICA_OK) return st;
     const double up =
         std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();

@@ -197,3 +197,36 @@ plan.destroy()
 e.close()
 print("capture-ok")
 """
+
+
+UPLOAD_CHILD = r"""
+import sys
+import torch
+sys.path.insert(0, sys.argv[1])
+from paper_2502_06319_amd import cosmica as C, workloads as W
+stream = torch.cuda.Stream()
+e = C.Engine(0, stream=stream)
+busy = e.plan(W.make_job(W.helio_1d(), W.species("p"), [0.5] * 64, [500_000] * 64), "fp64")
+other = W.c1_job(particles_per_bin=8)
+busy.execute()
+pending = not stream.query()       # tens of milliseconds
+plan = e.plan(other, "fp64")
+through = stream.query()           # what was enqueued before the tables, and they
+plan.destroy()
+busy.destroy()
+e.close()
+assert pending and through, (pending, through)
+print("upload-ok")
+"""
+
+
+def test_a_new_plan_has_its_tables_on_the_device():
+    """Also where the context's stream is busy: the plan may be captured and its
+    graph launched on another stream."""
+    if importlib.util.find_spec("torch") is None:
+        pytest.skip("torch not available")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", UPLOAD_CHILD, root], capture_output=True, text=True,
+                         timeout=100)
+    assert out.returncode == 0, out.stderr[-2000:]
+    assert "upload-ok" in out.stdout
