@@ -363,6 +363,19 @@ cosmica_status cosmica_tune_jobs(cosmica_ctx* ctx, const cosmica_job* jobs, int3
 /* Section timings of the last execution. */
 cosmica_status cosmica_get_timings(cosmica_ctx* ctx, cosmica_timings* out);
 
+/* Which kernels ran: for the radial and the 3D particles of the last
+ * execution, 1 if the kernel for few waves per SIMD took them; how many of its
+ * particles the other kernel handed over to it at the end (0 once their list
+ * has been given back); and, since the context was created, the serving slices
+ * enqueued and those of them in that kernel.  Waits for the last execution. */
+typedef struct {
+    int32_t latency[2];
+    uint64_t handed_over;
+    uint64_t slices;
+    uint64_t latency_slices;
+} cosmica_passes;
+cosmica_status cosmica_get_passes(cosmica_ctx* ctx, cosmica_passes* out);
+
 /* Serving (continuous batching).  cosmica_submit copies the job and queues it;
  * a worker thread admits queued jobs while the device-memory footprint of
  * resident particle state + exit records stays within the budget, and runs the

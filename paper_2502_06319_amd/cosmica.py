@@ -115,6 +115,11 @@ class Launch(ctypes.Structure):
                 ("chunk", ctypes.c_int32), ("order", ctypes.c_int32)]
 
 
+class Passes(ctypes.Structure):
+    _fields_ = [("latency", ctypes.c_int32 * 2), ("handed_over", ctypes.c_uint64),
+                ("slices", ctypes.c_uint64), ("latency_slices", ctypes.c_uint64)]
+
+
 class Timings(ctypes.Structure):
     _fields_ = [("upload_ms", ctypes.c_double), ("propagate_ms", ctypes.c_double),
                 ("reduce_ms", ctypes.c_double), ("download_ms", ctypes.c_double),
@@ -156,6 +161,7 @@ _SIGS = {
     "cosmica_tune_jobs": (ctypes.c_int, [ctypes.c_void_p, ctypes.POINTER(Job), ctypes.c_int32,
                                          ctypes.c_int, ctypes.c_uint64, ctypes.c_char_p]),
     "cosmica_get_timings": (ctypes.c_int, [ctypes.c_void_p, ctypes.POINTER(Timings)]),
+    "cosmica_get_passes": (ctypes.c_int, [ctypes.c_void_p, ctypes.POINTER(Passes)]),
     "cosmica_submit": (ctypes.c_int, [ctypes.c_void_p, ctypes.POINTER(Job), ctypes.c_int,
                                       ctypes.POINTER(Result), c_u64_p]),
     "cosmica_poll": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_uint64,
@@ -472,6 +478,13 @@ class Engine:
         t = Timings()
         _check(load().cosmica_get_timings(self.handle, ctypes.byref(t)), "get_timings")
         return {k: getattr(t, k) for k, _ in Timings._fields_}
+
+    def passes(self) -> dict:
+        """Which kernels ran: latency (radial, 3D), handed_over, slices, latency_slices."""
+        t = Passes()
+        _check(load().cosmica_get_passes(self.handle, ctypes.byref(t)), "get_passes")
+        return {"latency": (t.latency[0], t.latency[1]), "handed_over": t.handed_over,
+                "slices": t.slices, "latency_slices": t.latency_slices}
 
     # serving
     def submit(self, job: dict, precision="mixed", exits: bool = False) -> Ticket:

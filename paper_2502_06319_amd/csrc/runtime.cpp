@@ -417,6 +417,9 @@ struct cosmica_ctx {
     // kernel and the number of waves from the work of each pass
     bool auto_launch[2][2] = {{true, true}, {true, true}};
     cosmica_timings timings{};
+    int32_t latency_ran[2] = {0, 0};  // last execution: the latency kernel took the model's particles
+    bool handed = false;              // it handed particles over, and the list is still there
+    std::atomic<uint64_t> slices{0}, latency_slices{0};
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     // steps of the last execution: device array and its length
     const uint64_t* last_steps = nullptr;
@@ -837,6 +840,7 @@ void scratch_release(cosmica_ctx* ctx)
     {
         std::lock_guard<std::recursive_mutex> lk(ctx->scratch_mu);
         std::swap(hand, ctx->hand);
+        ctx->handed = false;
         for (cosmica_plan* p : ctx->lenders) {
             if (p->reduce_partial == nullptr || p->partial_captured) continue;
             parts.emplace_back(p, p->reduce_partial);
@@ -1013,6 +1017,7 @@ bool hand_ready(cosmica_ctx* ctx, uint32_t lanes)
         }
         scratch_give(ctx, ctx->hand.block, ctx->hand.bytes);
         ctx->hand = HandList{};
+        ctx->handed = false;
     }
     Carve c;
     const size_t o_f = c.take((size_t)lanes * 7 * sizeof(double));
@@ -1099,8 +1104,10 @@ int throughput_grid(cosmica_ctx* ctx, int model, int prec, const PassWork& w, bo
 template <typename R>
 cosmica_status execute_prop(cosmica_ctx* ctx, const PassDev& d)
 {
+    ctx->handed = false;
     for (int model = 0; model < 2; ++model) {
         const uint32_t nch = d.n_chunks[model];
+        ctx->latency_ran[model] = 0;
         if (nch == 0) continue;
         const cosmica_launch& L = ctx->launch[model][d.prec];
         PropArgs<R> a;
@@ -1145,12 +1152,14 @@ cosmica_status execute_prop(cosmica_ctx* ctx, const PassDev& d)
         }
         ctx->timings.grid_blocks = grid;
         ctx->timings.block = block;
+        ctx->latency_ran[model] = (int32_t)a.latency;
         const uint64_t lanes = (uint64_t)grid * (uint64_t)block;
         // (d.hand: the caller holds scratch_mu; a graph under capture may outlive
         // the list)
         if (a.latency == 0u && d.hand && hand_over(model, d.work[model], lanes) &&
             ctx->hand.block != nullptr && ctx->hand.cap >= lanes && !capturing(ctx)) {
             ctx->scratch_open = true;
+            ctx->handed = true;
             HIP_TRY(launch_fill_u32(ctx->hand.ctl, 0u, 16, ctx->stream));
             a.slice = ctx->hand.sl;
             a.hand_over = 1u;
@@ -2075,6 +2084,26 @@ cosmica_status cosmica_get_timings(cosmica_ctx* ctx, cosmica_timings* out)
     cosmica_status st = finish_timings(ctx);
     if (st != COSMICA_OK) return st;
     *out = ctx->timings;
+    return COSMICA_OK;
+}
+
+cosmica_status cosmica_get_passes(cosmica_ctx* ctx, cosmica_passes* out)
+{
+    if (ctx == nullptr || out == nullptr) return COSMICA_EINVAL;
+    HIP_TRY(hipSetDevice(ctx->device));
+    uint32_t n = 0;
+    {
+        std::lock_guard<std::recursive_mutex> lk(ctx->scratch_mu);
+        if (ctx->handed) {
+            HIP_TRY(hipEventSynchronize(ctx->scratch_ev));
+            HIP_TRY(hipMemcpy(&n, ctx->hand.ctl, sizeof(n), hipMemcpyDeviceToHost));
+        }
+    }
+    std::memset(out, 0, sizeof(*out));
+    for (int m = 0; m < 2; ++m) out->latency[m] = ctx->latency_ran[m];
+    out->handed_over = n;
+    out->slices = ctx->slices.load();
+    out->latency_slices = ctx->latency_slices.load();
     return COSMICA_OK;
 }
 
@@ -3034,6 +3063,8 @@ cosmica_status launch_slice(ServeGroup* g)
         }
     }
     HIP_TRY(launch_model<R>(g->model, a, grid, g->block, s));
+    ctx->slices += 1;
+    ctx->latency_slices += a.latency;
     CloseArgs k;
     std::memset(&k, 0, sizeof(k));
     k.sl = g->slice_h[p];

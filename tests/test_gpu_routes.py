@@ -1,0 +1,84 @@
+"""Which kernel a pass and a served slice run: the launch of the rule's choice,
+the latency kernel's where it is its, and results that do not depend on it."""
+import numpy as np
+import pytest
+
+from paper_2502_06319_amd import cosmica as C
+from paper_2502_06319_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("hist", "flux", "flux_se", "mean_exit_time_s", "steps", "n_capped", "n_nan")
+WAVES = 1024
+
+
+def _job(model, n, **kw):
+    if model == 0:
+        job = W.make_job(W.helio_1d(), W.species("p"), [2.0], [n])
+    else:
+        job = W.make_job(W.c2_helio(), W.species("p"), [2.0], [n])
+    job.update(kw)
+    return job
+
+
+def _same(a, b):
+    for k in KEYS:
+        np.testing.assert_array_equal(a[k], b[k], err_msg=k)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("model", [0, 1])
+@pytest.mark.parametrize("n", [1, 65, WAVES, WAVES + 1, 16 * WAVES, 64 * WAVES, 64 * WAVES + 1])
+def test_small_passes_run_the_latency_kernel(model, precision, n):
+    """By default, in as many workgroups as spread the particles over 1,024 waves
+    (1,025 particles: 2 a wave, 8 a workgroup, 129 of them); in a set shape
+    never, and with the same bits."""
+    job = _job(model, n, step_cap=200)
+    with C.Engine(0) as e:
+        few = e.run(job, precision)[0]
+        assert e.passes()["latency"][model] == 1
+        assert e.passes()["latency"][1 - model] == 0
+        per_wave = min(64, -(-n // WAVES))
+        if n <= 64 * WAVES:
+            assert e.timings()["grid_blocks"] == -(-n // (4 * per_wave))
+        e.set_launch(model, precision, block=256, blocks_per_cu=0, chunk=32, order=2)
+        full = e.run(job, precision)[0]
+        assert e.passes() == {"latency": (0, 0), "handed_over": 0, "slices": 0, "latency_slices": 0}
+        assert e.timings()["grid_blocks"] == -(-n // 256)
+    _same(few, full)
+
+
+@pytest.mark.parametrize("precision,energy", [("mixed", 0), ("mixed", 1), ("fp64", 0)])
+def test_particles_are_handed_over(precision, energy):
+    """A pass with more than twice as many particles as lanes and paths along the
+    sheet hands some over: at most one a lane, and not in run_static, whose
+    results are the same.  (The cap lets exits come first, so that the lanes of
+    a wave hold particles of different ages when the queue is empty.)"""
+    job = W.make_job(W.c2_helio(), W.species("e-"), W.log_bins(0.3, 30.0, 10), 6000, seed=21)
+    job.update(step_cap=5000, formulation=energy)
+    with C.Engine(0) as e:
+        e.set_launch(1, precision, block=64, blocks_per_cu=1)
+        got = e.run(job, precision)[0]
+        lanes = e.timings()["grid_blocks"] * 64
+        p = e.passes()
+        assert 60_000 >= 2 * lanes
+        assert 0 < p["handed_over"] <= lanes and p["latency"] == (0, 0)
+        want = e.run_static(job, precision)[0]
+        assert e.passes()["handed_over"] == 0
+    _same(got, want)
+
+
+@pytest.mark.parametrize("explicit", [False, True])
+def test_served_slices_are_counted_by_kernel(explicit):
+    """One small request: every slice in the latency kernel, or none in a set
+    shape."""
+    job = _job(1, 3000)
+    with C.Engine(0) as e:
+        if explicit:
+            e.set_launch(1, "mixed")
+        t = e.submit(job, "mixed")
+        assert t.wait(60000) == C.OK
+        p = e.passes()
+        _same(t.result(), e.run(job, "mixed")[0])
+    assert p["slices"] > 0
+    assert p["latency_slices"] == (0 if explicit else p["slices"])
