@@ -334,14 +334,19 @@ cosmica_status cosmica_run_static(cosmica_ctx* ctx, const cosmica_job* jobs, int
                                   cosmica_precision precision, cosmica_result* results);
 
 /* Launch shape used for (model, precision).  Until one is set here or by the
- * tuner, the library picks it per pass: built-in values (256 threads, full
- * residency, 32-particle chunks, order 2), or, where the expected work says that
- * the longest path and not the throughput bounds the pass, a kernel for few
- * waves per SIMD.  Results are the same bit for bit. */
+ * tuner, the library picks it per pass: 256 threads, 32-particle chunks, order 2
+ * and full residency (4 workgroups per CU for the 3D model in mixed precision),
+ * or, where the expected work says that the longest path and not the throughput
+ * bounds the pass, a kernel for few waves per SIMD.  cosmica_get_launch then
+ * gives {256, 0, 32, 2}; setting those values, like any others, ends the
+ * library's choice and cosmica_reset_launch brings it back.  Results are the
+ * same bit for bit. */
 cosmica_status cosmica_set_launch(cosmica_ctx* ctx, cosmica_model model,
                                   cosmica_precision precision, const cosmica_launch* cfg);
 cosmica_status cosmica_get_launch(cosmica_ctx* ctx, cosmica_model model,
                                   cosmica_precision precision, cosmica_launch* cfg);
+cosmica_status cosmica_reset_launch(cosmica_ctx* ctx, cosmica_model model,
+                                    cosmica_precision precision);
 
 /* Times a calibration batch over candidate launch shapes and keeps the fastest
  * for (model, precision) (the paper's warps-per-block sweep, Sec. VI "Version 2",

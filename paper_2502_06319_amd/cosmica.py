@@ -156,6 +156,7 @@ _SIGS = {
                                           ctypes.POINTER(Launch)]),
     "cosmica_get_launch": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.c_int,
                                           ctypes.POINTER(Launch)]),
+    "cosmica_reset_launch": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.c_int]),
     "cosmica_tune": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.c_int,
                                     ctypes.c_char_p]),
     "cosmica_tune_jobs": (ctypes.c_int, [ctypes.c_void_p, ctypes.POINTER(Job), ctypes.c_int32,
@@ -450,6 +451,11 @@ class Engine:
         c = Launch(block, blocks_per_cu, chunk, order)
         _check(load().cosmica_set_launch(self.handle, model, PRECISION[precision], ctypes.byref(c)),
                "set_launch")
+
+    def reset_launch(self, model, precision):
+        """Leaves the launch to the library again, as in a new engine."""
+        _check(load().cosmica_reset_launch(self.handle, model, PRECISION[precision]),
+               "reset_launch")
 
     def get_launch(self, model, precision) -> dict:
         c = Launch()

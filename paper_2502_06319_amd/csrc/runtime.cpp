@@ -387,6 +387,9 @@ struct StaticHost {
 
 struct cosmica_plan;
 
+// 256 threads, full residency, longest expected paths first.
+static constexpr cosmica_launch kDefaultLaunch{256, 0, (int)kSpreadChunk, 2};
+
 // Particles that a pass hands from the throughput to the latency kernel (68 B
 // per lane of the largest grid: 22 MB in binary32).
 struct HandList {
@@ -1273,7 +1276,7 @@ cosmica_status cosmica_create(cosmica_ctx** out, int device, uint64_t hbm_budget
     HIP_TRY(hipEventCreateWithFlags(&ctx->up_ev, hipEventDisableTiming));
     HIP_TRY(hipEventCreateWithFlags(&ctx->scratch_ev, hipEventDisableTiming));
     for (int m = 0; m < 2; ++m)
-        for (int q = 0; q < 2; ++q) ctx->launch[m][q] = cosmica_launch{256, 0, (int)kSpreadChunk, 2};
+        for (int q = 0; q < 2; ++q) ctx->launch[m][q] = kDefaultLaunch;
     *out = ctx.release();
     return COSMICA_OK;
 }
@@ -2067,6 +2070,16 @@ cosmica_status cosmica_set_launch(cosmica_ctx* ctx, cosmica_model model,
     return COSMICA_OK;
 }
 
+cosmica_status cosmica_reset_launch(cosmica_ctx* ctx, cosmica_model model,
+                                    cosmica_precision precision)
+{
+    if (ctx == nullptr || (model != 0 && model != 1) || (precision != 0 && precision != 1))
+        return COSMICA_EINVAL;
+    ctx->launch[model][precision] = kDefaultLaunch;
+    ctx->auto_launch[model][precision] = true;
+    return COSMICA_OK;
+}
+
 cosmica_status cosmica_get_launch(cosmica_ctx* ctx, cosmica_model model,
                                   cosmica_precision precision, cosmica_launch* cfg)
 {
@@ -2383,7 +2396,7 @@ cosmica_status sweep(cosmica_ctx* ctx, const cosmica_job* jobs, int n_jobs, int 
     // paths kept out of the tail); the other orders are tried last.  Timings
     // of one shape vary by about 1% from run to run as the device warms, so
     // another shape replaces the best only when it is more than 1% faster.
-    cosmica_launch best{256, 0, (int)kSpreadChunk, 2};
+    cosmica_launch best = kDefaultLaunch;
     double best_rate = -1.0;
     auto consider = [&](const cosmica_launch& c) -> cosmica_status {
         if (!launch_ok(c)) return COSMICA_OK;

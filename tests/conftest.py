@@ -45,3 +45,15 @@ def eng():
 @pytest.fixture(scope="session")
 def othreads():
     return ORACLE_THREADS
+
+
+@pytest.fixture(autouse=True)
+def default_launch(request):
+    """After a test that used the shared context, its launches are the library's
+    choice again (a shape read and set back would stay set)."""
+    yield
+    if "eng" in request.fixturenames:
+        e = request.getfixturevalue("eng")
+        for model in (0, 1):
+            for precision in ("fp64", "mixed"):
+                e.reset_launch(model, precision)

@@ -82,3 +82,43 @@ def test_served_slices_are_counted_by_kernel(explicit):
         _same(t.result(), e.run(job, "mixed")[0])
     assert p["slices"] > 0
     assert p["latency_slices"] == (0 if explicit else p["slices"])
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_the_choice_of_the_launch_can_be_returned(precision):
+    """A shape read, changed and set back stays set; reset_launch returns to the
+    library's choice, for passes and served slices."""
+    job = _job(1, 2000, step_cap=300)
+    with C.Engine(0) as e:
+        want = e.run(job, precision)[0]
+        assert e.passes()["latency"] == (0, 1)
+        shape = e.get_launch(1, precision)
+        for block in (64, 256):
+            e.set_launch(1, precision, **dict(shape, block=block))
+            _same(e.run(job, precision)[0], want)
+            assert e.passes()["latency"] == (0, 0)
+        assert e.get_launch(1, precision) == shape
+        e.reset_launch(1, precision)
+        assert e.get_launch(1, precision) == shape
+        _same(e.run(job, precision)[0], want)
+        assert e.passes()["latency"] == (0, 1)
+        t = e.submit(job, precision)
+        assert t.wait(60000) in (C.OK, C.ESTEPCAP)
+        _same(t.result(), want)
+        p = e.passes()
+        assert p["latency_slices"] == p["slices"] > 0
+        for bad in ((2, 0), (0, 2), (-1, 0)):
+            assert C.load().cosmica_reset_launch(e.handle, *bad) == C.EINVAL
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_the_default_launch_changes_no_bit_of_a_mixed_batch(eng, precision):
+    """Both models in one batch, of several sizes, by default and in set shapes."""
+    jobs = [_job(1, 700, job_tag=1), _job(0, 65, job_tag=2), _job(1, 17 * WAVES, job_tag=3)]
+    want = eng.run(jobs, precision)
+    assert eng.passes()["latency"] == (1, 1)
+    for shape in ((256, 0, 32, 2), (64, 1, 1, 1), (128, 2, 1024, 0)):
+        for model in (0, 1):
+            eng.set_launch(model, precision, *shape)
+        for a, b in zip(eng.run(jobs, precision), want):
+            _same(a, b)
