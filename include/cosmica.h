@@ -333,14 +333,15 @@ void cosmica_plan_destroy(cosmica_plan* plan);
 cosmica_status cosmica_run_static(cosmica_ctx* ctx, const cosmica_job* jobs, int32_t n_jobs,
                                   cosmica_precision precision, cosmica_result* results);
 
-/* Launch shape used for (model, precision).  Until one is set here or by the
- * tuner, the library picks it per pass: 256 threads, 32-particle chunks, order 2
- * and full residency (4 workgroups per CU for the 3D model in mixed precision),
- * or, where the expected work says that the longest path and not the throughput
- * bounds the pass, a kernel for few waves per SIMD.  cosmica_get_launch then
- * gives {256, 0, 32, 2}; setting those values, like any others, ends the
- * library's choice and cosmica_reset_launch brings it back.  Results are the
- * same bit for bit. */
+/* Launch shape used for (model, precision).  Until one is set here, the library
+ * picks per pass and served slice: where the expected work says that the longest
+ * path and not the throughput bounds it, a kernel for few waves per SIMD; else
+ * the throughput kernel in the tuner's shape or, without one, 256 threads,
+ * 32-particle chunks, order 2 and full residency (4 workgroups per CU for the 3D
+ * model in mixed precision; cosmica_get_launch gives {256, 0, 32, 2}).  A shape
+ * set here, whatever its values, is used for every pass and slice, until
+ * cosmica_reset_launch brings the library's choice back (without a tuned
+ * shape).  Results are the same bit for bit. */
 cosmica_status cosmica_set_launch(cosmica_ctx* ctx, cosmica_model model,
                                   cosmica_precision precision, const cosmica_launch* cfg);
 cosmica_status cosmica_get_launch(cosmica_ctx* ctx, cosmica_model model,
@@ -348,8 +349,9 @@ cosmica_status cosmica_get_launch(cosmica_ctx* ctx, cosmica_model model,
 cosmica_status cosmica_reset_launch(cosmica_ctx* ctx, cosmica_model model,
                                     cosmica_precision precision);
 
-/* Times a calibration batch over candidate launch shapes and keeps the fastest
- * for (model, precision) (the paper's warps-per-block sweep, Sec. VI "Version 2",
+/* Times a calibration batch over candidate launch shapes of the throughput
+ * kernel and keeps the fastest for (model, precision), in place of a shape set
+ * before (the paper's warps-per-block sweep, Sec. VI "Version 2",
  * generalised).  cache_path, if not NULL, is read first (a hit skips the sweep)
  * and updated afterwards; the cache key includes the device architecture and
  * a digest of the kernel and runtime sources the library was built from.  A

@@ -387,6 +387,11 @@ struct StaticHost {
 
 struct cosmica_plan;
 
+// Who chose the launch shape of a (model, precision).  Unless a caller did, the
+// library picks the kernel from the work of each pass or slice: the tuner times
+// full batches, and its shape is the throughput kernel's.
+enum class LaunchBy { kDefault, kTuner, kCaller };
+
 // 256 threads, full residency, longest expected paths first.
 static constexpr cosmica_launch kDefaultLaunch{256, 0, (int)kSpreadChunk, 2};
 
@@ -416,9 +421,8 @@ struct cosmica_ctx {
     int wall_khz = 0;  // rate of the device's constant-rate clock [kHz]
     std::string arch;
     cosmica_launch launch[2][2];
-    // no caller and no tuner has chosen the launch shape: the library picks the
-    // kernel and the number of waves from the work of each pass
-    bool auto_launch[2][2] = {{true, true}, {true, true}};
+    LaunchBy launch_by[2][2] = {{LaunchBy::kDefault, LaunchBy::kDefault},
+                                {LaunchBy::kDefault, LaunchBy::kDefault}};
     cosmica_timings timings{};
     int32_t latency_ran[2] = {0, 0};  // last execution: the latency kernel took the model's particles
     bool handed = false;              // it handed particles over, and the list is still there
@@ -691,9 +695,11 @@ PassShape pass_shape(cosmica_ctx* ctx, int model, int prec, const PassWork& w, b
     const cosmica_launch& L = ctx->launch[model][prec];
     PassShape s;
     s.chunk = L.chunk;
-    if (!ctx->auto_launch[model][prec] || w.particles == 0) return s;
+    if (ctx->launch_by[model][prec] == LaunchBy::kCaller || w.particles == 0) return s;
+    // (the crossings above were measured against the lanes at full residency)
     const uint64_t lanes =
-        (uint64_t)grid_for(ctx, model, prec, L, ~0ull >> 8, shaped, energy, ukey) * (uint64_t)L.block;
+        (uint64_t)grid_for(ctx, model, prec, kDefaultLaunch, ~0ull >> 8, shaped, energy, ukey) *
+        (uint64_t)kDefaultLaunch.block;
     const double crossing = model == 1 ? (hand && w.long_paths() ? 2.0 : 10.0)
                                        : (prec == COSMICA_PREC_MIXED ? 6.0 : 20.0);
     if (w.steps >= crossing * (double)lanes * w.longest) return s;
@@ -1099,7 +1105,8 @@ int throughput_grid(cosmica_ctx* ctx, int model, int prec, const PassWork& w, bo
     // 4 waves per SIMD: a step of the longest paths takes less time than with 5
     // (batched mix, 12, 24 and 64 parameter sets: 634 and 617, 970 and 956, 2858
     // and 2807 ms with 5 and 4)
-    if (ctx->auto_launch[model][prec] && model == 1 && prec == COSMICA_PREC_MIXED)
+    if (ctx->launch_by[model][prec] == LaunchBy::kDefault && model == 1 &&
+        prec == COSMICA_PREC_MIXED)
         L.blocks_per_cu = 4;
     return grid_for(ctx, model, prec, L, w.particles, shaped, energy, ukey);
 }
@@ -1142,8 +1149,9 @@ cosmica_status execute_prop(cosmica_ctx* ctx, const PassDev& d)
         a.key_lo = (uint32_t)(d.key & 0xffffffffu);
         a.key_hi = (uint32_t)(d.key >> 32);
         int grid = 0, block = L.block;
-        if (d.shape[model].latency && ctx->auto_launch[model][d.prec]) {
+        if (d.shape[model].latency && ctx->launch_by[model][d.prec] != LaunchBy::kCaller) {
             const PassShape& f = d.shape[model];
+            block = kDefaultLaunch.block;
             a.latency = 1u;
             a.lane_cap = f.lane_cap;
             const uint64_t per_block = (uint64_t)f.lane_cap * (uint64_t)block / 64;
@@ -2066,7 +2074,7 @@ cosmica_status cosmica_set_launch(cosmica_ctx* ctx, cosmica_model model,
         (precision != 0 && precision != 1) || !launch_ok(*cfg))
         return COSMICA_EINVAL;
     ctx->launch[model][precision] = *cfg;
-    ctx->auto_launch[model][precision] = false;
+    ctx->launch_by[model][precision] = LaunchBy::kCaller;
     return COSMICA_OK;
 }
 
@@ -2076,7 +2084,7 @@ cosmica_status cosmica_reset_launch(cosmica_ctx* ctx, cosmica_model model,
     if (ctx == nullptr || (model != 0 && model != 1) || (precision != 0 && precision != 1))
         return COSMICA_EINVAL;
     ctx->launch[model][precision] = kDefaultLaunch;
-    ctx->auto_launch[model][precision] = true;
+    ctx->launch_by[model][precision] = LaunchBy::kDefault;
     return COSMICA_OK;
 }
 
@@ -2368,7 +2376,7 @@ cosmica_status time_shape(cosmica_ctx* ctx, const cosmica_job* jobs, int n_jobs,
                           int precision, const cosmica_launch& c, double* rate)
 {
     ctx->launch[model][precision] = c;
-    ctx->auto_launch[model][precision] = false;
+    ctx->launch_by[model][precision] = LaunchBy::kCaller;  // this shape, also for a small batch
     cosmica_plan* p = nullptr;
     cosmica_status st = cosmica_plan_create(ctx, jobs, n_jobs, (cosmica_precision)precision, 0, &p);
     if (st != COSMICA_OK) return st;
@@ -2391,7 +2399,7 @@ cosmica_status sweep(cosmica_ctx* ctx, const cosmica_job* jobs, int n_jobs, int 
 {
     const std::string key = tune_key(ctx, model, precision);
     const cosmica_launch saved = ctx->launch[model][precision];
-    const bool saved_auto = ctx->auto_launch[model][precision];
+    const LaunchBy saved_by = ctx->launch_by[model][precision];
     // Start from full residency, 32-particle chunks and queue order 2 (long
     // paths kept out of the tail); the other orders are tried last.  Timings
     // of one shape vary by about 1% from run to run as the device warms, so
@@ -2446,10 +2454,11 @@ cosmica_status sweep(cosmica_ctx* ctx, const cosmica_job* jobs, int n_jobs, int 
     }
     if (st != COSMICA_OK) {
         ctx->launch[model][precision] = saved;
-        ctx->auto_launch[model][precision] = saved_auto;
+        ctx->launch_by[model][precision] = saved_by;
         return st;
     }
     ctx->launch[model][precision] = best;
+    ctx->launch_by[model][precision] = LaunchBy::kTuner;
     cache_store(cache_path, key, best, best_rate);
     return COSMICA_OK;
 }
@@ -2464,7 +2473,7 @@ extern "C" cosmica_status cosmica_tune(cosmica_ctx* ctx, cosmica_model model,
     cosmica_launch L;
     if (cache_lookup(cache_path, tune_key(ctx, model, precision), &L)) {
         ctx->launch[model][precision] = L;
-        ctx->auto_launch[model][precision] = false;
+        ctx->launch_by[model][precision] = LaunchBy::kTuner;
         return COSMICA_OK;
     }
     HIP_TRY(hipSetDevice(ctx->device));
@@ -2492,7 +2501,7 @@ extern "C" cosmica_status cosmica_tune_jobs(cosmica_ctx* ctx, const cosmica_job*
     cosmica_launch L;
     if (cache_lookup(cache_path, tune_key(ctx, model, precision), &L)) {
         ctx->launch[model][precision] = L;
-        ctx->auto_launch[model][precision] = false;
+        ctx->launch_by[model][precision] = LaunchBy::kTuner;
         return COSMICA_OK;
     }
     HIP_TRY(hipSetDevice(ctx->device));
@@ -2996,7 +3005,7 @@ cosmica_status admit(cosmica_ctx* ctx)
         // (small requests in smaller chunks, so that slices of the latency kernel
         // can spread them over its waves)
         int chunk = L.chunk;
-        if (ctx->auto_launch[q->model][q->prec])
+        if (ctx->launch_by[q->model][q->prec] != LaunchBy::kCaller)
             chunk = (int)std::min<uint64_t>(
                 (uint64_t)chunk, std::max<uint64_t>(1, q->job.total / ((uint64_t)ctx->num_cus * 4)));
         std::vector<ChunkDev> chunks;
@@ -3055,7 +3064,7 @@ cosmica_status launch_slice(ServeGroup* g)
     // lanes than the previous slice parked particles: the closing kernel
     // carries what no wave claimed over to the next slice.
     int grid = g->grid_var[(a.shaped ? 1 : 0) | (a.energy ? 2 : 0)];
-    if (ctx->auto_launch[g->model][g->prec]) {
+    if (ctx->launch_by[g->model][g->prec] != LaunchBy::kCaller) {
         // Slices run the latency kernel while every particle left finds a lane of
         // it: at most what was parked or left over after the last slice read, and
         // the queue.

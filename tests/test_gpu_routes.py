@@ -122,3 +122,47 @@ def test_the_default_launch_changes_no_bit_of_a_mixed_batch(eng, precision):
             eng.set_launch(model, precision, *shape)
         for a, b in zip(eng.run(jobs, precision), want):
             _same(a, b)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("block,per_cu,chunk", [(256, 4, 32), (128, 2, 1024), (64, 1, 1)])
+def test_a_tuned_context_picks_the_kernel_too(tmp_path, precision, block, per_cu, chunk):
+    """The tuner's shape (from its cache here) is the throughput kernel's: small
+    passes and served slices run the latency kernel as without it, large ones
+    the tuned shape, all with the bits of a context that was not tuned."""
+    small = _job(1, 2000, step_cap=300)
+    large = _job(1, 6_000_000, step_cap=20)
+    cache = tmp_path / "tuned.txt"
+    with C.Engine(0) as e:
+        want, want_large = e.run(small, precision)[0], e.run(large, precision)[0]
+        assert e.passes()["latency"] == (0, 0)
+    key = next(l.split()[0] for l in open(_cache_of(tmp_path)))
+    cache.write_text("%s 1 %d %d %d %d 2 1e10\n" % (key, C.PRECISION[precision], block, per_cu, chunk))
+    with C.Engine(0) as e:
+        cfg = e.tune(1, precision, str(cache))
+        assert cfg == {"block": block, "blocks_per_cu": per_cu, "chunk": chunk, "order": 2}
+        _same(e.run(small, precision)[0], want)
+        assert e.passes()["latency"] == (0, 1) and e.timings()["block"] == 256
+        _same(e.run_static(small, precision)[0], want)
+        assert e.passes()["latency"] == (0, 1)
+        _same(e.run(large, precision)[0], want_large)
+        assert e.passes()["latency"] == (0, 0)
+        assert e.timings()["block"] == block
+        assert e.timings()["grid_blocks"] * block <= 64 * WAVES * per_cu
+        if chunk <= 32:
+            t = e.submit(small, precision)
+            assert t.wait(60000) in (C.OK, C.ESTEPCAP)
+            _same(t.result(), want)
+            p = e.passes()
+            assert p["latency_slices"] == p["slices"] > 0
+        e.set_launch(1, precision, **cfg)  # a caller's shape is used for all
+        _same(e.run(small, precision)[0], want)
+        assert e.passes()["latency"] == (0, 0)
+
+
+def _cache_of(tmp_path):
+    """A tuner cache that names this library's key (a sweep of the radial model)."""
+    path = tmp_path / "key.txt"
+    with C.Engine(0) as e:
+        e.tune(0, "mixed", str(path))
+    return path
