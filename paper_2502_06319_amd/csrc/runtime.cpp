@@ -393,7 +393,7 @@ struct cosmica_plan;
 enum class LaunchBy { kDefault, kTuner, kCaller };
 
 // 256 threads, full residency, longest expected paths first.
-static constexpr cosmica_launch kDefaultLaunch{256, 0, (int)kSpreadChunk, 2};
+static constexpr cosmica_launch kDefaultLaunch{256, 0, 32, 2};
 
 // Particles that a pass hands from the throughput to the latency kernel (68 B
 // per lane of the largest grid: 22 MB in binary32).
@@ -2538,7 +2538,9 @@ struct Req {
     int slot = -1;
     uint64_t ex0 = 0;
     uint32_t parts = 0;         // of its reduction
-    uint64_t ring_end = 0;      // queue position just past the request's last chunk
+    uint64_t ring_begin = 0;    // queue positions of the request's first chunk and
+    uint64_t ring_end = 0;      //   just past its last
+    uint64_t chunk = 1;         // particles of its chunks, at most
     uint64_t first_slice = 0;   // first slice of its group that can hold its particles
     uint64_t cancel_slice = 0;  // first slice of its group that sees its cancel flag
     // reduced results on their way to the host, and the event that ends the copy
@@ -3016,6 +3018,8 @@ cosmica_status admit(cosmica_ctx* ctx)
         // enqueued so far, before the request's first one)
         HIP_TRY(launch_fill_u32(g->ctl_d + ServeGroup::kCtlDone + q->slot, 0u, 1, s));
         HIP_TRY(launch_fill_u32(g->cancel_d + q->slot, 0u, 1, s));
+        q->ring_begin = g->q_tail;
+        q->chunk = (uint64_t)std::max(1, chunk);
         if ((st = ring_append(g, chunks)) != COSMICA_OK) return st;
         q->ring_end = g->q_tail;
         q->first_slice = g->seq;
@@ -3031,7 +3035,6 @@ template <typename R>
 cosmica_status launch_slice(ServeGroup* g)
 {
     cosmica_ctx* ctx = g->ctx;
-    const cosmica_launch& L = ctx->launch[g->model][g->prec];
     hipStream_t s = ctx->serve_stream;
     const int p = (int)(g->seq & 1u), o = p ^ 1;
     uint32_t* c = g->ctl_d;
@@ -3071,15 +3074,23 @@ cosmica_status launch_slice(ServeGroup* g)
         // Bursts with the throughput kernel alone and so: 8 requests (5.7e10
         // steps) 433 and 405 ms, 1 (1.2e10) 148 and 129 ms, 4 small ones (1.9e9)
         // 98 and 68 ms, 3 small ones in binary64 (4.8e8) 408 and 268 ms.
-        const uint64_t queued = g->q_tail - g->q_head;
-        const uint64_t left = g->in_flight + (queued + g->remainders) * (uint64_t)L.chunk;
+        // (a queued chunk holds at most its request's chunk size)
+        uint64_t queued = 0, chunk = 1;
+        for (const std::vector<Req*>* of : {&g->resident, &g->releasing})
+            for (const Req* q : *of) {
+                chunk = std::max(chunk, q->chunk);
+                const uint64_t from = std::max(g->q_head, q->ring_begin);
+                if (from < q->ring_end)
+                    queued += std::min<uint64_t>(q->job.total, (q->ring_end - from) * q->chunk);
+            }
+        const uint64_t left = g->in_flight + queued + g->remainders * chunk;
         const uint64_t simd_waves = (uint64_t)ctx->num_cus * 4;
         const uint64_t most = g->model == 1 && g->prec == COSMICA_PREC_FP64 ? 1 : 2;
         if (left <= most * simd_waves * 64) {
             const uint64_t bpc = left <= simd_waves * 64 ? 1 : most;
             const uint64_t waves = simd_waves * bpc;
             a.latency = 1u;
-            a.lane_cap = queued == 0 ? 0u
+            a.lane_cap = queued == 0 ? spread_lanes((uint32_t)std::min<uint64_t>(chunk, ~0u))
                                      : (uint32_t)std::max<uint64_t>(1, (left + waves - 1) / waves);
             grid = std::min<int>(grid, (int)(waves * 64 / (uint64_t)g->block));
         }

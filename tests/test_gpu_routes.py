@@ -149,12 +149,11 @@ def test_a_tuned_context_picks_the_kernel_too(tmp_path, precision, block, per_cu
         assert e.passes()["latency"] == (0, 0)
         assert e.timings()["block"] == block
         assert e.timings()["grid_blocks"] * block <= 64 * WAVES * per_cu
-        if chunk <= 32:
-            t = e.submit(small, precision)
-            assert t.wait(60000) in (C.OK, C.ESTEPCAP)
-            _same(t.result(), want)
-            p = e.passes()
-            assert p["latency_slices"] == p["slices"] > 0
+        t = e.submit(small, precision)
+        assert t.wait(60000) in (C.OK, C.ESTEPCAP)
+        _same(t.result(), want)
+        p = e.passes()
+        assert p["latency_slices"] == p["slices"] > 0
         e.set_launch(1, precision, **cfg)  # a caller's shape is used for all
         _same(e.run(small, precision)[0], want)
         assert e.passes()["latency"] == (0, 0)
@@ -166,3 +165,20 @@ def _cache_of(tmp_path):
     with C.Engine(0) as e:
         e.tune(0, "mixed", str(path))
     return path
+
+
+def test_small_requests_together_run_the_latency_kernel(monkeypatch):
+    """Eight requests of 1,000 particles, cut to chunks of one: far fewer than
+    the 131,072 lanes up to which slices run the latency kernel; in slices that
+    park and resume many times."""
+    monkeypatch.setenv("COSMICA_SLICE_MS", "0.2")
+    jobs = [W.make_job(W.c2_helio(), W.species("p"), W.log_bins(0.3, 30.0, 20), 50, seed=3 + i,
+                       job_tag=i) for i in range(8)]
+    with C.Engine(0) as e:
+        tickets = [e.submit(j, "mixed") for j in jobs]
+        for t in tickets:
+            assert t.wait(60000) == C.OK
+        p = e.passes()
+        for j, t in zip(jobs, tickets):
+            _same(t.result(), e.run(j, "mixed")[0])
+    assert p["latency_slices"] == p["slices"] > 2
