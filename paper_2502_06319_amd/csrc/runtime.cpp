@@ -795,6 +795,13 @@ struct cosmica_plan {
     PassWork work[2];      // of the radial and the 3D particles
     PassShape shape[2];
     uint32_t n_chunks[2] = {0, 0};
+    // The queue of a plan laid out for the latency kernel has smaller chunks than
+    // the launch shape's; in a shape that a caller sets later the plan runs the
+    // throughput kernel, with a queue cut for it by the first such execution.
+    int launch_chunk[2] = {0, 0};  // chunk and order of the launch at creation
+    int launch_order[2] = {0, 0};
+    ChunkDev* coarse_d[2] = {nullptr, nullptr};
+    uint32_t n_coarse[2] = {0, 0};
     DevSet mem;
     void* jobs_d = nullptr;
     void* regions_d = nullptr;
@@ -1186,6 +1193,30 @@ cosmica_status execute_prop(cosmica_ctx* ctx, const PassDev& d)
     return COSMICA_OK;
 }
 
+// Cuts the queue described at cosmica_plan::coarse_d; without room for it the
+// plan keeps to the one it has.
+cosmica_status cut_coarse(cosmica_plan* p, int model)
+{
+    std::vector<uint32_t> ids;
+    std::vector<double> cost;
+    for (uint32_t i = 0; i < p->segs.size(); ++i) {
+        const JobCopy& j = p->jobs[p->segs[i].job];
+        cost.push_back(expected_steps(j.helio, j.species, p->segs[i].P0));
+        if (j.helio.model == model) ids.push_back(i);
+    }
+    std::vector<ChunkDev> ch;
+    make_chunks(p->segs, ids, p->launch_chunk[model], p->launch_order[model], &ch, &cost);
+    ChunkDev* d = nullptr;
+    if (p->mem.alloc(&d, ch.size(), true) != COSMICA_OK) return COSMICA_OK;
+    const size_t bytes = ch.size() * sizeof(ChunkDev);
+    const cosmica_status st =
+        upload_block(p->ctx, d, bytes, [&](unsigned char* h) { std::memcpy(h, ch.data(), bytes); });
+    if (st != COSMICA_OK) return st;
+    p->coarse_d[model] = d;
+    p->n_coarse[model] = (uint32_t)ch.size();
+    return COSMICA_OK;
+}
+
 PassDev pass_of(const cosmica_plan* p)
 {
     PassDev d;
@@ -1194,8 +1225,10 @@ PassDev pass_of(const cosmica_plan* p)
     d.orbit = p->orbit_d;
     d.segs = p->segs_d;
     for (int m = 0; m < 2; ++m) {
-        d.chunks[m] = p->chunks_d[m];
-        d.n_chunks[m] = p->n_chunks[m];
+        const bool coarse = p->coarse_d[m] != nullptr &&
+                            p->ctx->launch_by[m][p->prec] == LaunchBy::kCaller;
+        d.chunks[m] = coarse ? p->coarse_d[m] : p->chunks_d[m];
+        d.n_chunks[m] = coarse ? p->n_coarse[m] : p->n_chunks[m];
         d.work[m] = p->work[m];
         d.shape[m] = p->shape[m];
     }
@@ -1347,8 +1380,9 @@ static cosmica_status plan_create(cosmica_ctx* ctx, const cosmica_job* jobs, int
     for (int m = 0; m < 2; ++m) {
         p->shape[m] =
             pass_shape(ctx, m, precision, p->work[m], p->shaped, p->energy, p->uniform_key, true);
-        make_chunks(p->segs, ids[m], p->shape[m].chunk, ctx->launch[m][precision].order,
-                    &chunks[m], &cost);
+        p->launch_chunk[m] = ctx->launch[m][precision].chunk;
+        p->launch_order[m] = ctx->launch[m][precision].order;
+        make_chunks(p->segs, ids[m], p->shape[m].chunk, p->launch_order[m], &chunks[m], &cost);
         if (p->shape[m].latency || p->work[m].particles == 0) continue;
         const uint64_t lanes =
             (uint64_t)throughput_grid(ctx, m, precision, p->work[m], p->shaped, p->energy,
@@ -1413,6 +1447,13 @@ cosmica_status cosmica_plan_execute(cosmica_plan* p, const cosmica_bins_dev* out
     if (p == nullptr) return COSMICA_EINVAL;
     cosmica_ctx* ctx = p->ctx;
     HIP_TRY(hipSetDevice(ctx->device));
+    for (int m = 0; m < 2; ++m)
+        if (p->shape[m].latency && p->shape[m].chunk < p->launch_chunk[m] &&
+            p->coarse_d[m] == nullptr && ctx->launch_by[m][p->prec] == LaunchBy::kCaller &&
+            !capturing(ctx)) {
+            const cosmica_status st = cut_coarse(p, m);
+            if (st != COSMICA_OK) return st;
+        }
     HIP_TRY(hipEventRecord(ctx->ev[0], ctx->stream));
     HIP_TRY(launch_fill_u32(p->counters_d, 0u, 8, ctx->stream));
     std::lock_guard<std::recursive_mutex> lk(ctx->scratch_mu);

@@ -182,3 +182,28 @@ def test_small_requests_together_run_the_latency_kernel(monkeypatch):
         for j, t in zip(jobs, tickets):
             _same(t.result(), e.run(j, "mixed")[0])
     assert p["latency_slices"] == p["slices"] > 2
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_a_plan_laid_out_before_a_shape_is_set(precision):
+    """Its queue has chunks of one particle, for the latency kernel (0.36 ms in the
+    throughput kernel, 0.32 with chunks of 32): the first execution in a set
+    shape cuts one of 2 x 500 / 32 chunks of 16 B, once; back in the default
+    shape it runs the latency kernel.  Always the same bits."""
+    job = W.make_job(W.helio_1d(), W.species("p"), [2.0, 9.0], [500, 500])
+    with C.Engine(0) as e:
+        plan = e.plan(job, precision)
+        plan.execute()
+        want = plan.read()[0]
+        held = e.serve_stats()["bytes_in_use"]
+        e.set_launch(0, precision)
+        for _ in range(2):
+            plan.execute()
+            _same(plan.read()[0], want)
+            assert e.passes()["latency"] == (0, 0)
+            assert e.serve_stats()["bytes_in_use"] - held == 512
+        e.reset_launch(0, precision)
+        plan.execute()
+        _same(plan.read()[0], want)
+        assert e.passes()["latency"] == (1, 0)
+        plan.destroy()
