@@ -98,3 +98,22 @@ def test_radial_binary32_keeps_five_waves(kernels):
     assert len(k) == 2
     for name, (vgpr, _, occ) in k.items():
         assert occ >= 5, f"{name}: {vgpr} VGPRs, {occ} waves/SIMD"
+
+
+@pytest.mark.parametrize("real,model_3d,waves", [("f", False, 3), ("f", True, 2), ("d", False, 2),
+                                                 ("d", True, 1)])
+def test_latency_kernels_keep_the_waves_they_are_launched_with(kernels, real, model_3d, waves):
+    """pass_shape launches that many waves per SIMD where there are particles
+    for them."""
+    pat = re.compile(r"k_latencyI%sLb%dELb[01]ELb[01]ELb[01]E" % (real, int(model_3d)))
+    k = {n: v for n, v in kernels.items() if pat.search(n)}
+    assert len(k) == (8 if model_3d else 2)
+    for name, (vgpr, _, occ) in k.items():
+        assert occ >= waves, f"{name}: {vgpr} VGPRs, {occ} waves/SIMD"
+
+
+def test_reweighting_keeps_two_waves(kernels):
+    k = {n: v for n, v in kernels.items() if re.search(r"10k_reweightE", n)}
+    assert len(k) == 1
+    for name, (vgpr, _, occ) in k.items():
+        assert occ >= 2, f"{name}: {vgpr} VGPRs, {occ} waves/SIMD"
