@@ -2029,10 +2029,17 @@ cosmica_status run_static(cosmica_ctx* ctx, const cosmica_job* jobs, uint32_t n_
     r.exL = d.exL;
     r.seg_base = 0;
     r.out_base = 0;
-    // the parts' sums where the array has room past the work's buffers
+    // the parts' sums past the work's buffers or, in a full array, over the queue,
+    // which the propagation has emptied
     r.n_segs = n_bins;
-    r.n_parts = Lo.total + n_parts * kReducePartBytes <= COSMICA_STATIC_BYTES ? n_parts : 0u;
-    r.partial = at(Lo.total);
+    const size_t part_bytes = n_parts * kReducePartBytes;
+    r.n_parts = n_parts;
+    if (Lo.total + part_bytes <= COSMICA_STATIC_BYTES)
+        r.partial = at(Lo.total);
+    else if (part_bytes <= nc * sizeof(ChunkDev))
+        r.partial = at(Lo.chunks);
+    else
+        r.n_parts = 0;
     r.hist = (uint32_t*)at(Lo.hist);
     r.flux = (double*)at(Lo.flux);
     r.flux_se = (double*)at(Lo.se);

@@ -189,3 +189,29 @@ def test_reweighting_at_the_edges_of_its_parts(eng, counts):
                 w = np.exp(rows[l, 0] - g * (np.log(P) + 2.0)) * (P0 / P) ** 2
                 np.testing.assert_allclose(flux[l, b], w.mean(), rtol=1e-12)
                 np.testing.assert_allclose(se[l, b], w.std(ddof=1) / np.sqrt(len(P)), rtol=1e-12)
+
+
+def test_static_array_filled_to_its_limit(eng):
+    """The largest bin that cosmica_run_static takes (to 64 exits) is spread
+    over workgroups too, in about the time of a plan's reduction and with the
+    same bits."""
+    job = W.make_job(W.helio_1d(), W.species("p"), [2.0], [1])
+    job["step_cap"] = 40
+    lo, hi = 6_000_000, 7_000_000
+    while hi - lo > 64:
+        n = (lo + hi) // 2
+        try:
+            got = eng.run_static(dict(job, particles_per_bin=[n]), "mixed")[0]
+            lo = n
+        except C.CosmicaError as err:
+            assert err.status == C.ESCRATCH
+            hi = n
+    job["particles_per_bin"] = [lo]
+    ms = []
+    for _ in range(4):
+        got = eng.run_static(job, "mixed")[0]
+        ms.append(eng.timings()["reduce_ms"])
+    want = eng.run(job, "mixed")[0]
+    for k in want:
+        np.testing.assert_array_equal(got[k], want[k], err_msg=k)
+    assert min(ms) < 1.5 * _reduce_ms(eng, job) + 0.05
