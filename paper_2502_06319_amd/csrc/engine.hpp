@@ -115,6 +115,9 @@ struct SliceDev {
     uint32_t left_cap;            // entries of leftover
 };
 
+// Refill chunk of the default launch shape.
+constexpr uint32_t kSpreadChunk = 32;
+
 template <typename R>
 struct PropArgs {
     const JobDev<R>* jobs;
@@ -143,14 +146,10 @@ struct PropArgs {
     uint32_t key_lo, key_hi;
     uint32_t hand_over;           // 1: park a wave's particles once the queue is empty
     uint32_t latency;             // 1: run the kernel for few particles per SIMD
-    // lanes a wave of that kernel fills: 1..64, or spread_lanes(c): what the last
-    // slice left, spread evenly, its chunk remainders counted as c particles each
-    uint32_t lane_cap;
+    uint32_t lane_cap;            // lanes a wave of that kernel fills (1..64; 0: see k_latency)
     const uint32_t* job_cancel;   // optional per-job cancel flags
     uint32_t* job_done;           // optional per-job count of finished particles
 };
-
-constexpr uint32_t spread_lanes(uint32_t c) { return (c < 65536u ? c : 65536u) << 8; }
 
 // End of a serving slice (one workgroup, after the propagation kernel):
 // resume entries and chunk remainders of the previous slice that no wave

@@ -823,14 +823,15 @@ __device__ __forceinline__ void propagate(const PropArgs<R>& a)
     bool queue_open = true;
     bool launch_open = true;  // false once this wave used its step budget
 
-    // Lanes this wave may still fill (spread_lanes: a slice with an empty queue).
+    // Lanes this wave may still fill.  lane_cap = 0 (a slice with an empty queue):
+    // what the previous slice left, spread evenly.
     uint32_t lane_cap = 64u;
     if constexpr (TAIL) {
         lane_cap = a.lane_cap;
-        if (lane_cap > 64u) {
+        if (lane_cap == 0u) {
             const uint32_t waves = gridDim.x * (blockDim.x >> 6);
             const uint32_t n = min(*sv->n_resume, sv->park_cap) +
-                               (lane_cap >> 8) * min(*sv->n_left_in, sv->left_cap);
+                               kSpreadChunk * min(*sv->n_left_in, sv->left_cap);
             lane_cap = wave_uniform(min(64u, max(1u, (n + waves - 1u) / waves)));
         }
     }

@@ -393,7 +393,7 @@ struct cosmica_plan;
 enum class LaunchBy { kDefault, kTuner, kCaller };
 
 // 256 threads, full residency, longest expected paths first.
-static constexpr cosmica_launch kDefaultLaunch{256, 0, 32, 2};
+static constexpr cosmica_launch kDefaultLaunch{256, 0, (int)kSpreadChunk, 2};
 
 // Particles that a pass hands from the throughput to the latency kernel (68 B
 // per lane of the largest grid: 22 MB in binary32).
@@ -3138,8 +3138,11 @@ cosmica_status launch_slice(ServeGroup* g)
             const uint64_t bpc = left <= simd_waves * 64 ? 1 : most;
             const uint64_t waves = simd_waves * bpc;
             a.latency = 1u;
-            a.lane_cap = queued == 0 ? spread_lanes((uint32_t)std::min<uint64_t>(chunk, ~0u))
-                                     : (uint32_t)std::max<uint64_t>(1, (left + waves - 1) / waves);
+            // (no chunk remainders after the last slice read and none queued: the
+            // particles parked since are all there is, and the waves count them)
+            a.lane_cap = queued == 0 && g->remainders == 0
+                             ? 0u
+                             : (uint32_t)std::max<uint64_t>(1, (left + waves - 1) / waves);
             grid = std::min<int>(grid, (int)(waves * 64 / (uint64_t)g->block));
         }
     }
