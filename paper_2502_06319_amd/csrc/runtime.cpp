@@ -425,7 +425,7 @@ struct cosmica_ctx {
                                 {LaunchBy::kDefault, LaunchBy::kDefault}};
     cosmica_timings timings{};
     int32_t latency_ran[2] = {0, 0};  // last execution: the latency kernel took the model's particles
-    bool handed = false;              // it handed particles over, and the list is still there
+    std::atomic<bool> handed{false};  // it handed particles over, and the list is still there
     std::atomic<uint64_t> slices{0}, latency_slices{0};
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     // steps of the last execution: device array and its length
@@ -1504,7 +1504,7 @@ cosmica_status cosmica_plan_execute(cosmica_plan* p, const cosmica_bins_dev* out
         HIP_TRY(hipMemcpyAsync(p->steps, r.steps, p->segs.size() * 8, hipMemcpyDeviceToDevice,
                                ctx->stream));
     HIP_TRY(hipEventRecord(ctx->ev[2], ctx->stream));
-    if (ctx->scratch_open) {
+    if (ctx->scratch_open && !capturing(ctx)) {
         HIP_TRY(hipEventRecord(ctx->scratch_ev, ctx->stream));
         ctx->scratch_open = false;
     }
@@ -2161,12 +2161,11 @@ cosmica_status cosmica_get_passes(cosmica_ctx* ctx, cosmica_passes* out)
     if (ctx == nullptr || out == nullptr) return COSMICA_EINVAL;
     HIP_TRY(hipSetDevice(ctx->device));
     uint32_t n = 0;
-    {
+    if (ctx->handed) {
+        HIP_TRY(hipEventSynchronize(ctx->scratch_ev));
         std::lock_guard<std::recursive_mutex> lk(ctx->scratch_mu);
-        if (ctx->handed) {
-            HIP_TRY(hipEventSynchronize(ctx->scratch_ev));
+        if (ctx->handed)
             HIP_TRY(hipMemcpy(&n, ctx->hand.ctl, sizeof(n), hipMemcpyDeviceToHost));
-        }
     }
     std::memset(out, 0, sizeof(*out));
     for (int m = 0; m < 2; ++m) out->latency[m] = ctx->latency_ran[m];
