@@ -1656,7 +1656,8 @@ static void split_bins(const cosmica_plan* p, uint32_t groups, uint32_t least, u
     if ((uint64_t)p->segs.size() * groups >= want && largest <= most) return;
     uint64_t c = p->total_particles * groups / want;
     c = std::max<uint64_t>({c, least, (largest + 63) / 64});
-    c = (std::min<uint64_t>(c, most) + 255) / 256 * 256;
+    c = std::max<uint64_t>(std::min<uint64_t>(c, most), (largest + 65534) / 65535);  // grid limit
+    c = (c + 255) / 256 * 256;
     if (largest <= c) return;
     *part = (uint32_t)c;
     *parts = (uint32_t)((largest + c - 1) / c);
