@@ -235,7 +235,9 @@ cosmica_status cosmica_validate_job(const cosmica_job* job);
  * memory the context may hold (0 = 90% of the device's free memory).  Device
  * blocks freed by finished runs and plans stay with the context (up to a
  * quarter of the budget) for reuse by allocations of the same size, and are
- * given back first when an allocation would exceed the budget.
+ * given back first when an allocation would exceed the budget; next goes the
+ * scratch that batch passes can do without (particles handed between kernels,
+ * partial sums of reductions), once the passes that use it have ended.
  * hip_stream: a hipStream_t to run on, or NULL for a stream the context owns.
  * *out receives the handle (NULL on error). */
 cosmica_status cosmica_create(cosmica_ctx** out, int device, uint64_t hbm_budget_bytes,
@@ -286,7 +288,7 @@ cosmica_status cosmica_plan_info(const cosmica_plan* plan, uint64_t* total_bins,
  * 1..COSMICA_MAX_REWEIGHT, n_knots outside 2..COSMICA_MAX_LIS_KNOTS, dlnP <= 0
  * or a table value is not finite.  Blocking; it holds n_lis * (n_knots + 2 *
  * total_bins) doubles of device memory for the call (ENOMEM beyond the
- * context's budget). */
+ * context's budget), and partial sums of large bins where there is room. */
 #define COSMICA_MAX_REWEIGHT 4096
 #define COSMICA_MAX_LIS_KNOTS 256
 cosmica_status cosmica_plan_reweight(cosmica_plan* plan, uint32_t n_lis, uint32_t n_knots,

@@ -1550,7 +1550,8 @@ __device__ __forceinline__ uint32_t segment_of_part(const ReduceArgs& a, uint32_
 // A part's weights stay in registers, four a thread: their mean first, then
 // the deviations from it, one power per exit and no cancellation whatever the
 // weights.  Bound by FP64 VALU and latency.  31 bins of 3,001 to 20,011 exits:
-// 23 us, of which the launches take 10; one bin of 2,000,000: 82 us (0.5 TB/s).
+// 27 us with sums about the bin's first weight, 23 us so (clear 4, parts 13, sum
+// 5); one bin of 2,000,000: 229 and 82 us (0.5 TB/s).
 template <bool SPLIT>
 __global__ void __launch_bounds__(kReduceBlock) k_reduce(const ReduceArgs a)
 {
@@ -1709,11 +1710,12 @@ hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s)
 // mean of all.
 // Segments are split over workgroups where segments and groups alone would
 // leave CUs idle.  64 spectra x 516,000 exits of 30 bins: 521 us with two passes
-// of the library's exp in 120 workgroups, 73 us so.
+// of the library's exp in 120 workgroups, 72 us so.
 // ---------------------------------------------------------------------------
 // e^x = 2^k e^r, k = round(x / ln 2), the Taylor series of e^r to r^13 (|r| <=
 // ln(2)/2: the next term is below 2^-57).  For |x| < 2^30; ldexp saturates to 0
-// and infinity.
+// and infinity.  At most 0.874 ulp off and 0.301 rms over |x| <= 700; the
+// library's exp 0.872 and 0.302.
 __device__ __forceinline__ double exp_taylor(double x)
 {
     const double k = __builtin_rint(x * 1.4426950408889634);
