@@ -462,8 +462,12 @@ struct cosmica_ctx {
     HandList hand;
     std::vector<cosmica_plan*> lenders;
     std::atomic<uint64_t> scratch_bytes{0};  // of all of it; counted in in_use
-    hipEvent_t scratch_ev = nullptr;  // the end of the last pass that used some (never captured)
-    bool scratch_open = false;        // launches use it that the event does not cover yet
+    // Each pass that used some ends with a store of its number to pinned memory:
+    // a wait for it needs no call on the stream, which may be under capture.
+    uint32_t* scratch_done = nullptr;      // (within `up`)
+    uint32_t* scratch_done_dev = nullptr;  // its device address
+    uint32_t scratch_pass = 0;             // number of the last such pass
+    bool scratch_open = false;             // launches use it that no number covers yet
     cosmica_ctx() = default;
     ~cosmica_ctx();  // defined once the serving types are complete
 };
@@ -843,18 +847,49 @@ struct cosmica_plan {
 
 namespace {
 
+// Whether the context's stream is under capture (or cannot be asked).
+bool capturing(cosmica_ctx* ctx)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return cap != hipStreamCaptureStatusNone;
+}
+
+// Waits until pass `number` has stored its number; false if the stream failed.
+bool scratch_wait(cosmica_ctx* ctx, uint32_t number)
+{
+    for (uint64_t polls = 1;; ++polls) {
+        const uint32_t done = __atomic_load_n(ctx->scratch_done, __ATOMIC_ACQUIRE);
+        if ((int32_t)(done - number) >= 0) return true;
+        if (polls % 16384 == 0 && !capturing(ctx)) {  // about once a second: does it still run?
+            const hipError_t e = hipStreamQuery(ctx->stream);
+            if (e == hipErrorNotReady) {
+                (void)hipGetLastError();
+            } else {
+                const uint32_t now = __atomic_load_n(ctx->scratch_done, __ATOMIC_ACQUIRE);
+                return (int32_t)(now - number) >= 0;
+            }
+        }
+        std::this_thread::sleep_for(std::chrono::microseconds(50));
+    }
+}
+
 // Takes the context's scratch back for an allocation that needs the room, on
 // whichever thread that runs: no pass finds it from here on, and those enqueued
-// with it are waited for, by an event of their own and without the lock, so
-// that neither later passes nor a capture of the stream are held up.
+// with it are waited for, without the lock and without a call on their stream,
+// so that neither later passes nor a capture of it are held up.
 void scratch_release(cosmica_ctx* ctx)
 {
     HandList hand;
     std::vector<std::pair<cosmica_plan*, unsigned char*>> parts;
     std::vector<size_t> bytes;
-    bool open = false;
+    uint32_t last = 0;
     {
         std::lock_guard<std::recursive_mutex> lk(ctx->scratch_mu);
+        if (ctx->scratch_open) return;  // a pass failed between its launches
         std::swap(hand, ctx->hand);
         ctx->handed = false;
         for (cosmica_plan* p : ctx->lenders) {
@@ -863,13 +898,10 @@ void scratch_release(cosmica_ctx* ctx)
             bytes.push_back(p->partial_bytes);
             p->reduce_partial = nullptr;
         }
-        open = ctx->scratch_open;
+        last = ctx->scratch_pass;
     }
     if (hand.block == nullptr && parts.empty()) return;
-    const hipError_t e =
-        open ? hipStreamSynchronize(ctx->stream) : hipEventSynchronize(ctx->scratch_ev);
-    if (e != hipSuccess) {  // it may be in use: it stays where it was
-        (void)hipGetLastError();
+    if (!scratch_wait(ctx, last)) {  // it may be in use: it stays where it was
         std::lock_guard<std::recursive_mutex> lk(ctx->scratch_mu);
         if (ctx->hand.block == nullptr) std::swap(hand, ctx->hand);
         for (auto& q : parts)
@@ -1079,17 +1111,6 @@ bool hand_ready(cosmica_ctx* ctx, uint32_t lanes)
     }
     ctx->hand = h;
     return true;
-}
-
-// Whether the context's stream is under capture (or cannot be asked).
-bool capturing(cosmica_ctx* ctx)
-{
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) {
-        (void)hipGetLastError();
-        return true;
-    }
-    return cap != hipStreamCaptureStatusNone;
 }
 
 // Whether a pass in the throughput kernel ends in the latency kernel: the waves
@@ -1312,10 +1333,12 @@ cosmica_status cosmica_create(cosmica_ctx** out, int device, uint64_t hbm_budget
         ctx->own_stream = true;
     }
     for (int i = 0; i < 4; ++i) HIP_TRY(hipEventCreate(&ctx->ev[i]));
-    HIP_TRY(hipHostMalloc((void**)&ctx->up, cosmica_ctx::kUpBytes, hipHostMallocDefault));
+    HIP_TRY(hipHostMalloc((void**)&ctx->up, cosmica_ctx::kUpBytes + 256, hipHostMallocDefault));
     HIP_TRY(hipHostMalloc((void**)&ctx->down, cosmica_ctx::kDownBytes, hipHostMallocDefault));
     HIP_TRY(hipEventCreateWithFlags(&ctx->up_ev, hipEventDisableTiming));
-    HIP_TRY(hipEventCreateWithFlags(&ctx->scratch_ev, hipEventDisableTiming));
+    ctx->scratch_done = (uint32_t*)(ctx->up + cosmica_ctx::kUpBytes);
+    *ctx->scratch_done = 0u;
+    HIP_TRY(hipHostGetDevicePointer((void**)&ctx->scratch_done_dev, ctx->scratch_done, 0));
     for (int m = 0; m < 2; ++m)
         for (int q = 0; q < 2; ++q) ctx->launch[m][q] = kDefaultLaunch;
     *out = ctx.release();
@@ -1505,7 +1528,8 @@ cosmica_status cosmica_plan_execute(cosmica_plan* p, const cosmica_bins_dev* out
                                ctx->stream));
     HIP_TRY(hipEventRecord(ctx->ev[2], ctx->stream));
     if (ctx->scratch_open && !capturing(ctx)) {
-        HIP_TRY(hipEventRecord(ctx->scratch_ev, ctx->stream));
+        HIP_TRY(launch_fill_u32(ctx->scratch_done_dev, ctx->scratch_pass + 1u, 1, ctx->stream));
+        ++ctx->scratch_pass;
         ctx->scratch_open = false;
     }
     p->executed = true;
@@ -2163,7 +2187,7 @@ cosmica_status cosmica_get_passes(cosmica_ctx* ctx, cosmica_passes* out)
     HIP_TRY(hipSetDevice(ctx->device));
     uint32_t n = 0;
     if (ctx->handed) {
-        HIP_TRY(hipEventSynchronize(ctx->scratch_ev));
+        HIP_TRY(hipEventSynchronize(ctx->ev[2]));
         std::lock_guard<std::recursive_mutex> lk(ctx->scratch_mu);
         if (ctx->handed)
             HIP_TRY(hipMemcpy(&n, ctx->hand.ctl, sizeof(n), hipMemcpyDeviceToHost));
@@ -3564,7 +3588,6 @@ void cosmica_destroy(cosmica_ctx* ctx)
     for (int i = 0; i < 4; ++i)
         if (ctx->ev[i]) (void)hipEventDestroy(ctx->ev[i]);
     if (ctx->up_ev) (void)hipEventDestroy(ctx->up_ev);
-    if (ctx->scratch_ev) (void)hipEventDestroy(ctx->scratch_ev);
     if (ctx->up) (void)hipHostFree(ctx->up);
     if (ctx->down) (void)hipHostFree(ctx->down);
     if (ctx->hand.block) (void)hipFree(ctx->hand.block);  // (its last pass has ended)

@@ -230,3 +230,84 @@ def test_a_new_plan_has_its_tables_on_the_device():
                          timeout=100)
     assert out.returncode == 0, out.stderr[-2000:]
     assert "upload-ok" in out.stdout
+
+
+SERVE_CHILD = r"""
+import os, sys, numpy as np
+os.environ["COSMICA_SERVE_POOL"] = str(64 << 20)
+import torch
+sys.path.insert(0, sys.argv[1])
+from paper_2502_06319_amd import cosmica as C, workloads as W
+captured = sys.argv[2] == "1"
+sheet = dict(W.make_job(W.c2_helio(), W.species("e-"), W.log_bins(0.3, 30.0, 10), 60000, seed=21),
+             step_cap=20)
+radial = W.make_job(W.helio_1d(), W.species("p"), [2.0, 5.0], [500, 300], seed=7)
+first = W.c2_job(200, n_bins=3)      # before the capture: the group's set-up is not for one
+served = dict(first, formulation=1)
+
+def opened(budget, stream):
+    e = C.Engine(0, hbm_budget_bytes=budget, stream=stream)
+    e.set_launch(1, "mixed", block=256, blocks_per_cu=4)
+    return e, e.plan(sheet, "mixed"), e.plan(radial, "mixed")
+
+stream = torch.cuda.Stream()
+e, p, q = opened(0, stream)
+p.execute()
+p.read()
+q.execute()
+want = q.read()[0]
+for job in (first, served):
+    t = e.submit(job, "mixed")
+    assert t.wait(60000) == C.OK
+want_t = t.result()
+held = e.serve_stats()["bytes_in_use"]
+p.destroy(); q.destroy(); e.close()
+
+# 8 MB short of all of it: the energy form's records need the list's 17 MB
+e, p, q = opened(held - (8 << 20), stream)
+t = e.submit(first, "mixed")
+assert t.wait(60000) == C.OK
+p.execute()
+p.read()
+out = {k: torch.zeros(2, dtype=torch.float64, device="cuda:0") for k in ("flux", "flux_se")}
+torch.cuda.synchronize()
+status = []
+def serve():
+    t = e.submit(served, "mixed")
+    status.append(t.wait(60000))
+    return t
+if captured:
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream, capture_error_mode="relaxed"):
+        q.execute(out)
+        t = serve()
+    with torch.cuda.stream(stream):
+        g.replay()
+else:
+    t = serve()
+    q.execute(out)
+stream.synchronize()
+got = {k: v.cpu().numpy() for k, v in out.items()}
+res, now = t.result(), e.serve_stats()["bytes_in_use"]
+p.destroy(); q.destroy(); e.close()
+assert status == [C.OK], status
+assert now < held - (8 << 20)
+for k in got:
+    np.testing.assert_array_equal(got[k], want[k])
+for k in want_t:
+    np.testing.assert_array_equal(res[k], want_t[k])
+print("serve-ok")
+"""
+
+
+@pytest.mark.parametrize("captured", [0, 1])
+def test_serving_takes_the_list_back_beside_the_batch_stream(captured):
+    """The serving worker needs the hand-over list's room, also while the batch
+    stream is being captured: the capture stays whole."""
+    if importlib.util.find_spec("torch") is None:
+        pytest.skip("torch not available")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", SERVE_CHILD, root, str(captured)],
+                         capture_output=True, text=True, timeout=100)
+    assert out.returncode == 0, out.stderr[-2000:]
+    assert "serve-ok" in out.stdout
