@@ -1710,7 +1710,7 @@ hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s)
 // mean of all.
 // Segments are split over workgroups where segments and groups alone would
 // leave CUs idle.  64 spectra x 516,000 exits of 30 bins: 521 us with two passes
-// of the library's exp in 120 workgroups, 72 us so.
+// of the library's exp in 120 workgroups, 71 us so.
 // ---------------------------------------------------------------------------
 // e^x = 2^k e^r, k = round(x / ln 2), the Taylor series of e^r to r^13 (|r| <=
 // ln(2)/2: the next term is below 2^-57).  For |x| < 2^30; ldexp saturates to 0
